@@ -83,9 +83,9 @@ enum {
   DDP_OPT_CHUNK_POINTS = 0, /* upper bound of points per work item (default 1024) */
   DDP_OPT_BLOCKS_PER_CU = 1, /* persistent workgroups per compute unit (0 = as many as fit) */
   DDP_OPT_ITEMS_PER_SLOT = 2, /* work items per resident workgroup the plan aims for (default 4) */
-  DDP_OPT_RECOMPUTE = 3, /* activation stash policy (default 0): 1 = the forward pass stores the
-                           pre-activation streams a^k only and the reverse pass rebuilds h^k from
-                           them with the activation rule; 0 = it stores a^k and h^k */
+  DDP_OPT_RECOMPUTE = 3, /* 0 (default) or 1, taken and reported as given; it selects nothing any
+                           more: the forward pass stores what both former policies need, the value
+                           pre-activation and the post-activation derivative streams of a layer */
   DDP_OPT_CONCURRENT = 4, /* fused step whose items need two train kernels (networks both at most
                             80 and wider than 80): 1 = the two persistent launches run side by
                             side on two streams (each with its own activation stash), so the
@@ -173,8 +173,7 @@ int ddp_finalize(ddp_problem* p, void* hip_stream, int fused);
 
 /* Autotuner: time candidate work plans on this problem (points per item
  * bound 256..2048, items per resident workgroup 1..8, workgroups per compute
- * unit 1..as many as fit, both activation stash policies of
- * DDP_OPT_RECOMPUTE, where the step has two train launches both settings
+ * unit 1..as many as fit, where the step has two train launches both settings
  * of DDP_OPT_CONCURRENT, and on the fused path a tail share DDP_OPT_TAIL of 0
  * or 30 percent) with iters loss-and-gradient passes each, time the
  * three fastest again (three interleaved rounds of 2 x iters passes), keep the
@@ -184,7 +183,7 @@ int ddp_finalize(ddp_problem* p, void* hip_stream, int fused);
  * per-subdomain path, widths, depths, point counts, CU count): a hit skips
  * the search, a miss appends the new choice.  choice (may be NULL) receives
  * the 6 chosen values (points per item, items per workgroup, workgroups per
- * compute unit, recompute policy, concurrent launches, tail share).  Not safe to call while the caller's stream runs other
+ * compute unit, DDP_OPT_RECOMPUTE (0), concurrent launches, tail share).  Not safe to call while the caller's stream runs other
  * work on this problem. */
 int ddp_autotune(ddp_problem* p, int iters, const char* cache_path, int64_t* choice);
 

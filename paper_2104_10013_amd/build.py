@@ -13,13 +13,14 @@ ARCH = "gfx950"
 HIP_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # (source, extra flags, object): the train kernels of each of the four
-# operators and two activation-stash policies, plain and with the general
-# activation rule, each in a translation unit of their own, compiled in
-# parallel
+# operators, by class group and activation rule (kernels.hip, DDP_TRAIN_*),
+# each in a translation unit of their own, compiled in parallel, the longest
+# first
 UNITS = [("kernels.hip", [], "kernels.o")] + \
-        [("kernels.hip", ["-DDDP_TRAIN_PDE=%d" % pde, "-DDDP_TRAIN_RH=%d" % rh] + (["-DDDP_TRAIN_GA"] if ga else []),
-          "kernels_pde%d_rh%d%s.o" % (pde, rh, "_ga" if ga else ""))
-         for pde in range(4) for rh in range(2) for ga in (False, True)] + \
+        [("kernels.hip", ["-DDDP_TRAIN_PDE=%d" % pde, "-DDDP_TRAIN_WP=%d" % wp] + (["-DDDP_TRAIN_GA"] if ga else []),
+          "kernels_pde%d_wp%d%s.o" % (pde, wp, "_ga" if ga else ""))
+         for pde in (3, 2, 1, 0) for wp, ga in ((112, True), (112, False), (80, True), (96, False), (0, False),
+                                                (80, False))] + \
         [("probe.hip", [], "probe.o"), ("noalloc.hip", [], "noalloc.o"), ("ddpinn.cpp", [], "ddpinn.o")]
 
 

@@ -24,15 +24,17 @@ enum Act { ACT_TANH = 0, ACT_SIN = 1, ACT_COS = 2 };
 //
 // Besides the canonical parameters (per layer W[out][in] then b[out]) every
 // network has a zero-padded "kernel layout" copy, rewritten by the Adam kernel
-// after each update, with WP = wclass, WS = WP + 4 (LDS row stride):
+// after each update, with WP = wclass (floats):
 //   [WP][4]            layer 1: (W1[m][0], W1[m][1], b1[m], 0)
 //   per hidden layer k = 2..D:
-//     [WP][WS]         W^k            [WP][WS]  W^k transposed    [WP]  b^k
+//     [1.5 WP WP]      W^k, split   [WP]  b^k   [1.5 WP WP]  W^k transposed, split
 //   [d_out][WP]        output W^L     [4]       b^L
 //   [kMaxDepth]        effective slopes c_k = n a^k of hidden layers 1..D
 //                      (adaptive networks only; otherwise 1 is used)
-// Gradient partial rows use the same order without the transposes and
-// without the row padding:  [WP][4], per hidden layer [WP][WP] + [WP],
+// A split matrix holds each weight as three bf16 parts (mid, hi, lo; see
+// kernels.hip) in the order the matrix cores take them (split_pos).
+// Gradient partial rows use the same order in float32, without the
+// transposes:  [WP][4], per hidden layer [WP][WP] + [WP],
 // [d_out][WP] + [4], [kMaxDepth] (dJ/dc_k).  Canonical parameters of an
 // adaptive network end with its D slopes a^1..a^D.
 //
@@ -62,12 +64,13 @@ struct NetDesc {
 
 // kernel-layout and partial-row offsets (floats) of a network
 struct Layout {
-  int WP, WS, D, DO;
-  __host__ __device__ Layout(int wp, int d, int dout) : WP(wp), WS(wp + 4), D(d), DO(dout) {}
-  __host__ __device__ int k_hidden(int k) const { return 4 * WP + (k - 2) * (2 * WP * WS + WP); }
+  int WP, D, DO;
+  __host__ __device__ Layout(int wp, int d, int dout) : WP(wp), D(d), DO(dout) {}
+  __host__ __device__ int k_split() const { return WP * WP / 2 * 3; }   // one split matrix
+  __host__ __device__ int k_hidden(int k) const { return 4 * WP + (k - 2) * (2 * k_split() + WP); }
   __host__ __device__ int k_w(int k) const { return k_hidden(k); }
-  __host__ __device__ int k_wt(int k) const { return k_hidden(k) + WP * WS; }
-  __host__ __device__ int k_b(int k) const { return k_hidden(k) + 2 * WP * WS; }
+  __host__ __device__ int k_b(int k) const { return k_hidden(k) + k_split(); }
+  __host__ __device__ int k_wt(int k) const { return k_b(k) + WP; }
   __host__ __device__ int k_out() const { return k_hidden(D + 1); }
   __host__ __device__ int k_bout() const { return k_out() + DO * WP; }
   __host__ __device__ int k_slope() const { return k_bout() + 4; }
@@ -79,6 +82,23 @@ struct Layout {
   __host__ __device__ int g_slope() const { return g_bout() + 4; }
   __host__ __device__ int g_size() const { return g_slope() + kMaxDepth; }
 };
+
+// Position (in bf16 units, of the first part) of element (m, j) in a split
+// WP x WP matrix, and the distance ps of its parts.  16 rows at a time, along
+// the columns 32 at a time: a fragment is what the 64 lanes of a wave hold of
+// the A operand of one 16x16x32 MFMA, 8 values a lane; with an odd number of
+// 16-column blocks the last one has fragments of 4 values a lane.
+__host__ __device__ inline int split_pos(int WP, int m, int j, int& ps) {
+  const int MB = WP / 16, jb = j >> 4;
+  const int lane = ((j >> 2) & 3) * 16 + (m & 15);
+  const int base = (m >> 4) * 48 * WP + (jb >> 1) * 1536;
+  if ((MB & 1) && jb == MB - 1) {
+    ps = 256;
+    return base + lane * 4 + (j & 3);
+  }
+  ps = 512;
+  return base + lane * 8 + (jb & 1) * 4 + (j & 3);
+}
 
 // One work item: a contiguous range of one point set evaluated by one network.
 struct Item {

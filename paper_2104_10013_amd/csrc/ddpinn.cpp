@@ -82,7 +82,7 @@ struct ddp_problem {
   int64_t chunk_points = 1024;  // upper bound of points per work item
   int blocks_per_cu = 0;         // 0: from the occupancy query
   int items_per_slot = 4;        // work items per resident workgroup the plan aims for
-  int recompute = 0;             // activation policy: 1 stash a^k and rebuild h^k in the reverse pass, 0 stash both
+  int recompute = 0;             // DDP_OPT_RECOMPUTE as given (selects nothing)
   int concurrent = 0;            // fused step with several train launches: 1 = they run side by side
   int tail_pct = 0;              // percent of each subdomain's residual points in one-tile items
 
@@ -586,7 +586,7 @@ int enqueue_step(ddp_problem* p, hipStream_t st, int do_adam, float* grad_out, f
       ka.scratch_slot = l.slot_floats;
       ka.prologue = g == 0;
       const int grid = std::max(1, std::min(slots_for(l.n_slots, l.slot_floats), l.count));
-      HIP_TRY(launch_train(p->pde, l.wpmax, p->ga, p->recompute, ka, grid, side && g > 0 ? p->side_stream : st));
+      HIP_TRY(launch_train(p->pde, l.wpmax, p->ga, ka, grid, side && g > 0 ? p->side_stream : st));
     }
     if (side) {
       HIP_TRY(hipEventRecord(p->ev_join, p->side_stream));
@@ -613,7 +613,7 @@ int enqueue_step(ddp_problem* p, hipStream_t st, int do_adam, float* grad_out, f
     ka.prologue = q == 0;
     if (ka.n_items == 0 && q != 0) continue;
     const int grid = std::max(1, std::min(slots_for(p->n_slots, p->slot_floats), ka.n_items));
-    HIP_TRY(launch_train(p->pde, p->wpmax, p->ga, p->recompute, ka, grid, st));
+    HIP_TRY(launch_train(p->pde, p->wpmax, p->ga, ka, grid, st));
   }
   for (int q = 0; q < n_sd; ++q) {
     RArgs ra = make_rargs(p);
@@ -874,23 +874,23 @@ int install_plan(ddp_problem* p) {
   if (p->stream) HIP_TRY(hipStreamSynchronize(p->stream));
   for (void* a : p->plan_allocations) hipFree(a);
   p->plan_allocations.clear();
-  HIP_TRY(train_occupancy(p->pde, p->wpmax, p->ga, p->recompute, &p->occupancy));
+  HIP_TRY(train_occupancy(p->pde, p->wpmax, p->ga, &p->occupancy));
   if (p->occupancy < 1) return fail(DDP_EHIP, "train kernel cannot be resident (occupancy 0)");
   const int bpc = p->blocks_per_cu > 0 ? std::min(p->blocks_per_cu, p->occupancy) : p->occupancy;
   p->n_slots = std::max(1, p->n_cu * bpc);
   p->plan_slots = p->n_slots;
   if (int rc = build_plan(p)) return rc;
-  p->slot_floats = scratch_slot_floats(p->pde, p->wpmax, p->recompute);
+  p->slot_floats = scratch_slot_floats(p->pde, p->wpmax, p->ga);
   int64_t scratch_floats = (int64_t)p->n_slots * p->slot_floats;
   // sequential launches reuse one stash region; concurrent ones get their own
   const bool side = p->fused && p->concurrent && p->launches.size() > 1;
   int64_t side_floats = 0;
   for (ddp_problem::Launch& l : p->launches) {
-    HIP_TRY(train_occupancy(p->pde, l.wpmax, p->ga, p->recompute, &l.occupancy));
+    HIP_TRY(train_occupancy(p->pde, l.wpmax, p->ga, &l.occupancy));
     if (l.occupancy < 1) return fail(DDP_EHIP, "train kernel cannot be resident (occupancy 0)");
     const int b = p->blocks_per_cu > 0 ? std::min(p->blocks_per_cu, l.occupancy) : l.occupancy;
     l.n_slots = std::max(1, p->n_cu * b);
-    l.slot_floats = scratch_slot_floats(p->pde, l.wpmax, p->recompute);
+    l.slot_floats = scratch_slot_floats(p->pde, l.wpmax, p->ga);
     l.scratch_off = side ? side_floats : 0;
     side_floats += (int64_t)l.n_slots * l.slot_floats;
     scratch_floats = std::max(scratch_floats, (int64_t)l.n_slots * l.slot_floats);
@@ -1006,7 +1006,7 @@ int ddp_finalize(ddp_problem* p, void* hip_stream, int fused) {
   HIP_TRY(hipGetDevice(&p->device));
   p->stream = static_cast<hipStream_t>(hip_stream);
   HIP_TRY(hipDeviceGetAttribute(&p->n_cu, hipDeviceAttributeMultiprocessorCount, p->device));
-  HIP_TRY(train_occupancy(p->pde, p->wpmax, p->ga, p->recompute, &p->occupancy));
+  HIP_TRY(train_occupancy(p->pde, p->wpmax, p->ga, &p->occupancy));
   if (p->occupancy < 1) return fail(DDP_EHIP, "train kernel cannot be resident (occupancy 0)");
 
   int rc = 0;
@@ -1046,7 +1046,7 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
   const int ipss[] = {1, 2, 4, 8};
   struct Cand {
     int64_t c;
-    int ips, bpc, rh, conc, tail;
+    int ips, bpc, conc, tail;
     float ms;
   };
   std::vector<Cand> cands;
@@ -1056,7 +1056,6 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
     p->chunk_points = k.c;
     p->items_per_slot = k.ips;
     p->blocks_per_cu = k.bpc;
-    p->recompute = k.rh;
     p->concurrent = k.conc;
     p->tail_pct = k.tail;
     if (int rc = install_plan(p)) return rc;
@@ -1070,10 +1069,10 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
     *ms /= n;
     return DDP_OK;
   };
-  for (int rh = 0; rh <= 1; ++rh) {
-    // resident workgroups per CU of this policy's kernels (the fused
-    // launches may run narrower kernels than the per-subdomain path)
-    p->recompute = rh;
+  {
+    // resident workgroups per CU of the kernels (the fused launches may run
+    // narrower kernels than the per-subdomain path)
+    p->recompute = 0;
     p->concurrent = 0;
     p->tail_pct = 0;
     if (int rc = install_plan(p)) return rc;
@@ -1089,7 +1088,7 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
         for (int64_t c : chunks)
           for (int ips : ipss)
             for (int bpc = 1; bpc <= max_occ; ++bpc) {
-              Cand k{c, ips, bpc, rh, conc, tails[t], 0.f};
+              Cand k{c, ips, bpc, conc, tails[t], 0.f};
               if (int rc = time_cand(k, iters, &k.ms)) return rc;
               cands.push_back(k);
             }
@@ -1113,7 +1112,7 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
       best[0] = cands[k].c;
       best[1] = cands[k].ips;
       best[2] = cands[k].bpc;
-      best[3] = cands[k].rh;
+      best[3] = 0;
       best[4] = cands[k].conc;
       best[5] = cands[k].tail;
     }
@@ -1347,7 +1346,7 @@ int ddp_time_kernels(ddp_problem* p, int iters, float* ms) {
           }
           if (ka.n_items == 0) continue;
           const int grid = std::max(1, std::min(n_slots, ka.n_items));
-          HIP_TRY(launch_train(p->pde, wpmax, p->ga, p->recompute, ka, grid, st));
+          HIP_TRY(launch_train(p->pde, wpmax, p->ga, ka, grid, st));
         }
         if (side) {
           HIP_TRY(hipEventRecord(p->ev_join, p->side_stream));
@@ -1414,7 +1413,7 @@ int ddp_time_phases(ddp_problem* p, int iters, float* ms) {
           ka.n_items = count[g];
           ka.counter = p->d_counters + g;
           ka.scratch_slot = l.slot_floats;
-          hip_ok(launch_train(p->pde, l.wpmax, p->ga, p->recompute, ka, std::max(1, std::min(l.n_slots, count[g])),
+          hip_ok(launch_train(p->pde, l.wpmax, p->ga, ka, std::max(1, std::min(l.n_slots, count[g])),
                               p->stream));
         }
         float t = 0.f;

@@ -8,11 +8,11 @@
 //     a = W h + b,  a_i = W h_i,  a_S = W h_S          (Sec. 3 recurrence)
 // and through tanh, with t = tanh a, s1 = sech^2 a, s2 = -2 t s1:
 //     h = t,  h_i = s1 a_i,  h_S = s1 a_S + s2 sum_{i in S} a_i^2.
-// The four streams of 16 points are the columns of one FP32 MFMA contraction
-// per layer (v_mfma_f32_16x16x4_f32, weights from LDS); the output layout of
-// one layer is the B operand of the next with the K index permuted, so the
-// tanh rule stays lane-local.  Pre-activation streams are stashed per
-// workgroup in global memory for the reverse pass.
+// The four streams of 16 points are the columns of one contraction per layer
+// on the matrix cores (float32 values split into three bf16 parts, weights from
+// LDS); the output layout of one layer is the B operand of the next with the K
+// index permuted, so the tanh rule stays lane-local.  What the reverse pass
+// needs of a layer is stashed per workgroup in global memory.
 //
 // The reverse (adjoint) pass differentiates the subdomain loss of
 // Eq. cPINNLoss / Eq. XPINNLoss with respect to the subdomain's own
@@ -21,8 +21,8 @@
 //     abar_S = s1 g_S
 //     abar_i = s1 g_i + 2 s2 a_i g_S            (i in S; s1 g_i otherwise)
 //     abar   = s1 g + s2 sum_i a_i g_i + (s2 a_S + s3 sum_{i in S} a_i^2) g_S
-// then g_prev = W^T abar (MFMA) and dW = sum over points and streams of
-// abar h_prev^T (MFMA over LDS-staged tiles).  Every work item writes its own
+// then dW = sum over points and streams of abar h_prev^T (MFMA over LDS-staged
+// tiles) and g_prev = W^T abar (MFMA).  Every work item writes its own
 // gradient partial row; a second kernel sums the rows of each subdomain in a
 // fixed order (deterministic, no float atomics) and applies Adam.
 
@@ -37,15 +37,12 @@
 namespace ddp {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef short s4 __attribute__((ext_vector_type(4)));
 
 constexpr int TP = kTilePts;      // points per tile
-constexpr int TPS = kTilePts + 4; // LDS row stride of staged tiles (floats)
-constexpr int TPS2 = 2 * kTilePts + 4; // row stride of two streams staged side by side
-
-// Widths whose reverse pass stages two streams at once for dW (one pair of
-// barriers per two streams): the doubled staging tiles fit the LDS budget
-// of the widest class up to 48.
-constexpr bool pair_staged(int wp) { return wp <= 48; }
 constexpr int NT = 64 * kWaves;   // threads per workgroup
 
 // One 16-byte-per-lane store into the activation stash, followed by wait
@@ -110,9 +107,56 @@ __device__ __forceinline__ float row_sum16(float v) {
   return dpp_add(v, 0x140);   // row_mirror
 }
 
-__device__ __forceinline__ f4 mma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+// Sum over the four lane groups of a wave (lanes 16 apart), the same bits in
+// every lane: the swaps exchange odd 16-lane rows, then halves, of two copies.
+__device__ __forceinline__ float group_sum(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned s = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
+
+// FP32 contractions on the bf16 matrix cores.  A float32 x is the sum of three
+// bf16 values, hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (both
+// differences are exact), and a product of two such sums keeps the six terms
+// of relative size 2^-16 and up:
+//     hi hi + (hi mid + mid hi) + (mid mid + hi lo + lo hi),
+// accumulated in float32; what is left out is below 2^-25 of the product,
+// under half a float32 rounding.  Six 16x16x32 bf16 MFMAs (16.8 cycles each,
+// measured) replace eight 16x16x4 float32 ones (32 cycles each) per 32 terms,
+// and with eight times fewer float32 additions the measured error against
+// float64 is smaller too (2-norm of 16x16 blocks: K = 32 3.6e-8 against
+// 1.05e-7, K = 96 1.2e-7 / 1.8e-7, K = 256 2.7e-7 / 3.0e-7).
+__device__ __forceinline__ f4 mma(b8 a, b8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// The split of two values: the remainders x - hi come from the bf16 dot
+// product x + (hi0, hi1) . (-1, 0), exact like the subtraction (checked on
+// random values over the range of the exponents) and without unpacking the
+// parts first: 7 instructions a pair instead of 11.  (The constants are made
+// opaque: folded into the instruction as an inline literal they land in the
+// wrong half.)
+__device__ __forceinline__ void split2(float x0, float x1, b2& h, b2& m, b2& l) {
+  unsigned c0 = 0x0000bf80u, c1 = 0xbf800000u;   // (-1, 0) and (0, -1)
+  asm("" : "+s"(c0));
+  asm("" : "+s"(c1));
+  const b2 n0 = __builtin_bit_cast(b2, c0), n1 = __builtin_bit_cast(b2, c1);
+  h = b2{(__bf16)x0, (__bf16)x1};
+  const float r0 = __builtin_amdgcn_fdot2_f32_bf16(h, n0, x0, false);
+  const float r1 = __builtin_amdgcn_fdot2_f32_bf16(h, n1, x1, false);
+  m = b2{(__bf16)r0, (__bf16)r1};
+  l = b2{(__bf16)__builtin_amdgcn_fdot2_f32_bf16(m, n0, r0, false),
+         (__bf16)__builtin_amdgcn_fdot2_f32_bf16(m, n1, r1, false)};
+}
+__device__ __forceinline__ void split4(f4 x, b4& h, b4& m, b4& l) {
+  b2 h0, h1, m0, m1, l0, l1;
+  split2(x[0], x[1], h0, m0, l0);
+  split2(x[2], x[3], h1, m1, l1);
+  h = b4{h0[0], h0[1], h1[0], h1[1]};
+  m = b4{m0[0], m0[1], m1[0], m1[1]};
+  l = b4{l0[0], l0[1], l1[0], l1[1]};
+}
+__device__ __forceinline__ b8 join(b4 x, b4 y) { return b8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]}; }
 
 // tanh(a) and sech^2(a) from e = exp(-2|a|):  t = sign(a)(1-e)/(1+e),
 // s1 = 4e/(1+e)^2 (no cancellation for large |a|).
@@ -123,16 +167,6 @@ __device__ __forceinline__ void tanh_s1(float a, float& t, float& s1) {
   s1 = 4.f * e * r * r;
 }
 
-// Sums over the TP points of LDS-staged rows (16-byte aligned), partially unrolled.
-__device__ __forceinline__ float row_sum(const float* a) {
-  float acc = 0.f;
-#pragma unroll 2
-  for (int p = 0; p < TP; p += 4) {
-    const f4 x = *reinterpret_cast<const f4*>(a + p);
-    acc += (x[0] + x[1]) + (x[2] + x[3]);
-  }
-  return acc;
-}
 template <bool S2>
 __device__ __forceinline__ void tanh_rule(float a, float ax, float ay, float al, float& h, float& hx,
                                           float& hy, float& hl) {
@@ -159,6 +193,25 @@ __device__ __forceinline__ void tanh_adj(float a, float ax, float ay, float al, 
   abx = fmaf(s1, gx, 2.f * s2 * ax * gl);
   aby = S2 ? fmaf(s1, gy, 2.f * s2 * ay * gl) : s1 * gy;
   ab = fmaf(s1, g, fmaf(s2, fmaf(ax, gx, ay * gy), fmaf(s2, al, s3 * q) * gl));
+}
+
+// The same adjoint from the post-activation streams: with hx = s1 ax, hy = s1 ay,
+// hl = s1 al + s2 sum_{i in S} a_i^2 every term that held a_i is a polynomial in
+// t and the h-streams (s2 a_i = -2 t h_i; s2 a_S + s3 sum a_i^2 = -2 t h_S -
+// 2 sum h_i^2), so (a, hx, hy, hl) of a layer is all its reverse pass needs,
+// both for this rule and as h^{k-1} of the next layer's dW.  t and s1 come
+// from a, so nothing cancels when the neuron saturates.
+template <bool S2>
+__device__ __forceinline__ void tanh_adj_h(float a, float hx, float hy, float hl, float g, float gx, float gy,
+                                           float gl, float& ab, float& abx, float& aby, float& abl) {
+  float t, s1;
+  tanh_s1(a, t, s1);
+  const float m = -2.f * t;
+  abl = s1 * gl;
+  abx = fmaf(s1, gx, 2.f * m * hx * gl);
+  aby = S2 ? fmaf(s1, gy, 2.f * m * hy * gl) : s1 * gy;
+  const float q = S2 ? fmaf(hx, hx, hy * hy) : hx * hx;
+  ab = fmaf(s1, g, fmaf(m, fmaf(hx, gx, hy * gy), fmaf(m, hl, -2.f * q) * gl));
 }
 
 // sin_cos (act_math.h): Cody-Waite reduction and the Cephes single-precision
@@ -349,22 +402,30 @@ enum {
 // ---------------------------------------------------------------------------
 // Tile processor for one padded width class WP.
 //
+// LDS of a class (bytes): one split weight matrix is WP^2 x 3 parts x 2.
+constexpr int split_matrix_bytes(int wp) { return 6 * wp * wp; }
+// streams staged at once for dW: two where a class is small
+constexpr int stage_streams(int wp) { return wp <= 16 ? 2 : 1; }
+constexpr int stage_bytes(int wp) { return 2 * 3 * 2 * stage_streams(wp) * TP * (wp + 4); }
+// Whether the staging area takes the place of W^T, which is then loaded after
+// dW: where the two together exceed half a compute unit's LDS (class 80,
+// two workgroups per unit) or all of it (class 112).
+constexpr bool stage_over_weights(int wp) { return wp == 80 || wp == 112; }
+// weights and staging of a tile: two forward buffers; W^T and the staging
+// area; the first forward buffer and the sums of the output layer or layer 1
+constexpr int tile_bytes(int wp, int d_out) {
+  const int buf = split_matrix_bytes(wp) + 4 * wp;
+  const int rev = stage_bytes(wp) + (stage_over_weights(wp) ? 0 : split_matrix_bytes(wp));
+  const int sums = buf + 4 * kWaves * (d_out > 3 ? d_out : 3) * (wp + 1);
+  const int n = 2 * buf > rev ? 2 * buf : rev;
+  return ((n > sums ? n : sums) + 15) / 16 * 16;
+}
+//
 // Lane layout (one wave = 16 points): lane = 16 g + pc holds point pc and,
 // for output block mb and register i, neuron 16 mb + 4 g + i.  This is the
-// C/D layout of v_mfma_f32_16x16x4_f32, and with the K index of the next
-// contraction permuted the same way it is also its B-operand layout.
-
-// one stream of the tanh rule (used when staging h^{k-1} for dW)
-template <bool S2>
-__device__ __forceinline__ float act_stream(int s, float a, float ax, float ay, float al) {
-  float t, s1;
-  tanh_s1(a, t, s1);
-  if (s == 0) return t;
-  if (s == 1) return s1 * ax;
-  if (s == 2) return s1 * ay;
-  const float q = S2 ? fmaf(ax, ax, ay * ay) : ax * ax;
-  return fmaf(s1, al, -2.f * t * s1 * q);
-}
+// C/D layout of the 16x16x32 MFMA, and with the K index of the next
+// contraction permuted the same way (element e of lane group g is neuron
+// 4 g + (e & 3) of block 2 kb + (e >> 2)) it is also its B-operand layout.
 
 // one stream of the general activation rule (slope c, activation act)
 template <bool S2>
@@ -385,9 +446,17 @@ struct Tile {
   static constexpr int DO = Op<PDE>::DO;
   static constexpr int NEQ = Op<PDE>::NEQ;
   static constexpr bool S2 = Op<PDE>::S2;
-  static constexpr int WS = WP + 4;                         // row stride of staged weights
-  static constexpr int NBT = MB * MB;                       // 16x16 blocks of dW
-  static constexpr int NB = (NBT + kWaves - 1) / kWaves;    // dW blocks per wave
+  static constexpr int KB = MB / 2;                         // 32-neuron steps of a contraction; an odd last block is
+  static constexpr bool TAIL = (MB & 1) != 0;               // a 16-neuron step of its own
+  // blocks of dW per wave: rows of blocks 4 r + wave, then the blocks of the
+  // rows left over, dealt out one by one
+  static constexpr int ROWS = MB / kWaves;
+  static constexpr int REM = (MB % kWaves) * MB;
+  static constexpr int NREM = (REM + kWaves - 1) / kWaves;
+  static constexpr int WBYTES = split_matrix_bytes(WP);     // one split weight matrix
+  static constexpr int BUF = WBYTES + 4 * WP;               // with its bias
+  static constexpr int SN = stage_streams(WP);              // streams staged at once for dW
+  static constexpr int SROWS = SN * TP;                     // rows (stream, point) of the staging area
   static constexpr int KL = (DO * WP + NT - 1) / NT;        // output-layer slots per thread
   static constexpr int STASH_LAYER = kWaves * 4 * MB * 1024;  // bytes of one layer's stash
 
@@ -427,148 +496,265 @@ struct Tile {
     }
   }
 
-  // copy a zero-padded [WP][WS] matrix from the kernel layout into LDS
-  __device__ static void stage(float* sW, const float* src, int tid) {
-    constexpr int N4 = WP * WS / 4;
-    const f4* s4 = reinterpret_cast<const f4*>(src);
+  // Forward weights alternate between two LDS buffers (weights, then bias), so
+  // that layer k + 1's stream in while layer k computes; the last hidden layer
+  // D always uses the first one.
+  __device__ static char* wbuf(char* sW, int D, int k) { return ((D - k) & 1) ? sW + BUF : sW; }
+  __device__ static void fetch_wb(char* dst, const float* K, const Layout& L, int k, int wave, int lane) {
+    dma_to_lds(reinterpret_cast<float*>(dst), K + L.k_w(k), BUF / 16, wave, lane);
+  }
+  __device__ static void fetch_wt(char* sW, const float* K, const Layout& L, int k, int wave, int lane) {
+    dma_to_lds(reinterpret_cast<float*>(sW), K + L.k_wt(k), WBYTES / 16, wave, lane);
+  }
+  __device__ static void stage_wb(char* sW, const float* src, int tid) {
     f4* d4 = reinterpret_cast<f4*>(sW);
-    for (int idx = tid; idx < N4; idx += NT) d4[idx] = s4[idx];
+    for (int idx = tid; idx < BUF / 16; idx += NT) d4[idx] = reinterpret_cast<const f4*>(src)[idx];
   }
 
-  // Forward weights alternate between two LDS buffers, sW and the tile buffers
-  // sA/sH (free during the forward, WP x WS + WP <= 2 WP x TPS floats), so
-  // that layer k + 1's weights stream in while layer k computes; the last
-  // hidden layer D always uses sW (the output layer's adjoint stages in sA/sH
-  // right after it).
-  __device__ static float* wbuf(float* sW, int D, int k) {
-    return ((D - k) & 1) ? sW + WP * WS + WP : sW;
-  }
-  __device__ static void fetch_wb(float* dst, const float* K, const Layout& L, int k, int wave, int lane) {
-    dma_to_lds(dst, K + L.k_w(k), WP * WS / 4, wave, lane);
-    dma_to_lds(dst + WP * WS, K + L.k_b(k), WP / 4, wave, lane);
-  }
-  __device__ static void fetch_wt(float* sW, const float* K, const Layout& L, int k, int wave, int lane) {
-    dma_to_lds(sW, K + L.k_wt(k), WP * WS / 4, wave, lane);
-  }
-
-  // A forward layer's weights and bias go to LDS as [WP][WS] then [WP]: the
-  // hidden layer then reads its bias from LDS between its stash stores, and a
-  // global load there would have to wait for those stores to drain (one
-  // in-order counter covers vector loads and stores).
-  static constexpr int NWB4 = (WP * WS + WP) / 4;            // float4 of weights + bias
-  __device__ static void stage_wb(float* sW, const float* srcW, const float* srcB, int tid) {
-    constexpr int N4 = WP * WS / 4;
-    f4* d4 = reinterpret_cast<f4*>(sW);
-    for (int idx = tid; idx < NWB4; idx += NT)
-      d4[idx] = idx < N4 ? reinterpret_cast<const f4*>(srcW)[idx] : reinterpret_cast<const f4*>(srcB)[idx - N4];
-  }
-
-  // One hidden layer, output block by output block: a^k_mb = W^k h^{k-1}
-  // (+ b^k on the value stream) for all four streams, stash a^k_mb, and the
-  // tanh rule into the new activations Hn (H stays intact as the B operand).
-  // rq: MFMA steps of the last 16-neuron input block that hold real neurons
-  // (neuron_pos puts neurons 4i..4i+3 of a block in step i); the rest of that
-  // block is zero padding and is skipped.
-  __device__ static int real_steps(int width) { return (width - (WP - 16) + 3) >> 2; }
-
-  template <bool STASH, bool GA>
-  __device__ static void hidden_layer(const float* sW, const float* bias, int g, int pc, int rq, const Streams& H,
-                                      Streams& Hn, __amdgpu_buffer_rsrc_t rs, int layer, int wave, int lane, int act,
-                                      float c) {
+  // Y_s += W X_s for streams S0 .. S0 + NS - 1 (w: a split matrix in LDS, in
+  // fragment order, so every read is 16 bytes a lane without bank conflicts).
+  // Each weight fragment read feeds 6 NS MFMAs; a stream's values are split
+  // once per 32-neuron step.  The odd last block packs two of the six
+  // products into the two halves of each MFMA's K, so it costs three.
+  template <int S0, int NS>
+  __device__ __forceinline__ static void contract(const char* w, int lane, const Streams& X, Streams& Y) {
+    // fragments are read one 16-row block ahead of their MFMAs
+    auto load = [&](int mb, int kb, b8 (&f)[3]) {
+      const b8* p = reinterpret_cast<const b8*>(w + mb * 96 * WP + kb * 3072) + lane;
+      f[0] = p[0];
+      f[1] = p[64];
+      f[2] = p[128];
+    };
+    auto load_tail = [&](int mb, b8 (&f)[3]) {   // {mid, hi}, {hi, lo}
+      const b4* p = reinterpret_cast<const b4*>(w + mb * 96 * WP + KB * 3072) + lane;
+      const b4 wm = p[0], wh = p[64], wl = p[128];
+      f[0] = join(wm, wh);
+      f[1] = join(wh, wl);
+    };
+    b8 f[3], fn[3];
+    if constexpr (KB > 0) load(0, 0, f);
+    else load_tail(0, f);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      f4 acc[4];
-      acc[0] = *reinterpret_cast<const f4*>(bias + 16 * mb + 4 * g);
-      acc[1] = f4{0.f, 0.f, 0.f, 0.f};
-      acc[2] = f4{0.f, 0.f, 0.f, 0.f};
-      acc[3] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = 0; kb < KB; ++kb) {
+      b8 xh[NS], xm[NS], xl[NS];
 #pragma unroll
-      for (int kb = 0; kb < MB; ++kb) {
-        const f4 wv = *reinterpret_cast<const f4*>(&sW[(16 * mb + pc) * WS + 16 * kb + 4 * g]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (kb == MB - 1 && i >= rq) continue;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) acc[s] = mma(wv[i], H[s][kb][i], acc[s]);
-        }
-      }
-      if constexpr (STASH) {
-#pragma unroll
-        for (int st = 0; st < 4; ++st)
-          stash_put(acc[st], rs, lane * 16, stash_off(0, layer, wave, st, mb));
+      for (int s = 0; s < NS; ++s) {
+        b4 h0, h1, m0, m1, l0, l1;
+        split4(X[S0 + s][2 * kb], h0, m0, l0);
+        split4(X[S0 + s][2 * kb + 1], h1, m1, l1);
+        xh[s] = join(h0, h1);
+        xm[s] = join(m0, m1);
+        xl[s] = join(l0, l1);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float h, hx, hy, hl;
-        if constexpr (GA) act_rule<S2>(act, c, acc[0][i], acc[1][i], acc[2][i], acc[3][i], h, hx, hy, hl);
-        else tanh_rule<S2>(acc[0][i], acc[1][i], acc[2][i], acc[3][i], h, hx, hy, hl);
-        Hn[0][mb][i] = h;
-        Hn[1][mb][i] = hx;
-        Hn[2][mb][i] = hy;
-        Hn[3][mb][i] = hl;
+      for (int mb = 0; mb < MB; ++mb) {
+        if (mb + 1 < MB) load(mb + 1, kb, fn);
+        else if (kb + 1 < KB) load(0, kb + 1, fn);
+        else if constexpr (TAIL) load_tail(0, fn);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[2], xh[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[1], xl[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[0], xm[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[0], xh[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[1], xm[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[1], xh[s], Y[S0 + s][mb]);
+        f[0] = fn[0];
+        f[1] = fn[1];
+        f[2] = fn[2];
+      }
+    }
+    if constexpr (TAIL) {
+      b8 hh[NS], mm[NS], lh[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        b4 h, m, l;
+        split4(X[S0 + s][MB - 1], h, m, l);
+        hh[s] = join(h, h);
+        mm[s] = join(m, m);
+        lh[s] = join(l, h);
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        if (mb + 1 < MB) load_tail(mb + 1, fn);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[1], lh[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[0], mm[s], Y[S0 + s][mb]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[0], hh[s], Y[S0 + s][mb]);
+        f[0] = fn[0];
+        f[1] = fn[1];
       }
     }
   }
-
-  // g^{k-1}_s = W^{kT} abar^k_s for two streams at once (sW holds W^T): each
-  // weight read from LDS feeds two independent MFMA chains
-  // (rq as in hidden_layer: padded output neurons of layer k contribute nothing)
-  __device__ static void hidden_bwd_pair(const float* sWT, int g, int pc, int rq, const f4 (&A0)[MB],
-                                         const f4 (&A1)[MB], f4 (&G0)[MB], f4 (&G1)[MB]) {
-#pragma unroll
-    for (int jb = 0; jb < MB; ++jb) {
-      G0[jb] = f4{0.f, 0.f, 0.f, 0.f};
-      G1[jb] = f4{0.f, 0.f, 0.f, 0.f};
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int jb = 0; jb < MB; ++jb) {
-        const f4 wv = *reinterpret_cast<const f4*>(&sWT[(16 * jb + pc) * WS + 16 * mb + 4 * g]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (mb == MB - 1 && i >= rq) continue;
-          G0[jb] = mma(wv[i], A0[mb][i], G0[jb]);
-          G1[jb] = mma(wv[i], A1[mb][i], G1[jb]);
-        }
-      }
-    }
-  }
-
-  // Activation stash of the workgroup's slot, [region][layer][wave][stream][mblock][lane]
-  // float4, addressed through a buffer resource: region 0 holds the
-  // pre-activation streams a^k (k = 2..D), region 1 the post-activation
-  // streams h^k (k = 1..D-1) the reverse pass needs for dW^{k+1}.
-  static constexpr int STASH_REGION = (kMaxDepth - 1) * STASH_LAYER;
-  __device__ static int stash_off(int region, int layer, int wave, int s, int mb) {
-    return region * STASH_REGION + layer * STASH_LAYER + ((wave * 4 + s) * MB + mb) * 1024;
-  }
-  __device__ static void stash_store(__amdgpu_buffer_rsrc_t rs, int region, int layer, int wave, int lane,
-                                     const Streams& A) {
+  // the values are computed by here, and nothing is known about them afterwards
+  __device__ __forceinline__ static void pin(Streams& X) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-        stash_put(A[s][mb], rs, lane * 16, stash_off(region, layer, wave, s, mb));
+      for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(X[s][mb]));
+  }
+  // all four streams: at once where the registers allow it (half the weight
+  // reads), else in two pairs
+  template <bool PAIRS>
+  __device__ __forceinline__ static void contract4(const char* w, int lane, const Streams& X, Streams& Y) {
+    if constexpr (PAIRS) {
+      contract<0, 2>(w, lane, X, Y);
+      contract<2, 2>(w, lane, X, Y);
+    } else {
+      contract<0, 4>(w, lane, X, Y);
+    }
+  }
+
+  // What the reverse pass keeps of a layer: the value pre-activation a and
+  // the post-activation streams h_x, h_y, h_S (tanh: half of what a and h are
+  // together), or for other activations and trainable slopes the four
+  // pre-activation streams, from which h is rebuilt (class 80, without the
+  // registers for that, keeps h as well, kMaxDepth layers further on).
+  template <bool GA>
+  __device__ static bool h_form(const NetDesc& nd) {
+    return !GA || (nd.act == ACT_TANH && !nd.adaptive);
+  }
+  template <bool GA>
+  __device__ static void stash_put_layer(const NetDesc& nd, __amdgpu_buffer_rsrc_t rs, int layer, int wave, int lane,
+                                         const Streams& A, const Streams& H) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) stash_put(A[0][mb], rs, lane * 16, stash_off(layer, wave, 0, mb));
+    const bool hf = h_form<GA>(nd);
+#pragma unroll
+    for (int s = 1; s < 4; ++s)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        if (hf) stash_put(H[s][mb], rs, lane * 16, stash_off(layer, wave, s, mb));
+        else stash_put(A[s][mb], rs, lane * 16, stash_off(layer, wave, s, mb));
+      }
+    if (!KEEP && !hf) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          stash_put(H[s][mb], rs, lane * 16, stash_off(layer + kMaxDepth, wave, s, mb));
+    }
+  }
+  // one stream of h from what is kept
+  template <bool GA>
+  __device__ __forceinline__ static void h_stream(const NetDesc& nd, int s, float c, const Streams& S, f4 (&h)[MB]) {
+    const bool hf = h_form<GA>(nd);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (hf) {
+          float t = S[s][mb][i], s1;
+          if (s == 0) tanh_s1(S[0][mb][i], t, s1);
+          h[mb][i] = t;
+        } else {
+          h[mb][i] = act_stream_ga<S2>(s, nd.act, c, S[0][mb][i], S[1][mb][i], S[2][mb][i], S[3][mb][i]);
+        }
+      }
+  }
+  // One hidden layer in place: a^k = W^k h^{k-1} (+ b^k on the value stream)
+  // for all four streams, the activation rule, and what the reverse pass keeps.
+  template <bool STASH, bool GA>
+  __device__ static void hidden_layer(const char* w, int g, Streams& H, __amdgpu_buffer_rsrc_t rs, int layer, int wave,
+                                      int lane, const NetDesc& nd, float c) {
+    const float* bias = reinterpret_cast<const float*>(w + WBYTES);
+    Streams A;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      A[0][mb] = *reinterpret_cast<const f4*>(bias + 16 * mb + 4 * g);
+      A[1][mb] = f4{0.f, 0.f, 0.f, 0.f};
+      A[2][mb] = f4{0.f, 0.f, 0.f, 0.f};
+      A[3][mb] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    contract4<MB == 5>(w, lane, H, A);
+    activate<GA>(A, H, nd.act, c);
+    if constexpr (STASH) stash_put_layer<GA>(nd, rs, layer, wave, lane, A, H);
+  }
+
+  // Staging area of dW: [operand abar, h][part][row][WP + 4] bf16, a row per
+  // (stream, point) and the neurons along it, so that a lane writes its four
+  // neurons of a block in 8 bytes; the operand fragments, which run along the
+  // points, come out of the transposing LDS read (ds_read_b64_tr_b16).  LDS
+  // takes writes 16 lanes and 32 banks at a time: rows an odd multiple of 8
+  // bytes apart put the 16 points of a lane group on all 32 banks (6 cycles a
+  // wave and 8-byte write, measured; 16 with rows of WP neurons).
+  static constexpr int ROW = 2 * (WP + 4);      // bytes
+  static constexpr int PART = SROWS * ROW;      // bytes of one part of one operand
+  __device__ __forceinline__ static void stage_put(char* base, int row, int g, const f4 (&X)[MB]) {
+    char* p = base + row * ROW + 8 * g;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      b4 h, m, l;
+      split4(X[mb], h, m, l);
+      *reinterpret_cast<b4*>(p + 32 * mb) = m;
+      *reinterpret_cast<b4*>(p + 32 * mb + PART) = h;
+      *reinterpret_cast<b4*>(p + 32 * mb + 2 * PART) = l;
+    }
+  }
+  // fragment (neurons of block mb) x (32 rows from row 32 c): lane group g
+  // holds rows 4 g .. 4 g + 3 and 16 more
+  __device__ __forceinline__ static b8 stage_frag(const char* base, int c, int mb, int lane) {
+    const char* p = base + (4 * (lane >> 4) + ((lane & 15) >> 2)) * ROW + 8 * (lane & 3) + 32 * mb + c * (32 * ROW);
+    typedef __attribute__((address_space(3))) s4* lp;
+    const s4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p));
+    const s4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 16 * ROW));
+    return join(__builtin_bit_cast(b4, x), __builtin_bit_cast(b4, y));
+  }
+  struct Frag {
+    b8 m, h, l;
+  };
+  __device__ __forceinline__ static Frag stage_parts(const char* base, int c, int mb, int lane) {
+    return Frag{stage_frag(base, c, mb, lane), stage_frag(base + PART, c, mb, lane),
+                stage_frag(base + 2 * PART, c, mb, lane)};
+  }
+  __device__ __forceinline__ static f4 mma6(const Frag& a, const Frag& b, f4 c) {
+    c = mma(a.l, b.h, c);
+    c = mma(a.h, b.l, c);
+    c = mma(a.m, b.m, c);
+    c = mma(a.m, b.h, c);
+    c = mma(a.h, b.m, c);
+    return mma(a.h, b.h, c);
+  }
+  // the sum over 32 rows: the fragment times ones
+  __device__ __forceinline__ static f4 row_sums(const Frag& a, f4 c) {
+    const __bf16 o = (__bf16)1.f;
+    const b8 one = {o, o, o, o, o, o, o, o};
+    return mma(a.h, one, mma(a.m, one, mma(a.l, one, c)));
+  }
+
+  // Whether the registers hold two layers' shares of the stash beside the
+  // adjoint streams (not at two waves per SIMD and 80 neurons).
+  static constexpr bool KEEP = MB != 5;
+
+  // Activation stash of the workgroup's slot, [layer 1..D][wave][stream][mblock][lane]
+  // float4, addressed through a buffer resource.
+  __device__ static int stash_off(int layer, int wave, int s, int mb) {
+    return (layer - 1) * STASH_LAYER + ((wave * 4 + s) * MB + mb) * 1024;
   }
   // Stash loads read at device scope (SC1): a slot is rewritten by the same
   // wave on every tile, and the per-CU vector L1 must not serve a copy from
   // before the rewrite.
   static constexpr int kStashLoadPolicy = 16;
-  __device__ static void stash_load(__amdgpu_buffer_rsrc_t rs, int region, int layer, int wave, int lane,
-                                    Streams& A) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-        A[s][mb] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, stash_off(region, layer, wave, s, mb), kStashLoadPolicy);
+  __device__ __forceinline__ static void stash_load_block(__amdgpu_buffer_rsrc_t rs, int layer, int wave, int lane,
+                                                          int s, int mb, f4& v) {
+    v = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, stash_off(layer, wave, s, mb), kStashLoadPolicy);
   }
-  __device__ static void stash_load_stream(__amdgpu_buffer_rsrc_t rs, int region, int layer, int wave, int lane,
-                                           int s, f4 (&As)[MB]) {
+  __device__ static void stash_load_stream(__amdgpu_buffer_rsrc_t rs, int layer, int wave, int lane, int s,
+                                           f4 (&As)[MB]) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-      As[mb] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, stash_off(region, layer, wave, s, mb), kStashLoadPolicy);
+    for (int mb = 0; mb < MB; ++mb) stash_load_block(rs, layer, wave, lane, s, mb, As[mb]);
+  }
+  __device__ static void stash_load(__amdgpu_buffer_rsrc_t rs, int layer, int wave, int lane, Streams& A) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) stash_load_stream(rs, layer, wave, lane, s, A[s]);
   }
 
   // output layer u = W^L h + b^L for DO outputs; every lane group ends with
@@ -587,9 +773,7 @@ struct Tile {
       }
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        float v = acc[s];
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
+        const float v = group_sum(acc[s]);
         u[c][s] = s == 0 ? v + bL[c] : v;
       }
     }
@@ -715,9 +899,10 @@ struct Tile {
   // the value a partial-row entry holds before this tile (0 on an item's first
   // tile): loaded early into the accumulator, so the tile's sums add onto it
   // and the entry is then simply stored
-  __device__ static float prior(const float* src, bool first) {
-    return first ? 0.f : __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __device__ static float device_load(const float* src) {
+    return __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __device__ static float prior(const float* src, bool first) { return first ? 0.f : device_load(src); }
 
   // ------------------------------------------------------------------------
   // forward only, one tile starting at point t0 of the item, results written by
@@ -740,7 +925,7 @@ struct Tile {
   template <int VMODE, bool GA>
   __device__ __forceinline__ static void values_tile(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds,
                                                      float* dst, const float* kin, int t0) {
-    float* sW = lds;
+    char* sW = reinterpret_cast<char*>(lds);
     const int tid = item_tid();
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, pc = lane & 15;
@@ -761,15 +946,9 @@ struct Tile {
     const __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc(lds, 0, 0, 0x00020000);  // unused
     for (int k = 2; k <= nd.depth; ++k) {
       __syncthreads();
-      stage_wb(sW, K + L.k_w(k), K + L.k_b(k), tid);
+      stage_wb(sW, K + L.k_w(k), tid);
       __syncthreads();
-      Streams Hn;
-      hidden_layer<false, GA>(sW, sW + WP * WS, g, pc, real_steps(nd.width), H, Hn, none, 0, wave, lane, nd.act,
-                              slope(nd, K, L, k));
-#pragma unroll
-      for (int st = 0; st < 4; ++st)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) H[st][mb] = Hn[st][mb];
+      hidden_layer<false, GA>(sW, g, H, none, k, wave, lane, nd, slope(nd, K, L, k));
     }
     float u[DO][4];
     out_fwd(K + L.k_out(), K + L.k_bout(), g, H, u);
@@ -794,8 +973,6 @@ struct Tile {
   // ------------------------------------------------------------------------
   // forward, loss, adjoint and parameter-gradient partials of one item
   //
-  // PREFETCH_A: load a^{k-1} during layer k of the reverse pass (and a^D while
-  // the output layer runs) instead of at the top of each reverse layer.
   // Tiles starting at t_lo .. t_hi - 1 (step TP) of the item; roff is the
   // offset of this network's part in the item's gradient row; MODE selects the
   // epilogue (sInv: the LDS exchange area of the inverse problem); PHASE the
@@ -807,18 +984,14 @@ struct Tile {
     if (lane == 0) sSl[wave] = dc;
   }
 
-  template <bool PREFETCH_A, int MODE, int PHASE, bool GA, bool RH>
+  template <int MODE, int PHASE, bool GA>
   __device__ __forceinline__ static void run_train(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds,
                                    float* slot, int64_t slot_floats, const float* sNb, float* sInv, int t_lo,
                                    int t_hi, int roff) {
-    constexpr bool kPair = pair_staged(WP);
-    float* sW = lds;
-    float* sA = sW + WP * WS + WP;   // after the staged weights and bias
-    float* sH = sA + WP * TPS;
-    // two streams side by side ([neuron][stream][point], rows of TPS2 floats)
-    // over the same space and beyond it
-    float* sH2 = sA + WP * TPS2;
-    float* sRed = sA + 2 * WP * (kPair ? TPS2 : TPS);   // [kWaves][kLossTerms]
+    char* sW = reinterpret_cast<char*>(lds);
+    float* sA = reinterpret_cast<float*>(sW + BUF);   // sums of the output layer and of layer 1 (the second buffer)
+    char* sS = sW + (stage_over_weights(WP) ? 0 : WBYTES);   // staging area of dW
+    float* sRed = reinterpret_cast<float*>(sW + tile_bytes(WP, DO));   // [kWaves][kLossTerms]
     float* sSl = sRed + kWaves * kLossTerms;   // [kWaves] slope-gradient sums
     const int D = nd.depth;
     const Layout L(WP, D, DO);
@@ -847,14 +1020,22 @@ struct Tile {
       // the first hidden layer's weights stream in during layer 1
       if (PHASE != PH_BWD && D >= 2) fetch_wb(wbuf(sW, D, 2), K, L, 2, wave, lane);
 
-      // ---- forward: Taylor streams through every layer, stash a^k (in PH_BWD
-      // only h^D is rebuilt, from the stashed a^D, or from layer 1 if D = 1)
+      // ---- forward: Taylor streams through every layer, stashing what the
+      // reverse pass needs (in PH_BWD only h^D is rebuilt, from the stash, or
+      // from layer 1 if D = 1)
       Streams H;
       {
         Streams A;
-        if (PHASE == PH_BWD && D >= 2) stash_load(rs, 0, D - 2, wave, lane, A);
-        else layer1(K, x, y, g, A);
-        activate<GA>(A, H, nd.act, slope(nd, K, L, PHASE == PH_BWD && D >= 2 ? D : 1));
+        if (PHASE == PH_BWD && D >= 2) {
+          stash_load(rs, D, wave, lane, A);
+          const float cD = slope(nd, K, L, D);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) h_stream<GA>(nd, s, cD, A, H[s]);
+        } else {
+          layer1(K, x, y, g, A);
+          activate<GA>(A, H, nd.act, slope(nd, K, L, 1));
+          if (D >= 2) stash_put_layer<GA>(nd, rs, 1, wave, lane, A, H);
+        }
       }
       for (int k = 2; k <= (PHASE == PH_BWD ? 1 : D); ++k) {
         tid = item_tid();
@@ -868,15 +1049,7 @@ struct Tile {
         dma_landed();
         __syncthreads();
         if (k < D) fetch_wb(wbuf(sW, D, k + 1), K, L, k + 1, wave, lane);
-        if constexpr (!RH) stash_store(rs, 1, k - 2, wave, lane, H);   // h^{k-1}
-        Streams Hn;
-        float* wb = wbuf(sW, D, k);
-        hidden_layer<true, GA>(wb, wb + WP * WS, g, pc, real_steps(nd.width), H, Hn, rs, k - 2, wave, lane,
-                               nd.act, slope(nd, K, L, k));   // stashes a^k
-#pragma unroll
-        for (int st = 0; st < 4; ++st)
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb) H[st][mb] = Hn[st][mb];
+        hidden_layer<true, GA>(wbuf(sW, D, k), g, H, rs, k, wave, lane, nd, slope(nd, K, L, k));
       }
       float u[DO][4];
       if constexpr (PHASE == PH_BWD) {
@@ -898,11 +1071,7 @@ struct Tile {
       epilogue<MODE>(ka, it, nd, pt, tp, valid, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss, kb);
 #pragma unroll
       for (int t = 0; t < kLossTerms; ++t) {
-        float v = g == 0 ? loss[t] : 0.f;
-        v += __shfl_xor(v, 1);
-        v += __shfl_xor(v, 2);
-        v += __shfl_xor(v, 4);
-        v += __shfl_xor(v, 8);
+        const float v = row_sum16(loss[t]);   // (the same in every lane group)
         if (lane == 0) sRed[wave * kLossTerms + t] = v;
       }
       if constexpr (MODE == EPI_INV_U) {
@@ -916,7 +1085,7 @@ struct Tile {
       // dW^L[c][n] = sum over points and streams of ubar_c h^D_n and db^L[c] =
       // sum over points of ubar_c (value stream): each lane's point term, summed
       // over the wave's 16 points by row_sum16 and over the waves through LDS
-      // (sA is free: the last forward layer used sW)
+      // (the second weight buffer is free: the last forward layer used the first)
       {
         float* sOut = sA;                      // [kWaves][DO][WP], then [kWaves][DO] bias sums
         float* sOutB = sA + kWaves * DO * WP;
@@ -938,6 +1107,7 @@ struct Tile {
         }
       }
       Streams G;
+      __builtin_amdgcn_sched_barrier(0);
       {
         const float* WL = K + L.k_out();
 #pragma unroll
@@ -957,13 +1127,15 @@ struct Tile {
           }
         }
       }
-      // a^D for the first reverse layer, loaded while the output layer runs
-      // (where registers allow; else at the top of each reverse layer)
-      Streams Ak;
-      if ((PREFETCH_A || RH) && D >= 2) stash_load(rs, 0, D - 2, wave, lane, Ak);
+      __builtin_amdgcn_sched_barrier(0);
+      // what was kept of layer k; the last layer's is loaded while the output
+      // layer's sums run
+      Streams Sk;
+      if (KEEP && D >= 2) stash_load(rs, D, wave, lane, Sk);
       __syncthreads();
-      // every wave is past the last forward layer: W^{D T} streams into sW
-      if (D >= 2) fetch_wt(sW, K, L, D, wave, lane);
+      // every wave is past the last forward layer: W^{D T} streams into the
+      // first buffer (where the staging area of dW does not cover it)
+      if (!stage_over_weights(WP) && D >= 2) fetch_wt(sW, K, L, D, wave, lane);
 #pragma unroll
       for (int r = 0; r < KL; ++r) {
         const int t = tid + r * NT;
@@ -986,10 +1158,16 @@ struct Tile {
         accum(ka.loss_part + (int64_t)it.lrow * kLossTerms + tid, v * it.inv_n, first);
       }
 
-      // ---- hidden layers, top down.  G holds g^k on entry to layer k; it is
-      // turned into abar^k in place, and stream by stream each abar^k_s is
-      // replaced by g^{k-1}_s once it has been staged for dW^k, so the reverse
-      // pass holds one layer of streams plus one stream in flight.
+      // ---- hidden layers, top down.  G holds g^k on entry to layer k and is
+      // turned into abar^k in place; then, stream by stream, abar^k and h^{k-1}
+      // go through LDS for dW^k = sum_{points, streams} abar^k h^{k-1 T} and
+      // db^k = sum_points abar^k_0, and last g^{k-1} = W^{kT} abar^k.  With dW
+      // first, a pair of streams of g^{k-1} takes the registers its abar^k
+      // leaves, so one layer of streams and one pair are live at most.
+      if constexpr (!KEEP) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (D >= 2) stash_load(rs, D, wave, lane, Sk);
+      }
       for (int k = D; k >= 2; --k) {
         // and again per layer, so address arithmetic is not pinned across layers
         tid = item_tid();
@@ -1000,215 +1178,201 @@ struct Tile {
         tp = wave * 16 + pc;
         // dW^k / db^k accumulators start from the partial row
         float* Rw = R + L.g_w(k);
-        f4 dacc[NB];
+        float* Rb = R + L.g_b(k);
+        auto block_prior = [&](int mb, int jb) {
+          f4 v;
 #pragma unroll
-        for (int r = 0; r < NB; ++r) {
-          const int b = wave + r * kWaves;
-          if (b < NBT) {
-            const int mb = b / MB, jb = b - (b / MB) * MB;
+          for (int i = 0; i < 4; ++i) v[i] = device_load(Rw + (16 * mb + 4 * g + i) * WP + 16 * jb + pc);
+          return v;
+        };
+        auto bias_prior = [&](int mb) {
+          f4 v;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dacc[r][i] = prior(Rw + (16 * mb + 4 * g + i) * WP + 16 * jb + pc, first);
-          } else {
-            dacc[r] = f4{0.f, 0.f, 0.f, 0.f};
-          }
-        }
-        float dbias = tid < WP ? prior(R + L.g_b(k) + tid, first) : 0.f;
-        // abar^k from the stashed a^k (loaded ahead) and the incoming g^k (in place
-        // of g^k); with a general activation also the layer's slope gradient
+          for (int i = 0; i < 4; ++i) v[i] = device_load(Rb + 16 * mb + 4 * g + i);
+          return v;
+        };
+        // layer k - 1's share of the stash, for h^{k-1} here and for the next
+        // layer's adjoint, takes the place of layer k's block by block (KEEP);
+        // class 80 has no registers to hold it, loads h^{k-1} stream by
+        // stream and the whole again at the end
+        Streams Sp;
+        // abar^k from what was kept of layer k and the incoming g^k (in place of
+        // g^k); with a general activation also the layer's slope gradient
         {
-          if (!PREFETCH_A && !RH) stash_load(rs, 0, k - 2, wave, lane, Ak);
           const float ck = GA ? slope(nd, K, L, k) : 1.f;
           float dc = 0.f;
+          const bool hk = h_form<GA>(nd);
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               float a0, a1, a2, a3;
-              if constexpr (GA)
-                act_adj<S2>(nd.act, ck, Ak[0][mb][i], Ak[1][mb][i], Ak[2][mb][i], Ak[3][mb][i], G[0][mb][i],
-                            G[1][mb][i], G[2][mb][i], G[3][mb][i], a0, a1, a2, a3, dc);
+              if (hk)
+                tanh_adj_h<S2>(Sk[0][mb][i], Sk[1][mb][i], Sk[2][mb][i], Sk[3][mb][i], G[0][mb][i], G[1][mb][i],
+                               G[2][mb][i], G[3][mb][i], a0, a1, a2, a3);
               else
-                tanh_adj<S2>(Ak[0][mb][i], Ak[1][mb][i], Ak[2][mb][i], Ak[3][mb][i], G[0][mb][i], G[1][mb][i],
-                             G[2][mb][i], G[3][mb][i], a0, a1, a2, a3);
+                act_adj<S2>(nd.act, ck, Sk[0][mb][i], Sk[1][mb][i], Sk[2][mb][i], Sk[3][mb][i], G[0][mb][i],
+                            G[1][mb][i], G[2][mb][i], G[3][mb][i], a0, a1, a2, a3, dc);
               G[0][mb][i] = a0;
               G[1][mb][i] = a1;
               G[2][mb][i] = a2;
               G[3][mb][i] = a3;
             }
+            if constexpr (MB >= 3) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (KEEP) {
+#pragma unroll
+              for (int s = 0; s < 4; ++s) stash_load_block(rs, k - 1, wave, lane, s, mb, Sp[s][mb]);
+            }
           }
           if constexpr (GA) slope_wave_sum(dc, sSl, lane, wave);
         }
-        // recompute policy: a^{k-1} now (the stash for k - 1 >= 2, layer 1
-        // from the point itself), h^{k-1} rebuilt from it stream by stream below
-        if constexpr (RH) {
-          if (k > 2) stash_load(rs, 0, k - 3, wave, lane, Ak);
-          else layer1(K, x, y, g, Ak);
-        }
-        Streams& Ab = G;
-        dma_landed();
-        __syncthreads();   // W^{kT} is in sW (fetched during the previous stage)
-        if constexpr (GA) {
-          if (nd.adaptive && tid == 0) accum(R + L.g_slope() + k - 1, (sSl[0] + sSl[1]) + (sSl[2] + sSl[3]), first);
-        }
-        // per stream: g^{k-1}_s = W^{kT} abar^k_s, then the stream's share of
-        // dW^k = sum_{points, streams} abar^k h^{k-1 T}; db^k = sum_points abar^k_0.
-        // The barrier that frees sA/sH from the previous stream's dW comes after
-        // the W^T abar products, which only read sW: a wave that finished its
-        // dW blocks early goes on with them.
-        // streams in pairs (0, 1), (2, 3): g^{k-1} of both = W^{kT} abar^k
-        // (one weight read per two MFMAs), then per stream its share of dW^k
-        // wider classes load h^{k-1} per stream: in the inverse problem's
-        // kernels and the one-wave classes one stream ahead (stream s + 1 while
-        // stream s runs its dW and, after stream 1, the next pair's W^T abar);
-        // elsewhere right before use, where the register budget is tighter
-        // (measured: ahead is 1.7-2.7 % faster there, 1.3-1.8 % slower here)
-        constexpr bool kEarlyH = WP <= 64;
-        constexpr bool kNextH = !RH && !kEarlyH && (PDE == PDE_INV || WP >= 96);
-        f4 Hnext[MB];
-        if constexpr (kNextH) stash_load_stream(rs, 1, k - 2, wave, lane, 0, Hnext);
+        pin(G);   // the adjoint is done here, not after the branches below
+        f4 dacc[ROWS + 1][MB], drem[NREM + 1], dbias[ROWS + 1], dbrem[NREM + 1];
+        if (first) {
+          const f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int sp = 0; sp < 2; ++sp) {
-          // h^{k-1} of both streams (stored in the forward), loaded ahead of the
-          // pair's MFMAs so that their latency hides behind them (where the
-          // registers allow: classes up to 64; wider ones one stream ahead)
-          f4 Hp[2][MB];
-          if constexpr (!RH && kEarlyH) {
+          for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) stash_load_stream(rs, 1, k - 2, wave, lane, 2 * sp + hh, Hp[hh]);
+            for (int jb = 0; jb < MB; ++jb) dacc[r][jb] = zero;
+            dbias[r] = zero;
           }
-          f4 Gp[2][MB];
-          hidden_bwd_pair(sW, g, pc, real_steps(nd.width), Ab[2 * sp], Ab[2 * sp + 1], Gp[0], Gp[1]);
-          if constexpr (kPair) {
-            // both streams of the pair staged at once: dW^k over 2 x 64
-            // (stream, point) terms per barrier pair
-            f4 Hs2[2][MB];
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-              const int s = 2 * sp + hh;
-              if constexpr (RH) {
-                const float cp = GA ? slope(nd, K, L, k - 1) : 1.f;
+          for (int r = 0; r < NREM; ++r) drem[r] = dbrem[r] = zero;
+        } else {
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
+          for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
-                  for (int i = 0; i < 4; ++i) {
-                    if constexpr (GA)
-                      Hs2[hh][mb][i] =
-                          act_stream_ga<S2>(s, nd.act, cp, Ak[0][mb][i], Ak[1][mb][i], Ak[2][mb][i], Ak[3][mb][i]);
-                    else
-                      Hs2[hh][mb][i] = act_stream<S2>(s, Ak[0][mb][i], Ak[1][mb][i], Ak[2][mb][i], Ak[3][mb][i]);
-                  }
-              } else {
+            for (int jb = 0; jb < MB; ++jb) dacc[r][jb] = block_prior(4 * r + wave, jb);
+            dbias[r] = bias_prior(4 * r + wave);
+          }
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) Hs2[hh][mb] = Hp[hh][mb];
-              }
+          for (int r = 0; r < NREM; ++r) {
+            const int b = min(wave + r * kWaves, REM - 1);
+            drem[r] = block_prior(4 * ROWS + b / MB, b % MB);
+            dbrem[r] = bias_prior(4 * ROWS + b / MB);
+          }
+        }
+        f4 Hn[SN][MB];
+        const bool hf = h_form<GA>(nd);
+        const int hlayer = k - 1 + (hf ? 0 : kMaxDepth);
+        if constexpr (!KEEP) {
+#pragma unroll
+          for (int st = 0; st < SN; ++st) stash_load_stream(rs, hlayer, wave, lane, st, Hn[st]);
+        }
+#pragma unroll
+        for (int s0 = 0; s0 < 4; s0 += SN) {
+          __syncthreads();   // the previous stage's dW, or the last W^T abar, is done with the staging area
+          if (s0 == 0) {   // (the barrier published the slope sums too)
+            if constexpr (GA) {
+              if (nd.adaptive && tid == 0)
+                accum(R + L.g_slope() + k - 1, (sSl[0] + sSl[1]) + (sSl[2] + sSl[3]), first);
             }
-            if (sp > 0) __syncthreads();
+          }
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
+          for (int st = 0; st < SN; ++st) {
+            const int s = s0 + st;
+            stage_put(sS, st * TP + tp, g, G[s]);
+            if constexpr (KEEP) {
+              h_stream<GA>(nd, s, GA ? slope(nd, K, L, k - 1) : 1.f, Sp, Hn[st]);
+            } else if (s == 0 && hf) {
 #pragma unroll
               for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                  sA[(16 * mb + 4 * g + i) * TPS2 + hh * TP + tp] = Ab[2 * sp + hh][mb][i];
-                  sH2[(16 * mb + 4 * g + i) * TPS2 + hh * TP + tp] = Hs2[hh][mb][i];
+                  float t, s1;
+                  tanh_s1(Hn[st][mb][i], t, s1);
+                  Hn[st][mb][i] = t;
                 }
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb) G[2 * sp + hh][mb] = Gp[hh][mb];
-            if (PREFETCH_A && !RH && sp == 1 && k > 2) stash_load(rs, 0, k - 3, wave, lane, Ak);
-            __syncthreads();
-            if (sp == 1 && k > 2) fetch_wt(sW, K, L, k - 1, wave, lane);
-#pragma unroll
-            for (int r = 0; r < NB; ++r) {
-              __builtin_amdgcn_sched_barrier(0);
-              const int b = wave + r * kWaves;
-              if (b < NBT) {
-                const int mb = b / MB, jb = b - (b / MB) * MB;
-#pragma unroll
-                for (int gq = 0; gq < 2 * TP / 16; ++gq) {
-                  const f4 av = *reinterpret_cast<const f4*>(&sA[(16 * mb + pc) * TPS2 + 16 * gq + 4 * g]);
-                  const f4 hv = *reinterpret_cast<const f4*>(&sH2[(16 * jb + pc) * TPS2 + 16 * gq + 4 * g]);
-#pragma unroll
-                  for (int i = 0; i < 4; ++i) dacc[r] = mma(av[i], hv[i], dacc[r]);
-                }
-              }
             }
-            // db^k from stream 0 (the first half of each row)
-            if (sp == 0 && tid < WP) dbias += row_sum(sA + tid * TPS2);
-            continue;
+            stage_put(sS + 3 * PART, st * TP + tp, g, Hn[st]);
+            if constexpr (!KEEP) {
+              if (s0 + SN < 4) stash_load_stream(rs, hlayer, wave, lane, s + SN, Hn[st]);
+            }
           }
+          // every wave is past W^{k+1 T}: W^{kT} streams in during dW^k (issued here,
+          // behind the waits for the stash)
+          if (!stage_over_weights(WP) && s0 == 0 && k < D) fetch_wt(sW, K, L, k, wave, lane);
+          __syncthreads();
+          // fragments are read one block ahead of their MFMAs
+#pragma unroll (MB <= 2 ? SROWS / 32 : 1)
+          for (int c = 0; c < SROWS / 32; ++c) {
+            const bool value = s0 == 0 && c < TP / 32;   // rows of the value stream: db^k
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            const int s = 2 * sp + hh;
-            f4 Hs[MB];
-            if constexpr (RH) {   // h^{k-1}_s = the activation rule on a^{k-1}
-              const float cp = GA ? slope(nd, K, L, k - 1) : 1.f;
+            for (int r = 0; r < ROWS; ++r) {
+              const Frag a = stage_parts(sS, c, 4 * r + wave, lane);
+              Frag h = stage_parts(sS + 3 * PART, c, 0, lane);
+              if (value) dbias[r] = row_sums(a, dbias[r]);
 #pragma unroll
-              for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                  if constexpr (GA)
-                    Hs[mb][i] =
-                        act_stream_ga<S2>(s, nd.act, cp, Ak[0][mb][i], Ak[1][mb][i], Ak[2][mb][i], Ak[3][mb][i]);
-                  else
-                    Hs[mb][i] = act_stream<S2>(s, Ak[0][mb][i], Ak[1][mb][i], Ak[2][mb][i], Ak[3][mb][i]);
-                }
-            } else if constexpr (kEarlyH) {
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb) Hs[mb] = Hp[hh][mb];
-            } else if constexpr (kNextH) {
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb) Hs[mb] = Hnext[mb];   // h^{k-1}_s (stored in the forward)
-            } else {
-              stash_load_stream(rs, 1, k - 2, wave, lane, s, Hs);   // h^{k-1}_s (stored in the forward)
-            }
-            if (s > 0) __syncthreads();
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                sA[(16 * mb + 4 * g + i) * TPS + tp] = Ab[s][mb][i];
-                sH[(16 * mb + 4 * g + i) * TPS + tp] = Hs[mb][i];
+              for (int jb = 0; jb < MB; ++jb) {
+                Frag hn = h;
+                if (jb + 1 < MB) hn = stage_parts(sS + 3 * PART, c, jb + 1, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                dacc[r][jb] = mma6(a, h, dacc[r][jb]);
+                h = hn;
               }
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) G[s][mb] = Gp[hh][mb];   // g^{k-1}_s replaces abar^k_s
-            // a^{k-1} for the next reverse layer, loaded during the last dW^k stream
-            if (PREFETCH_A && !RH && s == 3 && k > 2) stash_load(rs, 0, k - 3, wave, lane, Ak);
-            if constexpr (kNextH) {
-              if (s < 3) stash_load_stream(rs, 1, k - 2, wave, lane, s + 1, Hnext);
             }
-            __syncthreads();
-            // every wave is done with W^{kT}: W^{(k-1)T} streams in during the last dW^k
-            if (s == 3 && k > 2) fetch_wt(sW, K, L, k - 1, wave, lane);
 #pragma unroll
-            for (int r = 0; r < NB; ++r) {
-              __builtin_amdgcn_sched_barrier(0);
+            for (int r = 0; r < NREM; ++r) {
               const int b = wave + r * kWaves;
-              if (b < NBT) {
-                const int mb = b / MB, jb = b - (b / MB) * MB;
-#pragma unroll
-                for (int gq = 0; gq < TP / 16; ++gq) {
-                  const f4 av = *reinterpret_cast<const f4*>(&sA[(16 * mb + pc) * TPS + 16 * gq + 4 * g]);
-                  const f4 hv = *reinterpret_cast<const f4*>(&sH[(16 * jb + pc) * TPS + 16 * gq + 4 * g]);
-#pragma unroll
-                  for (int i = 0; i < 4; ++i) dacc[r] = mma(av[i], hv[i], dacc[r]);
-                }
+              if (b < REM) {
+                const Frag a = stage_parts(sS, c, 4 * ROWS + b / MB, lane);
+                const Frag h = stage_parts(sS + 3 * PART, c, b % MB, lane);
+                if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);
+                if (value) dbrem[r] = row_sums(a, dbrem[r]);
+                drem[r] = mma6(a, h, drem[r]);
               }
             }
-            if (s == 0 && tid < WP) dbias += row_sum(sA + tid * TPS);
           }
         }
+        if constexpr (stage_over_weights(WP)) {
+          __syncthreads();   // every wave is done with the staging area, which now receives W^{kT}
+          fetch_wt(sW, K, L, k, wave, lane);
+        }
+        auto block_store = [&](int mb, int jb, f4 v) {
 #pragma unroll
-        for (int r = 0; r < NB; ++r) {
+          for (int i = 0; i < 4; ++i) Rw[(16 * mb + 4 * g + i) * WP + 16 * jb + pc] = v[i];
+        };
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+          for (int jb = 0; jb < MB; ++jb) block_store(4 * r + wave, jb, dacc[r][jb]);
+          if (pc == 0) *reinterpret_cast<f4*>(Rb + 16 * (4 * r + wave) + 4 * g) = dbias[r];
+        }
+#pragma unroll
+        for (int r = 0; r < NREM; ++r) {
           const int b = wave + r * kWaves;
-          if (b < NBT) {
-            const int mb = b / MB, jb = b - (b / MB) * MB;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Rw[(16 * mb + 4 * g + i) * WP + 16 * jb + pc] = dacc[r][i];
+          if (b < REM) {
+            const int mb = 4 * ROWS + b / MB;
+            block_store(mb, b % MB, drem[r]);
+            if (b % MB == 0 && pc == 0) *reinterpret_cast<f4*>(Rb + 16 * mb + 4 * g) = dbrem[r];
           }
         }
-        if (tid < WP) R[L.g_b(k) + tid] = dbias;
+        dma_landed();
+        __syncthreads();   // W^{kT} is in LDS
+        {
+          if constexpr (MB >= 4) pin(G);   // else the parts just staged are kept for W^T abar, half as many registers again
+          Streams Gn;
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) Gn[s][mb] = f4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (KEEP) {
+            contract4<MB <= 5>(sW, lane, G, Gn);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb) Sk[s][mb] = Sp[s][mb];
+          } else {
+            contract<0, 2>(sW, lane, G, Gn);
+            contract<2, 2>(sW, lane, G, Gn);
+            __builtin_amdgcn_sched_barrier(0);
+            if (k > 2) stash_load(rs, k - 1, wave, lane, Sk);
+          }
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) G[s][mb] = Gn[s][mb];
+        }
       }
 
       // ---- layer 1: abar^1 from a^1 and g^1; dW^1[n] = sum over points of
@@ -1227,7 +1391,7 @@ struct Tile {
         const float c1 = GA ? slope(nd, K, L, 1) : 1.f;
         float dc = 0.f;
         float* sOut = sA;   // [kWaves][3][WP]
-        __syncthreads();    // every wave is done with sA (the last dW, or the output layer's sums)
+        __syncthreads();    // every wave is done with LDS (the last W^T abar, or the output layer's sums)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
@@ -1272,39 +1436,17 @@ struct Tile {
     }
   }
 
-  // entry from a kernel built for classes up to WPMAX: the a^k prefetch costs
-  // registers, so it is used for classes up to 48 in kernels that run two
-  // waves per SIMD anyway because of a wider class
-  // (GA as in values_tile)
-  template <int WPMAX, int MODE, int PHASE, bool GA, bool RH>
-  __device__ __forceinline__ static void train(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds, float* slot,
-                               int64_t slot_floats, const float* sNb, float* sInv, int t_lo, int t_hi, int roff) {
-    run_train<(WP <= 48 && WPMAX >= 48), MODE, PHASE, GA, RH>(ka, it, nd, lds, slot, slot_floats, sNb, sInv, t_lo,
-                                                               t_hi, roff);
-  }
 };
 
 // LDS floats of a train kernel for classes up to WP: the tile buffers of
-// Tile<WP> (sW, sA, sH, sRed, sSl), then the neighbour values sNb (6 per
-// point), then for the inverse problem 9 per point: the own K streams, the K
-// seeds, the neighbour's K streams.
-template <int WP>
-constexpr int tile_need_floats() {
-  return WP * (WP + 4) + WP + 2 * WP * (pair_staged(WP) ? TPS2 : TPS) + kWaves * kLossTerms + kWaves;
-}
+// Tile<WP> (weights and staging, sRed, sSl), then the neighbour values sNb (6
+// per point), then for the inverse problem 9 per point: the own K streams,
+// the K seeds, the neighbour's K streams.
 template <int WP, int PDE>
 constexpr int lds_tile_floats() {
-  // the largest need of the classes up to WP (a pair-staged narrow class
-  // can need more than a wider one)
-  int n = 0;
-  if (WP >= 16) n = tile_need_floats<16>();
-  if (WP >= 32) n = n > tile_need_floats<32>() ? n : tile_need_floats<32>();
-  if (WP >= 48) n = n > tile_need_floats<48>() ? n : tile_need_floats<48>();
-  if (WP >= 64) n = n > tile_need_floats<64>() ? n : tile_need_floats<64>();
-  if (WP >= 80) n = n > tile_need_floats<80>() ? n : tile_need_floats<80>();
-  if (WP >= 96) n = n > tile_need_floats<96>() ? n : tile_need_floats<96>();
-  if (WP >= 112) n = n > tile_need_floats<112>() ? n : tile_need_floats<112>();
-  return n;
+  int n = 0;   // the largest need of the classes up to WP
+  for (int w = 16; w <= WP; w += 16) n = tile_bytes(w, Op<PDE>::DO) > n ? tile_bytes(w, Op<PDE>::DO) : n;
+  return n / 4 + kWaves * kLossTerms + kWaves;
 }
 template <int WP, int PDE>
 constexpr int lds_train_floats() {
@@ -1323,7 +1465,7 @@ constexpr int lds_train_bytes() {
 // A paired item of the inverse problem goes tile by tile: the neighbour's K-
 // and u-networks (interfaces), the own K-network's streams, the u-network's
 // train pass (loss, u seeds, K seeds), then the K-network's train pass.
-template <int WPMAX, int PDE, bool GA, bool RH>
+template <int WPMAX, int PDE, bool GA>
 __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds,
                                          float* slot) {
   float* sNb = lds + lds_tile_floats<WPMAX, PDE>();
@@ -1365,11 +1507,11 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
           DDP_SWITCH(nbu.wclass, template values_tile<VAL_INV_NB, GA>(ka, it, nbu, lds, sNb, sInv + 6 * TP, t0))
           __syncthreads();
         }
-        DDP_SWITCH(ndk.wclass, template train<WPMAX, EPI_SEED, PH_FWD, GA, RH>(ka, it, ndk, lds, slot + half, half,
+        DDP_SWITCH(ndk.wclass, template run_train<EPI_SEED, PH_FWD, GA>(ka, it, ndk, lds, slot + half, half,
                                                                             sNb, sInv, t0, t0 + 1, nd.gsize))
         DDP_SWITCH(nd.wclass,
-                   template train<WPMAX, EPI_INV_U, PH_ALL, GA, RH>(ka, it, nd, lds, slot, half, sNb, sInv, t0, t0 + 1, 0))
-        DDP_SWITCH(ndk.wclass, template train<WPMAX, EPI_SEED, PH_BWD, GA, RH>(ka, it, ndk, lds, slot + half, half,
+                   template run_train<EPI_INV_U, PH_ALL, GA>(ka, it, nd, lds, slot, half, sNb, sInv, t0, t0 + 1, 0))
+        DDP_SWITCH(ndk.wclass, template run_train<EPI_SEED, PH_BWD, GA>(ka, it, ndk, lds, slot + half, half,
                                                                             sNb, sInv, t0, t0 + 1, nd.gsize))
       }
       return;
@@ -1381,7 +1523,7 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
     DDP_SWITCH(ndn.wclass, template values_tile<VAL_OWN, GA>(ka, it, ndn, lds, sNb, nullptr, 0))
     __syncthreads();
   }
-  DDP_SWITCH(nd.wclass, template train<WPMAX, EPI_OWN, PH_ALL, GA, RH>(ka, it, nd, lds, slot,
+  DDP_SWITCH(nd.wclass, template run_train<EPI_OWN, PH_ALL, GA>(ka, it, nd, lds, slot,
                                                        PDE == PDE_INV ? ka.scratch_slot / 2 : ka.scratch_slot, sNb,
                                                        sInv, 0, it.count, 0))
 #undef DDP_SWITCH
@@ -1394,13 +1536,13 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
 // run one wave per SIMD.
 template <int WPMAX>
 constexpr int min_waves_per_eu() {
-  return WPMAX <= 80 ? 2 : 1;
+  return WPMAX <= 16 ? 4 : WPMAX <= 32 ? 3 : WPMAX <= 80 ? 2 : 1;
 }
 
 // GA: kernels with the general activation rule, launched for problems where a
 // network uses another activation than tanh or trainable slopes (built for
 // the class groups up to 80 and up to 112 only)
-template <int WPMAX, int PDE, bool GA, bool RH>
+template <int WPMAX, int PDE, bool GA>
 __global__ __launch_bounds__(NT, min_waves_per_eu<WPMAX>()) void k_train(KArgs ka) {
   // one 16-byte aligned dynamic LDS block: the tile buffers, then the slot
   // that broadcasts the next work item (no static LDS, so the float4
@@ -1421,36 +1563,31 @@ __global__ __launch_bounds__(NT, min_waves_per_eu<WPMAX>()) void k_train(KArgs k
     if (idx >= ka.n_items) break;
     const Item it = ka.items[idx];
     const NetDesc nd = ka.nets[it.q];
-    dispatch<WPMAX, PDE, GA, RH>(ka, it, nd, lds, slot);
+    dispatch<WPMAX, PDE, GA>(ka, it, nd, lds, slot);
   }
 }
 
-// Position of hidden neuron n in the kernel layout and the gradient rows: the
-// index inside each 16-neuron block is transposed as a 4x4 grid (4a + b ->
-// 4b + a).  Register i of lane group g then holds neuron 16 mb + 4 i + g, so
-// the MFMA step i of a contraction over a block covers four consecutive
-// neurons, and in a padded last block the steps past the real neurons can be
-// skipped.  The map is its own inverse.
-__host__ __device__ __forceinline__ int neuron_pos(int n) { return (n & ~15) | ((n & 3) << 2) | ((n >> 2) & 3); }
-
 // Position of canonical parameter li of a network in its gradient partial row
-// (g) and in its kernel-layout copy (k1, and k2 for the transposed copy of a
-// hidden weight, else -1).  sc: the kernel copy holds sc times the parameter
-// and the partial rows hold the gradient divided by sc (n for a slope a^k,
-// whose kernel copy is c_k = n a^k; 1 otherwise).
-__device__ __forceinline__ void param_map(const NetDesc& nd, int li, int& g, int& k1, int& k2, float& sc) {
+// (g) and in its kernel-layout copy: a float at k1, or, for a hidden weight
+// (k1 = -1), the three bf16 parts at bf16 positions w, w + ws, w + 2 ws of the
+// weights and t, t + ts, t + 2 ts of the transposed copy.  sc: the kernel copy
+// holds sc times the parameter and the partial rows hold the gradient divided
+// by sc (n for a slope a^k, whose kernel copy is c_k = n a^k; 1 otherwise).
+struct ParamPos {
+  int g, k1, w, ws, t, ts;
+  float sc;
+};
+__device__ __forceinline__ ParamPos param_map(const NetDesc& nd, int li) {
   const int w = nd.width, WP = nd.wclass, D = nd.depth, DO = nd.d_out;
   const Layout L(WP, D, DO);
-  k2 = -1;
-  sc = 1.f;
+  ParamPos p{0, -1, 0, 0, 0, 0, 1.f};
   if (li < 2 * w) {                 // W^1[m][c]
-    const int m = li >> 1, c = li & 1;
-    g = k1 = neuron_pos(m) * 4 + c;
-    return;
+    p.g = p.k1 = (li >> 1) * 4 + (li & 1);
+    return p;
   }
   if (li < 3 * w) {                 // b^1[m]
-    g = k1 = neuron_pos(li - 2 * w) * 4 + 2;
-    return;
+    p.g = p.k1 = (li - 2 * w) * 4 + 2;
+    return p;
   }
   int r = li - 3 * w;
   const int per = w * w + w;
@@ -1459,32 +1596,46 @@ __device__ __forceinline__ void param_map(const NetDesc& nd, int li, int& g, int
     const int k = h + 2;
     const int rr = r - h * per;
     if (rr < w * w) {
-      const int m = neuron_pos(rr / w), j = neuron_pos(rr - (rr / w) * w);
-      g = L.g_w(k) + m * WP + j;
-      k1 = L.k_w(k) + m * L.WS + j;
-      k2 = L.k_wt(k) + j * L.WS + m;
+      const int m = rr / w, j = rr - (rr / w) * w;
+      p.g = L.g_w(k) + m * WP + j;
+      p.w = 2 * L.k_w(k) + split_pos(WP, m, j, p.ws);
+      p.t = 2 * L.k_wt(k) + split_pos(WP, j, m, p.ts);
     } else {
-      const int m = neuron_pos(rr - w * w);
-      g = L.g_b(k) + m;
-      k1 = L.k_b(k) + m;
+      p.g = L.g_b(k) + rr - w * w;
+      p.k1 = L.k_b(k) + rr - w * w;
     }
-    return;
+    return p;
   }
   r -= (D - 1) * per;               // output layer
   if (r < DO * w) {
-    const int c = r / w, j = neuron_pos(r - (r / w) * w);
-    g = L.g_out() + c * WP + j;
-    k1 = L.k_out() + c * WP + j;
+    const int c = r / w, j = r - (r / w) * w;
+    p.g = L.g_out() + c * WP + j;
+    p.k1 = L.k_out() + c * WP + j;
   } else if (r < DO * w + DO) {
-    const int c = r - DO * w;
-    g = L.g_bout() + c;
-    k1 = L.k_bout() + c;
+    p.g = L.g_bout() + r - DO * w;
+    p.k1 = L.k_bout() + r - DO * w;
   } else {                          // slope a^k of hidden layer k = 1..D
     const int k = r - DO * w - DO;
-    g = L.g_slope() + k;
-    k1 = L.k_slope() + k;
-    sc = nd.slope_n;
+    p.g = L.g_slope() + k;
+    p.k1 = L.k_slope() + k;
+    p.sc = nd.slope_n;
   }
+  return p;
+}
+
+// write the kernel-layout copy of a parameter with value v
+__device__ __forceinline__ void put_param(float* K, const ParamPos& p, float v) {
+  if (p.k1 >= 0) {
+    K[p.k1] = p.sc * v;
+    return;
+  }
+  b2 h, m, l;
+  split2(v, v, h, m, l);
+  __bf16* W = reinterpret_cast<__bf16*>(K) + p.w;
+  __bf16* T = reinterpret_cast<__bf16*>(K) + p.t;
+  W[0] = T[0] = m[0];
+  W[p.ws] = T[p.ts] = h[0];
+  W[2 * p.ws] = T[2 * p.ts] = l[0];
 }
 
 // network holding flat parameter i, searching upward from network n
@@ -1522,10 +1673,8 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
     const int r0 = ra.net_row_ptr[q], n = ra.net_row_ptr[q + 1] - r0;
     const int64_t* pr = ra.row_prow + r0;
     if (i < ra.net_poff[q + 1]) {
-      int gi, k1, k2;
-      float sc;
-      param_map(nd, (int)(i - ra.net_poff[q]), gi, k1, k2, sc);
-      const float* P = ra.partial + gi;
+      const ParamPos pp = param_map(nd, (int)(i - ra.net_poff[q]));
+      const float* P = ra.partial + pp.g;
       float a[kRedLanes];
 #pragma unroll
       for (int j = 0; j < kRedLanes; ++j) a[j] = 0.f;
@@ -1541,7 +1690,7 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
       for (int w = kRedLanes / 2; w >= 1; w /= 2)
 #pragma unroll
         for (int j = 0; j < w; ++j) a[j] += a[j + w];
-      const float s = sc * a[0];
+      const float s = pp.sc * a[0];
       if (ra.grad_out) ra.grad_out[i] = s;
       if (ra.do_adam) {
         const float tstep = (float)(ra.tstate[0] + 1);
@@ -1555,9 +1704,7 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
         const float vh = v / bc2;
         const float th = ra.params[i] - nd.lr * mh / (sqrtf(vh) + eps);
         ra.params[i] = th;
-        float* K = ra.kparams + nd.koff;
-        K[k1] = sc * th;
-        if (k2 >= 0) K[k2] = th;
+        put_param(ra.kparams + nd.koff, pp, th);
       }
     }
   }
@@ -1600,12 +1747,7 @@ __global__ __launch_bounds__(256) void k_pack(const float* params, float* kparam
        i += (int64_t)gridDim.x * blockDim.x) {
     const int q = find_net(net_poff, n_begin, i);
     const NetDesc nd = nets[q];
-    int gi, k1, k2;
-    float sc;
-    param_map(nd, (int)(i - net_poff[q]), gi, k1, k2, sc);
-    float* K = kparams + nd.koff;
-    K[k1] = sc * params[i];
-    if (k2 >= 0) K[k2] = params[i];
+    put_param(kparams + nd.koff, param_map(nd, (int)(i - net_poff[q])), params[i]);
   }
 }
 
@@ -1665,133 +1807,112 @@ __global__ __launch_bounds__(256) void k_eval(const float* params, const NetDesc
 // ---------------------------------------------------------------------------
 // host-side launchers
 
-static int wclass_index(int wpmax) {
-  switch (wpmax) {
-    case 16: return 0;
-    case 32: return 1;
-    case 48: return 2;
-    case 64: return 3;
-    case 80: return 4;
-    case 96: return 5;
-    case 112: return 6;
-  }
-  return -1;
-}
-
-// Train kernels per operator and activation policy RH (0: the forward
-// stashes a^k and h^k; 1: it stashes a^k only and the reverse pass rebuilds
-// h^{k-1} from a^{k-1}), and the LDS bytes per class (policy-independent).
-template <int PDE, int RH>
-struct KTable {
-  static const void* train[7];
-  static const void* train_ga[2];   // general activation: class groups up to 80, up to 112
+// One train kernel (operator, class group, activation rule) and the LDS bytes
+// it is launched with.  A unit built with DDP_TRAIN_PDE defines the kernels
+// of that operator for the class DDP_TRAIN_WP (0: those up to 64), with
+// DDP_TRAIN_GA the general-activation one.
+template <int PDE, int WPMAX, bool GA>
+struct Kernel {
+  static const void* fn;
+  static int lds;
 };
-template <int PDE>
-struct KLds {
-  static int lds[7];
-};
-// (a unit built with DDP_TRAIN_GA defines the general-activation row of its
-// operator and policy, one without it the plain row, and with policy 0 also
-// the LDS sizes)
-#ifndef DDP_TRAIN_RH
-#define DDP_TRAIN_RH 0
-#endif
-#ifdef DDP_TRAIN_GA
-#define DDP_ROW(PDE, RH)                                                                                          \
-  template <> const void* KTable<PDE, RH>::train_ga[2] = {(const void*)k_train<80, PDE, true, RH>,                \
-                                                          (const void*)k_train<112, PDE, true, RH>};
-#else
-#define DDP_ROW(PDE, RH)                                                                                          \
-  template <> const void* KTable<PDE, RH>::train[7] = {                                                           \
-      (const void*)k_train<16, PDE, false, RH>, (const void*)k_train<32, PDE, false, RH>,                         \
-      (const void*)k_train<48, PDE, false, RH>, (const void*)k_train<64, PDE, false, RH>,                         \
-      (const void*)k_train<80, PDE, false, RH>, (const void*)k_train<96, PDE, false, RH>,                         \
-      (const void*)k_train<112, PDE, false, RH>};
-#endif
 #ifdef DDP_TRAIN_PDE
-DDP_ROW(DDP_TRAIN_PDE, (DDP_TRAIN_RH != 0))
-#if !defined(DDP_TRAIN_GA) && DDP_TRAIN_RH == 0
-template <> int KLds<DDP_TRAIN_PDE>::lds[7] = {
-    lds_train_bytes<16, DDP_TRAIN_PDE>(), lds_train_bytes<32, DDP_TRAIN_PDE>(), lds_train_bytes<48, DDP_TRAIN_PDE>(),
-    lds_train_bytes<64, DDP_TRAIN_PDE>(), lds_train_bytes<80, DDP_TRAIN_PDE>(), lds_train_bytes<96, DDP_TRAIN_PDE>(),
-    lds_train_bytes<112, DDP_TRAIN_PDE>()};
-#endif
-#undef DDP_ROW
+#ifdef DDP_TRAIN_GA
+#define DDP_GA true
 #else
-#undef DDP_ROW
-// the tables are defined in the operators' own translation units
-#define DDP_DECL(PDE)                                                  \
-  template <> const void* KTable<PDE, false>::train[7];                \
-  template <> const void* KTable<PDE, true>::train[7];                 \
-  template <> const void* KTable<PDE, false>::train_ga[2];             \
-  template <> const void* KTable<PDE, true>::train_ga[2];              \
-  template <> int KLds<PDE>::lds[7];
+#define DDP_GA false
+#endif
+#define DDP_KERNEL(WPV)                                                                                            \
+  template <> const void* Kernel<DDP_TRAIN_PDE, WPV, DDP_GA>::fn = (const void*)k_train<WPV, DDP_TRAIN_PDE, DDP_GA>; \
+  template <> int Kernel<DDP_TRAIN_PDE, WPV, DDP_GA>::lds = lds_train_bytes<WPV, DDP_TRAIN_PDE>();
+#if DDP_TRAIN_WP == 0
+DDP_KERNEL(16)
+DDP_KERNEL(32)
+DDP_KERNEL(48)
+DDP_KERNEL(64)
+#else
+DDP_KERNEL(DDP_TRAIN_WP)
+#endif
+#undef DDP_KERNEL
+#undef DDP_GA
+#else
+// the kernels are defined in units of their own
+#define DDP_DECL1(PDE, WPV, GA)                     \
+  template <> const void* Kernel<PDE, WPV, GA>::fn; \
+  template <> int Kernel<PDE, WPV, GA>::lds;
+#define DDP_DECL(PDE)                                                                                     \
+  DDP_DECL1(PDE, 16, false) DDP_DECL1(PDE, 32, false) DDP_DECL1(PDE, 48, false) DDP_DECL1(PDE, 64, false) \
+  DDP_DECL1(PDE, 80, false) DDP_DECL1(PDE, 96, false) DDP_DECL1(PDE, 112, false)                          \
+  DDP_DECL1(PDE, 80, true) DDP_DECL1(PDE, 112, true)
 DDP_DECL(PDE_POISSON)
 DDP_DECL(PDE_BURGERS)
 DDP_DECL(PDE_NS)
 DDP_DECL(PDE_INV)
 #undef DDP_DECL
+#undef DDP_DECL1
 
-template <int RH>
-static const void* pick_rh(int pde, int c, bool ga, int g) {
-  switch (pde) {
-    case PDE_POISSON: return ga ? KTable<PDE_POISSON, RH>::train_ga[g] : KTable<PDE_POISSON, RH>::train[c];
-    case PDE_BURGERS: return ga ? KTable<PDE_BURGERS, RH>::train_ga[g] : KTable<PDE_BURGERS, RH>::train[c];
-    case PDE_NS: return ga ? KTable<PDE_NS, RH>::train_ga[g] : KTable<PDE_NS, RH>::train[c];
-    case PDE_INV: return ga ? KTable<PDE_INV, RH>::train_ga[g] : KTable<PDE_INV, RH>::train[c];
+// the kernel of a class (general-activation kernels exist for the groups up
+// to 80 and up to 112) and its LDS bytes
+template <class K>
+static const void* pick_kernel(int* lds) {
+  *lds = K::lds;
+  return K::fn;
+}
+template <int PDE>
+static const void* pick_pde(int wpmax, bool ga, int* lds) {
+  if (ga) {
+    if (wpmax == 80) return pick_kernel<Kernel<PDE, 80, true>>(lds);
+    if (wpmax == 112) return pick_kernel<Kernel<PDE, 112, true>>(lds);
+    return nullptr;
+  }
+  switch (wpmax) {
+    case 16: return pick_kernel<Kernel<PDE, 16, false>>(lds);
+    case 32: return pick_kernel<Kernel<PDE, 32, false>>(lds);
+    case 48: return pick_kernel<Kernel<PDE, 48, false>>(lds);
+    case 64: return pick_kernel<Kernel<PDE, 64, false>>(lds);
+    case 80: return pick_kernel<Kernel<PDE, 80, false>>(lds);
+    case 96: return pick_kernel<Kernel<PDE, 96, false>>(lds);
+    case 112: return pick_kernel<Kernel<PDE, 112, false>>(lds);
   }
   return nullptr;
 }
 
-static const void* pick(int pde, int wpmax, bool ga, bool rh) {
-  const int c = wclass_index(wpmax);
-  if (c < 0) return nullptr;
-  int g = 0;
-  if (ga) {   // general-activation kernels exist for the groups up to 80 and up to 112
-    if (wpmax != 80 && wpmax != 112) return nullptr;
-    g = wpmax == 80 ? 0 : 1;
-  }
-  return rh ? pick_rh<true>(pde, c, ga, g) : pick_rh<false>(pde, c, ga, g);
-}
-
-size_t lds_bytes(int pde, int wpmax) {
-  const int c = wclass_index(wpmax);
-  if (c < 0) return 0;
-  int f = 0;
+static const void* pick(int pde, int wpmax, bool ga, int* lds) {
   switch (pde) {
-    case PDE_POISSON: f = KLds<PDE_POISSON>::lds[c]; break;
-    case PDE_BURGERS: f = KLds<PDE_BURGERS>::lds[c]; break;
-    case PDE_NS: f = KLds<PDE_NS>::lds[c]; break;
-    case PDE_INV: f = KLds<PDE_INV>::lds[c]; break;
+    case PDE_POISSON: return pick_pde<PDE_POISSON>(wpmax, ga, lds);
+    case PDE_BURGERS: return pick_pde<PDE_BURGERS>(wpmax, ga, lds);
+    case PDE_NS: return pick_pde<PDE_NS>(wpmax, ga, lds);
+    case PDE_INV: return pick_pde<PDE_INV>(wpmax, ga, lds);
   }
-  return (size_t)f;
+  return nullptr;
 }
 
-int64_t scratch_slot_floats(int pde, int wpmax, bool rh) {
-  // two regions (a^k and h^k) of kMaxDepth - 1 layers, or the a^k region
-  // alone under the recompute policy; the inverse problem keeps one such
+int64_t scratch_slot_floats(int pde, int wpmax, bool ga) {
+  // four streams of up to kMaxDepth layers (the general-activation kernels
+  // keep four more of an 80-wide network); the inverse problem keeps one such
   // stash per network of a pair
-  const int64_t one = (int64_t)(rh ? 1 : 2) * (kMaxDepth - 1) * kWaves * 4 * (wpmax / 16) * 64 * 4;
+  const int64_t one = (int64_t)(ga ? 2 : 1) * kMaxDepth * kWaves * 4 * (wpmax / 16) * 64 * 4;
   return pde == PDE_INV ? 2 * one : one;
 }
 
 int kernel_wpmax(int wpmax, bool ga) { return ga ? (wpmax <= 80 ? 80 : 112) : wpmax; }
 
-hipError_t launch_train(int pde, int wpmax, bool ga, bool rh, const KArgs& ka, int grid, hipStream_t st) {
-  const void* fn = pick(pde, wpmax, ga, rh);
+hipError_t launch_train(int pde, int wpmax, bool ga, const KArgs& ka, int grid, hipStream_t st) {
+  int lds = 0;
+  const void* fn = pick(pde, wpmax, ga, &lds);
   if (!fn) return hipErrorInvalidValue;
   KArgs a = ka;
   void* args[] = {&a};
-  return hipLaunchKernel(fn, dim3(grid), dim3(NT), args, lds_bytes(pde, wpmax), st);
+  return hipLaunchKernel(fn, dim3(grid), dim3(NT), args, (size_t)lds, st);
 }
 
-hipError_t train_occupancy(int pde, int wpmax, bool ga, bool rh, int* blocks_per_cu) {
-  const void* fn = pick(pde, wpmax, ga, rh);
+hipError_t train_occupancy(int pde, int wpmax, bool ga, int* blocks_per_cu) {
+  int lds = 0;
+  const void* fn = pick(pde, wpmax, ga, &lds);
   if (!fn) return hipErrorInvalidValue;
-  const size_t lds = lds_bytes(pde, wpmax);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, NT, lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, NT, (size_t)lds);
 }
 
 hipError_t launch_reset_counter(int* c, hipStream_t st) {

@@ -768,3 +768,26 @@ def test_work_plans_against_oracle(name, scale, seed):
                         worst = max(worst, wl, wg)
                         pb.close()
     _say(f"{name}: every plan within the bar, worst {worst:.2e}")
+
+
+@pytest.mark.parametrize("widths", [(1, 15, 16, 17), (31, 32, 33, 47), (48, 49, 63, 64), (65, 79, 80, 81),
+                                    (95, 96, 97, 112)])
+@pytest.mark.parametrize("acts", ["tanh", "mixed"])
+def test_every_width_class_at_its_edges(widths, acts):
+    """Each width class with its odd or even number of 16-neuron blocks, at its
+    edges, one hidden-to-hidden product and several, over more than one tile
+    per work item with a last tile of one point: the split bf16 contractions,
+    the dW staging and its left-over blocks, the stash of each class, with the
+    plain and the general activation rule.  The bound is that of compare."""
+    depths = (2, 3, 4, 2)
+    prob = W.custom_box_problem("xpinn", "poisson2d", 2, 2, [[2] + [w] * d + [1] for w, d in zip(widths, depths)],
+                                [129, 193, 65, 130], n_bnd_seg=9, n_iface=17, seed=sum(widths))
+    if acts == "mixed":
+        W.with_activations(prob, ("tanh", "sin", "tanh", "cos"))
+    params = _params(prob, 31)
+    for chunk in (64, 4096):
+        _say(f"widths {widths} {acts} chunk {chunk}")
+        pb, lt, g = run(prob, params, chunk_points=chunk, items_per_slot=1)
+        wl, wg = compare(prob, params, lt, g)
+        _say(f"  worst loss rel {wl:.2e} grad rel {wg:.2e}")
+        pb.close()
