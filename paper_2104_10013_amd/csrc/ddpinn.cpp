@@ -1279,7 +1279,7 @@ int ddp_eval(ddp_problem* p, int n, const float* xy, const int* owner, float* u_
   if (int rc = check_final(p)) return rc;
   if (n < 0 || (n > 0 && (!xy || !owner || !u_out))) return fail(DDP_EINVAL, "bad evaluation arguments");
   const int n_cols = p->d_out + (p->pde == DDP_DIFFUSION2D_INV ? 1 : 0);
-  HIP_TRY(launch_eval(p->d_params, p->d_nets, p->d_sd_net, (int)p->sds.size(), n, xy, owner, u_out, n_cols,
+  HIP_TRY(launch_eval(p->d_kparams, p->d_nets, p->d_sd_net, (int)p->sds.size(), n, xy, owner, u_out, n_cols, p->n_cu,
                       p->stream));
   return DDP_OK;
 }

@@ -24,9 +24,10 @@ hipError_t launch_reduce(const RArgs& ra, int grid, hipStream_t st);
 // refresh the kernel-layout parameter copy of networks [n_begin, n_end)
 hipError_t launch_pack(const float* params, float* kparams, const NetDesc* nets, const int64_t* net_poff,
                        int n_begin, int n_end, int64_t n, hipStream_t st);
-// stitched evaluation: n_cols outputs per point from each owner's networks
-hipError_t launch_eval(const float* params, const NetDesc* nets, const int* sd_net, int n_sd, int n, const float* xy,
-                       const int* owner, float* out, int n_cols, hipStream_t st);
+// stitched evaluation from the kernel-layout copies: n_cols outputs per point
+// from each owner's networks
+hipError_t launch_eval(const float* kparams, const NetDesc* nets, const int* sd_net, int n_sd, int n, const float* xy,
+                       const int* owner, float* out, int n_cols, int n_cu, hipStream_t st);
 
 // Static device scratch of the allocation-free entry point (noalloc.hip):
 // kStaticCounterBytes of work counters, then activation stash slots.

@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 
 #include "act_math.h"
 #include "ddp_internal.h"
@@ -1753,53 +1754,195 @@ __global__ __launch_bounds__(256) void k_pack(const float* params, float* kparam
 
 // Stitched solution (Eq. FSol): average of the owning subdomains' outputs;
 // the columns are the outputs of a subdomain's networks in order (u, or u
-// then K for the inverse problem).  One thread per point.
-__global__ __launch_bounds__(256) void k_eval(const float* params, const NetDesc* nets, const int* sd_net, int n_sd,
-                                              int n, const float* xy, const int* owner, float* out, int n_cols) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float acc[kMaxOut] = {0.f, 0.f, 0.f};
-  int cnt = 0;
-  float h[kMaxWidth], h2[kMaxWidth];
-  const float x = xy[2 * i], y = xy[2 * i + 1];
-  for (int o = 0; o < 4; ++o) {
-    const int q = owner[4 * i + o];
-    if (q < 0 || q >= n_sd) continue;
-    ++cnt;
-    int col = 0;
-    for (int net = sd_net[q]; net < sd_net[q + 1]; ++net) {
-      const NetDesc nd = nets[net];
-      const float* P = params + nd.poff;
-      const int w = nd.width;
-      // slopes follow the output layer in the canonical layout
-      const float* Sl = P + 3 * w + (int64_t)(nd.depth - 1) * (w * w + w) + nd.d_out * w + nd.d_out;
-      // sin and cos as in training (sin_cos); tanh from the library
-      auto phi = [&](float a, int k) {
-        const float yv = nd.adaptive ? nd.slope_n * Sl[k - 1] * a : a;
-        if (nd.act == ACT_TANH) return tanhf(yv);
-        float sn, cs;
-        sin_cos(yv, sn, cs);
-        return nd.act == ACT_SIN ? sn : cs;
-      };
-      for (int m = 0; m < w; ++m) h[m] = phi(fmaf(P[2 * m], x, fmaf(P[2 * m + 1], y, P[2 * w + m])), 1);
-      int64_t off = 3 * w;
-      for (int k = 2; k <= nd.depth; ++k) {
-        for (int m = 0; m < w; ++m) {
-          float a = P[off + w * w + m];
-          for (int j = 0; j < w; ++j) a = fmaf(P[off + m * w + j], h[j], a);
-          h2[m] = phi(a, k);
+// then K for the inverse problem).
+//
+// A block takes pb consecutive points and sorts their (point, owner slot)
+// pairs by subdomain in LDS; its waves then evaluate one network at 16, 32 or
+// 64 of the pairs at once, the points being the columns of the contractions
+// of Tile::contract, with the weights read in fragment order from the L2 cache.
+// Each pair's outputs go to LDS and are summed in the order of the slots.
+// (One thread a point, with the activations in scratch memory, took 3.6 ms for
+// 40,401 points of 16 networks up to 80 wide and 11.1 ms for 10^6 points of 5 x
+// 60, the copies to the device included; now 0.10 and 1.24 ms, mostly copies.)
+constexpr int kEvalPts = 256;            // points per block at most
+
+// value of hidden layer k's activation; sin and cos as in training (sin_cos),
+// tanh from the library
+__device__ __forceinline__ float act_value(int act, float y) {
+  if (act == ACT_TANH) return tanhf(y);
+  float sn, cs;
+  sin_cos(y, sn, cs);
+  return act == ACT_SIN ? sn : cs;
+}
+
+// one network at up to 16 NG points: xs, ys the lane's points (16 i + pc of
+// each of the NG groups), val(i, c, u) takes output c of group i's point
+template <int WP, int NG, class F>
+__device__ __forceinline__ void eval_net(const float* K, const NetDesc& nd, int lane, const float (&xs)[4],
+                                         const float (&ys)[4], F val) {
+  using T = Tile<WP, PDE_POISSON>;
+  constexpr int MB = T::MB;
+  const int g = lane >> 4;
+  const Layout L(WP, nd.depth, nd.d_out);
+  typename T::Streams H, A;
+  for (int k = 1; k <= nd.depth; ++k) {
+    const float c = nd.adaptive ? K[L.k_slope() + k - 1] : 1.f;
+    if (k == 1) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f4 w = *reinterpret_cast<const f4*>(K + (16 * mb + 4 * g + i) * 4);
+#pragma unroll
+          for (int j = 0; j < NG; ++j) A[j][mb][i] = fmaf(w[0], xs[j], fmaf(w[1], ys[j], w[2]));
         }
-        for (int m = 0; m < w; ++m) h[m] = h2[m];
-        off += w * w + w;
+    } else {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const f4 b = *reinterpret_cast<const f4*>(K + L.k_b(k) + 16 * mb + 4 * g);
+#pragma unroll
+        for (int j = 0; j < NG; ++j) A[j][mb] = b;
       }
-      for (int c = 0; c < nd.d_out && col < n_cols; ++c, ++col) {
-        float a = P[off + nd.d_out * w + c];
-        for (int j = 0; j < w; ++j) a = fmaf(P[off + c * w + j], h[j], a);
-        acc[col] += a;
+      T::template contract<0, NG>(reinterpret_cast<const char*>(K + L.k_w(k)), lane, H, A);
+    }
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) H[j][mb][i] = act_value(nd.act, c * A[j][mb][i]);
+  }
+  for (int o = 0; o < nd.d_out; ++o) {
+    float acc[NG] = {};
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const f4 w = *reinterpret_cast<const f4*>(K + L.k_out() + o * WP + 16 * mb + 4 * g);
+#pragma unroll
+      for (int j = 0; j < NG; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[j] = fmaf(w[i], H[j][mb][i], acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < NG; ++j) val(j, o, group_sum(acc[j]) + K[L.k_bout() + o]);
+  }
+}
+
+// two waves per SIMD: 64 points of up to 80 neurons fit the registers, 32 of
+// the wider classes
+__global__ __launch_bounds__(NT, 2) void k_eval(const float* kparams, const NetDesc* nets, const int* sd_net, int n_sd,
+                                                int n, int pb, const float* xy, const int* owner, float* out,
+                                                int n_cols) {
+  __shared__ float s_xy[2 * kEvalPts];
+  __shared__ int s_owner[4 * kEvalPts];            // per pair: subdomain, or -1
+  __shared__ int s_order[4 * kEvalPts];            // pairs by subdomain
+  __shared__ int s_seg[4 * kEvalPts][2];           // per subdomain met: its number, first pair
+  __shared__ float s_val[4 * kEvalPts][kMaxOut];
+  __shared__ int s_min[kWaves], s_cnt[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int p0 = blockIdx.x * pb, np = min(pb, n - p0);
+  for (int i = tid; i < 4 * np; i += NT) {
+    const int q = owner[4 * (int64_t)p0 + i];
+    s_owner[i] = q >= 0 && q < n_sd ? q : -1;
+    if (i < 2 * np) s_xy[i] = xy[2 * (int64_t)p0 + i];
+  }
+  __syncthreads();
+  // pairs by subdomain: the next number up, then its pairs in order
+  int n_seg = 0, filled = 0;
+  for (int last = -1;;) {
+    int q = INT_MAX;
+    for (int i = tid; i < 4 * np; i += NT)
+      if (s_owner[i] > last) q = min(q, s_owner[i]);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) q = min(q, __shfl_xor(q, m));
+    if (lane == 0) s_min[wave] = q;
+    __syncthreads();
+    q = min(min(s_min[0], s_min[1]), min(s_min[2], s_min[3]));
+    if (q == INT_MAX) break;
+    if (tid == 0) {
+      s_seg[n_seg][0] = q;
+      s_seg[n_seg][1] = filled;
+    }
+    ++n_seg;
+    last = q;
+    for (int i0 = 0; i0 < 4 * np; i0 += NT) {
+      const bool mine = i0 + tid < 4 * np && s_owner[i0 + tid] == q;
+      const unsigned long long b = __ballot(mine);
+      if (lane == 0) s_cnt[wave] = __popcll(b);
+      __syncthreads();
+      int at = filled + __popcll(b & ((1ull << lane) - 1));
+      for (int w = 0; w < kWaves; ++w) {
+        at += w < wave ? s_cnt[w] : 0;
+        filled += s_cnt[w];
+      }
+      if (mine) s_order[at] = i0 + tid;
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  // work units of up to 64 pairs of one subdomain, dealt out to the waves
+  int unit = 0;
+  for (int sg = 0; sg < n_seg; ++sg) {
+    const int q = __builtin_amdgcn_readfirstlane(s_seg[sg][0]), b = __builtin_amdgcn_readfirstlane(s_seg[sg][1]);
+    const int e = sg + 1 < n_seg ? __builtin_amdgcn_readfirstlane(s_seg[sg + 1][1]) : filled;
+    const int groups = min(4, (e - b + 63) / 64);   // 16-point groups a unit: every wave gets a share first
+    const int step = 16 * (groups == 3 ? 4 : groups);
+    for (int u0 = b; u0 < e; u0 += step, ++unit) {
+      if ((unit & (kWaves - 1)) != wave) continue;
+      const int end = min(e, u0 + step);
+      int col = 0;
+      for (int net = sd_net[q]; net < sd_net[q + 1]; ++net) {
+        const NetDesc nd = nets[net];
+        const float* K = kparams + nd.koff;
+        const int most = nd.wclass > 80 ? 32 : 64;  // points at once
+        for (int u1 = u0; u1 < end; u1 += most) {
+          const int left = min(end - u1, most);
+          float xs[4], ys[4];
+          int pr[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int k = 16 * j + (lane & 15);
+            pr[j] = s_order[u1 + min(k, left - 1)];
+            xs[j] = s_xy[2 * (pr[j] >> 2)];
+            ys[j] = s_xy[2 * (pr[j] >> 2) + 1];
+          }
+          auto val = [&](int j, int o, float v) {
+            if (lane < 16 && 16 * j + lane < left && col + o < n_cols) s_val[pr[j]][col + o] = v;
+          };
+#define DDP_EVAL(WPV, NGV) eval_net<WPV, NGV>(K, nd, lane, xs, ys, val)
+#define DDP_EVAL_CASE(WPV, BIG)                \
+  case WPV:                                    \
+    if (left <= 16) DDP_EVAL(WPV, 1);          \
+    else if (left <= 32) DDP_EVAL(WPV, 2);     \
+    else DDP_EVAL(WPV, BIG);                   \
+    break;
+          switch (nd.wclass) {
+            DDP_EVAL_CASE(16, 4)
+            DDP_EVAL_CASE(32, 4)
+            DDP_EVAL_CASE(48, 4)
+            DDP_EVAL_CASE(64, 4)
+            DDP_EVAL_CASE(80, 4)
+            DDP_EVAL_CASE(96, 2)
+            DDP_EVAL_CASE(112, 2)
+            default: break;
+          }
+#undef DDP_EVAL_CASE
+#undef DDP_EVAL
+        }
+        col += nd.d_out;
       }
     }
   }
-  for (int c = 0; c < n_cols; ++c) out[(int64_t)i * n_cols + c] = cnt ? acc[c] / cnt : 0.f;
+  __syncthreads();
+  for (int i = tid; i < np; i += NT) {
+    float acc[kMaxOut] = {0.f, 0.f, 0.f};
+    int cnt = 0;
+    for (int o = 0; o < 4; ++o) {
+      if (s_owner[4 * i + o] < 0) continue;
+      ++cnt;
+      for (int c = 0; c < n_cols; ++c) acc[c] += s_val[4 * i + o][c];
+    }
+    for (int c = 0; c < n_cols; ++c) out[(int64_t)(p0 + i) * n_cols + c] = cnt ? acc[c] / cnt : 0.f;
+  }
 }
 
 #endif  // DDP_TRAIN_PDE
@@ -1933,11 +2076,15 @@ hipError_t launch_pack(const float* params, float* kparams, const NetDesc* nets,
   return hipGetLastError();
 }
 
-hipError_t launch_eval(const float* params, const NetDesc* nets, const int* sd_net, int n_sd, int n, const float* xy,
-                       const int* owner, float* out, int n_cols, hipStream_t st) {
+hipError_t launch_eval(const float* kparams, const NetDesc* nets, const int* sd_net, int n_sd, int n, const float* xy,
+                       const int* owner, float* out, int n_cols, int n_cu, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_eval, dim3((n + 255) / 256), dim3(256), 0, st, params, nets, sd_net, n_sd, n, xy, owner, out,
-                     n_cols);
+  // points per block: two blocks a compute unit before a block gets more than
+  // 16, and at most what its LDS holds
+  const int64_t share = ((int64_t)n + 2 * n_cu - 1) / (2 * n_cu);
+  const int pb = (int)std::min<int64_t>(kEvalPts, (share + 15) / 16 * 16);
+  hipLaunchKernelGGL(k_eval, dim3((n + pb - 1) / pb), dim3(NT), 0, st, kparams, nets, sd_net, n_sd, n, pb, xy, owner,
+                     out, n_cols);
   return hipGetLastError();
 }
 

@@ -791,3 +791,40 @@ def test_every_width_class_at_its_edges(widths, acts):
         wl, wg = compare(prob, params, lt, g)
         _say(f"  worst loss rel {wl:.2e} grad rel {wg:.2e}")
         pb.close()
+
+
+def _eval_by_slots(prob, params, xy, owner):
+    """Eq. FSol slot by slot: the mean over the valid owner slots of a point
+    (a subdomain listed twice counts twice, an unknown one not at all)."""
+    cols = prob.d_out + (1 if prob.pde == W.PDE_DIFFUSION2D_INV else 0)
+    acc, cnt = np.zeros((len(xy), cols)), np.zeros(len(xy))
+    for q, s in enumerate(prob.subdomains):
+        one = oracle.eval_stitched(prob, params, xy, np.where(np.arange(4) == 0, q, -1)[None, :].repeat(len(xy), 0))
+        times = (owner == q).sum(1)
+        acc += times[:, None] * one
+        cnt += times
+    return np.where(cnt[:, None] > 0, acc / np.maximum(cnt, 1)[:, None], 0.0)
+
+
+@pytest.mark.parametrize("n", [1, 16, 17, 255, 4097, 140001])
+def test_eval_owners_in_any_order(n):
+    """Blocks of points of every fill, with the owners mixed point by point:
+    repeated, missing and unknown subdomains, every width class, three
+    outputs and the network pairs of the inverse problem.  The bound is that
+    of the grid evaluations above."""
+    mixed = W.custom_box_problem("xpinn", "ns2d_steady", 4, 2,
+                                 [[2] + [w] * d + [3] for w, d in zip((5, 16, 20, 40, 64, 80, 90, 112), (1, 2, 3, 4, 2, 3, 2, 3))],
+                                 [9] * 8, n_bnd_seg=3, n_iface=3, seed=3, coef=(40.0,))
+    W.with_activations(mixed, ("tanh", "sin", "cos"))
+    rng = np.random.default_rng(n)
+    for prob in (mixed, W.c5_xpinn_inverse_diffusion(seed=1, scale=0.005)):
+        params = _params(prob, 17)
+        _say(f"eval of {prob.name} at {n} points")
+        pb = ddpinn.Problem(prob, fused=True)
+        pb.set_params(params)
+        xy = rng.uniform(0.0, 1.0, (n, 2)).astype(np.float32)
+        owner = rng.integers(-2, prob.n_sd + 2, (n, 4)).astype(np.int32)
+        owner[rng.random(n) < 0.5, 1:] = -1
+        got = pb.eval(xy, owner).cpu().numpy()
+        np.testing.assert_allclose(got, _eval_by_slots(prob, params, xy, owner), rtol=1e-5, atol=1e-6)
+        pb.close()
