@@ -85,6 +85,13 @@ __device__ __forceinline__ void dma_to_lds(float* dst, const float* src, int n4,
   }
 }
 
+// The wave's own LDS accesses (in order in hardware) stay in order for the
+// compiler.
+__device__ __forceinline__ void wave_fence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Wait until every vector-memory operation of this wave has completed
 // (s_waitcnt vmcnt(0), the other counters left alone), so its LDS DMA copies
 // have landed; gfx950 does not wait for them at a barrier by itself.
@@ -405,20 +412,30 @@ enum {
 //
 // LDS of a class (bytes): one split weight matrix is WP^2 x 3 parts x 2.
 constexpr int split_matrix_bytes(int wp) { return 6 * wp * wp; }
-// streams staged at once for dW: two where a class is small
-constexpr int stage_streams(int wp) { return wp <= 16 ? 2 : 1; }
-constexpr int stage_bytes(int wp) { return 2 * 3 * 2 * stage_streams(wp) * TP * (wp + 4); }
+// Whether each wave accumulates dW over its own 16 points (all blocks in its
+// registers, one sum over the waves at the end of the layer) instead of a
+// share of the blocks over all 64 points: classes up to 48, where the blocks
+// take at most 36 registers.  No barriers between the streams, and each
+// fragment read from LDS serves a row or column of blocks.
+constexpr bool private_dw(int wp) { return wp <= 48; }
+constexpr int stage_bytes(int wp) { return 2 * 3 * 2 * TP * (wp + 4); }
 // Whether the staging area takes the place of W^T, which is then loaded after
 // dW: where the two together exceed half a compute unit's LDS (class 80,
 // two workgroups per unit) or all of it (class 112).
 constexpr bool stage_over_weights(int wp) { return wp == 80 || wp == 112; }
+// The sums over the waves of the output layer's and layer 1's gradients: in the
+// second forward buffer, or behind the staging area where that is written
+// without a barrier after the output layer (private_dw).
+constexpr int sums_offset(int wp) {
+  return private_dw(wp) ? split_matrix_bytes(wp) + stage_bytes(wp) : split_matrix_bytes(wp) + 4 * wp;
+}
 // weights and staging of a tile: two forward buffers; W^T and the staging
-// area; the first forward buffer and the sums of the output layer or layer 1
+// area; the sums
 constexpr int tile_bytes(int wp, int d_out) {
   const int buf = split_matrix_bytes(wp) + 4 * wp;
   const int rev = stage_bytes(wp) + (stage_over_weights(wp) ? 0 : split_matrix_bytes(wp));
-  const int sums = buf + 4 * kWaves * (d_out > 3 ? d_out : 3) * (wp + 1);
   const int n = 2 * buf > rev ? 2 * buf : rev;
+  const int sums = sums_offset(wp) + 4 * kWaves * (d_out > 3 ? d_out : 3) * (wp + 1);
   return ((n > sums ? n : sums) + 15) / 16 * 16;
 }
 //
@@ -456,8 +473,8 @@ struct Tile {
   static constexpr int NREM = (REM + kWaves - 1) / kWaves;
   static constexpr int WBYTES = split_matrix_bytes(WP);     // one split weight matrix
   static constexpr int BUF = WBYTES + 4 * WP;               // with its bias
-  static constexpr int SN = stage_streams(WP);              // streams staged at once for dW
-  static constexpr int SROWS = SN * TP;                     // rows (stream, point) of the staging area
+  static constexpr bool PRIV = private_dw(WP);
+  static constexpr int SROWS = PRIV ? 16 : TP;              // rows (points) of a staging area
   static constexpr int KL = (DO * WP + NT - 1) / NT;        // output-layer slots per thread
   static constexpr int STASH_LAYER = kWaves * 4 * MB * 1024;  // bytes of one layer's stash
 
@@ -680,8 +697,8 @@ struct Tile {
     if constexpr (STASH) stash_put_layer<GA>(nd, rs, layer, wave, lane, A, H);
   }
 
-  // Staging area of dW: [operand abar, h][part][row][WP + 4] bf16, a row per
-  // (stream, point) and the neurons along it, so that a lane writes its four
+  // Staging area of dW (one per wave where PRIV): [operand abar, h][part][row]
+  // [WP + 4] bf16, a row per point of one stream and the neurons along it, so that a lane writes its four
   // neurons of a block in 8 bytes; the operand fragments, which run along the
   // points, come out of the transposing LDS read (ds_read_b64_tr_b16).  LDS
   // takes writes 16 lanes and 32 banks at a time: rows an odd multiple of 8
@@ -708,6 +725,18 @@ struct Tile {
     const s4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p));
     const s4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 16 * ROW));
     return join(__builtin_bit_cast(b4, x), __builtin_bit_cast(b4, y));
+  }
+  // the operands of a 16-row step: the parts of 16 rows in pairs, so that
+  // three MFMAs hold the six products (as in contract's last block)
+  struct Frag16 {
+    b4 m, h, l;
+  };
+  __device__ __forceinline__ static Frag16 stage_parts16(const char* base, int mb, int lane) {
+    const char* p = base + (4 * (lane >> 4) + ((lane & 15) >> 2)) * ROW + 8 * (lane & 3) + 32 * mb;
+    typedef __attribute__((address_space(3))) s4* lp;
+    return Frag16{__builtin_bit_cast(b4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p))),
+                  __builtin_bit_cast(b4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + PART))),
+                  __builtin_bit_cast(b4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 2 * PART)))};
   }
   struct Frag {
     b8 m, h, l;
@@ -990,7 +1019,7 @@ struct Tile {
                                    float* slot, int64_t slot_floats, const float* sNb, float* sInv, int t_lo,
                                    int t_hi, int roff) {
     char* sW = reinterpret_cast<char*>(lds);
-    float* sA = reinterpret_cast<float*>(sW + BUF);   // sums of the output layer and of layer 1 (the second buffer)
+    float* sA = reinterpret_cast<float*>(sW + sums_offset(WP));   // sums of the output layer and of layer 1
     char* sS = sW + (stage_over_weights(WP) ? 0 : WBYTES);   // staging area of dW
     float* sRed = reinterpret_cast<float*>(sW + tile_bytes(WP, DO));   // [kWaves][kLossTerms]
     float* sSl = sRed + kWaves * kLossTerms;   // [kWaves] slope-gradient sums
@@ -1086,7 +1115,6 @@ struct Tile {
       // dW^L[c][n] = sum over points and streams of ubar_c h^D_n and db^L[c] =
       // sum over points of ubar_c (value stream): each lane's point term, summed
       // over the wave's 16 points by row_sum16 and over the waves through LDS
-      // (the second weight buffer is free: the last forward layer used the first)
       {
         float* sOut = sA;                      // [kWaves][DO][WP], then [kWaves][DO] bias sums
         float* sOutB = sA + kWaves * DO * WP;
@@ -1165,10 +1193,6 @@ struct Tile {
       // db^k = sum_points abar^k_0, and last g^{k-1} = W^{kT} abar^k.  With dW
       // first, a pair of streams of g^{k-1} takes the registers its abar^k
       // leaves, so one layer of streams and one pair are live at most.
-      if constexpr (!KEEP) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (D >= 2) stash_load(rs, D, wave, lane, Sk);
-      }
       for (int k = D; k >= 2; --k) {
         // and again per layer, so address arithmetic is not pinned across layers
         tid = item_tid();
@@ -1180,23 +1204,12 @@ struct Tile {
         // dW^k / db^k accumulators start from the partial row
         float* Rw = R + L.g_w(k);
         float* Rb = R + L.g_b(k);
-        auto block_prior = [&](int mb, int jb) {
-          f4 v;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = device_load(Rw + (16 * mb + 4 * g + i) * WP + 16 * jb + pc);
-          return v;
-        };
-        auto bias_prior = [&](int mb) {
-          f4 v;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = device_load(Rb + 16 * mb + 4 * g + i);
-          return v;
-        };
         // layer k - 1's share of the stash, for h^{k-1} here and for the next
         // layer's adjoint, takes the place of layer k's block by block (KEEP);
         // class 80 has no registers to hold it, loads h^{k-1} stream by
         // stream and the whole again at the end
         Streams Sp;
+        if constexpr (!KEEP) stash_load(rs, k, wave, lane, Sk);
         // abar^k from what was kept of layer k and the incoming g^k (in place of
         // g^k); with a general activation also the layer's slope gradient
         {
@@ -1228,128 +1241,238 @@ struct Tile {
           if constexpr (GA) slope_wave_sum(dc, sSl, lane, wave);
         }
         pin(G);   // the adjoint is done here, not after the branches below
-        f4 dacc[ROWS + 1][MB], drem[NREM + 1], dbias[ROWS + 1], dbrem[NREM + 1];
-        if (first) {
-          const f4 zero = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (PRIV) {
+          // each wave on its own points, one stream after the other
+          constexpr int NE = (MB * MB + kWaves - 1) / kWaves;   // sums of 4 entries per thread
+          f4 before[NE];
+          float bias_before = 0.f;
 #pragma unroll
-          for (int r = 0; r < ROWS; ++r) {
+          for (int r = 0; r < NE; ++r) before[r] = f4{0.f, 0.f, 0.f, 0.f};
+          if (!first) {
 #pragma unroll
-            for (int jb = 0; jb < MB; ++jb) dacc[r][jb] = zero;
-            dbias[r] = zero;
+            for (int r = 0; r < NE; ++r) {
+              const int b = min(wave + r * kWaves, MB * MB - 1);
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                before[r][i] = device_load(Rw + (16 * (b / MB) + 4 * g + i) * WP + 16 * (b % MB) + pc);
+            }
+            if (tid < WP) bias_before = device_load(Rb + tid);
+          }
+          char* my = sS + wave * (6 * PART);
+          f4 dacc[MB][MB], dbias[MB];
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            dbias[mb] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int jb = 0; jb < MB; ++jb) dacc[mb][jb] = f4{0.f, 0.f, 0.f, 0.f};
           }
 #pragma unroll
-          for (int r = 0; r < NREM; ++r) drem[r] = dbrem[r] = zero;
-        } else {
+          for (int s = 0; s < 4; ++s) {
+            f4 hs[MB];
+            h_stream<GA>(nd, s, GA ? slope(nd, K, L, k - 1) : 1.f, Sp, hs);
+            stage_put(my, pc, g, G[s]);
+            stage_put(my + 3 * PART, pc, g, hs);
+            wave_fence();
+            b8 amh[MB], ahl[MB];
 #pragma unroll
-          for (int r = 0; r < ROWS; ++r) {
+            for (int mb = 0; mb < MB; ++mb) {
+              const Frag16 a = stage_parts16(my, mb, lane);
+              amh[mb] = join(a.m, a.h);
+              ahl[mb] = join(a.h, a.l);
+            }
 #pragma unroll
-            for (int jb = 0; jb < MB; ++jb) dacc[r][jb] = block_prior(4 * r + wave, jb);
-            dbias[r] = bias_prior(4 * r + wave);
+            for (int jb = 0; jb < MB; ++jb) {
+              const Frag16 h = stage_parts16(my + 3 * PART, jb, lane);
+              const b8 hh = join(h.h, h.h), mm = join(h.m, h.m), lh = join(h.l, h.h);
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb) dacc[mb][jb] = mma(ahl[mb], lh, dacc[mb][jb]);
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb) dacc[mb][jb] = mma(amh[mb], mm, dacc[mb][jb]);
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb) dacc[mb][jb] = mma(amh[mb], hh, dacc[mb][jb]);
+            }
+            if (s == 0) {   // db^k: the rows times ones
+              const __bf16 o = (__bf16)1.f, z = (__bf16)0.f;
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb)
+                dbias[mb] = mma(amh[mb], b8{o, o, o, o, o, o, o, o}, mma(ahl[mb], b8{z, z, z, z, o, o, o, o}, dbias[mb]));
+            }
+            wave_fence();
           }
+          // the wave's sums in place of its staging area, then their sum over the waves
+          f4* red = reinterpret_cast<f4*>(my);
 #pragma unroll
-          for (int r = 0; r < NREM; ++r) {
-            const int b = min(wave + r * kWaves, REM - 1);
-            drem[r] = block_prior(4 * ROWS + b / MB, b % MB);
-            dbrem[r] = bias_prior(4 * ROWS + b / MB);
+          for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int jb = 0; jb < MB; ++jb) red[(mb * MB + jb) * 64 + lane] = dacc[mb][jb];
+            if (pc == 0) red[MB * MB * 64 + 4 * mb + g] = dbias[mb];
           }
-        }
-        f4 Hn[SN][MB];
-        const bool hf = h_form<GA>(nd);
-        const int hlayer = k - 1 + (hf ? 0 : kMaxDepth);
-        if constexpr (!KEEP) {
+          dma_landed();
+          __syncthreads();   // the sums are there, and W^{kT}
+          if constexpr (GA) {
+            if (nd.adaptive && tid == 0) accum(R + L.g_slope() + k - 1, (sSl[0] + sSl[1]) + (sSl[2] + sSl[3]), first);
+          }
+          const char* all = sS;
 #pragma unroll
-          for (int st = 0; st < SN; ++st) stash_load_stream(rs, hlayer, wave, lane, st, Hn[st]);
-        }
+          for (int r = 0; r < NE; ++r) {
+            const int b = wave + r * kWaves;
+            if (b < MB * MB) {
+              f4 v = before[r];
 #pragma unroll
-        for (int s0 = 0; s0 < 4; s0 += SN) {
-          __syncthreads();   // the previous stage's dW, or the last W^T abar, is done with the staging area
-          if (s0 == 0) {   // (the barrier published the slope sums too)
-            if constexpr (GA) {
-              if (nd.adaptive && tid == 0)
-                accum(R + L.g_slope() + k - 1, (sSl[0] + sSl[1]) + (sSl[2] + sSl[3]), first);
+              for (int w = 0; w < kWaves; ++w) v += reinterpret_cast<const f4*>(all + w * (6 * PART))[b * 64 + lane];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) Rw[(16 * (b / MB) + 4 * g + i) * WP + 16 * (b % MB) + pc] = v[i];
             }
           }
+          if (tid < WP) {
+            float v = bias_before;
 #pragma unroll
-          for (int st = 0; st < SN; ++st) {
-            const int s = s0 + st;
-            stage_put(sS, st * TP + tp, g, G[s]);
+            for (int w = 0; w < kWaves; ++w)
+              v += reinterpret_cast<const float*>(all + w * (6 * PART))[MB * MB * 256 + tid];
+            Rb[tid] = v;
+          }
+        } else {
+          auto block_prior = [&](int mb, int jb) {
+            f4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = device_load(Rw + (16 * mb + 4 * g + i) * WP + 16 * jb + pc);
+            return v;
+          };
+          auto bias_prior = [&](int mb) {
+            f4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = device_load(Rb + 16 * mb + 4 * g + i);
+            return v;
+          };
+          // the wave's left-over block r (the last one again where there is none)
+          auto left_over = [&](int r) { return min(wave + r * kWaves, REM - 1); };
+          f4 dacc[ROWS][MB], drem[NREM + 1], dbias[ROWS], dbrem[NREM + 1];
+          if (first) {
+            const f4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+              for (int jb = 0; jb < MB; ++jb) dacc[r][jb] = zero;
+              dbias[r] = zero;
+            }
+#pragma unroll
+            for (int r = 0; r < NREM; ++r) drem[r] = dbrem[r] = zero;
+          } else {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+              for (int jb = 0; jb < MB; ++jb) dacc[r][jb] = block_prior(4 * r + wave, jb);
+              dbias[r] = bias_prior(4 * r + wave);
+            }
+#pragma unroll
+            for (int r = 0; r < NREM; ++r) {
+              drem[r] = block_prior(4 * ROWS + left_over(r) / MB, left_over(r) % MB);
+              dbrem[r] = bias_prior(4 * ROWS + left_over(r) / MB);
+            }
+          }
+          f4 Hn[MB];
+          const bool hf = h_form<GA>(nd);
+          const int hlayer = k - 1 + (hf ? 0 : kMaxDepth);
+          if constexpr (!KEEP) stash_load_stream(rs, hlayer, wave, lane, 0, Hn);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            __syncthreads();   // the previous stage's dW, or the last W^T abar, is done with the staging area
+            if (s == 0) {      // (the barrier published the slope sums too)
+              if constexpr (GA) {
+                if (nd.adaptive && tid == 0)
+                  accum(R + L.g_slope() + k - 1, (sSl[0] + sSl[1]) + (sSl[2] + sSl[3]), first);
+              }
+            }
+            stage_put(sS, tp, g, G[s]);
             if constexpr (KEEP) {
-              h_stream<GA>(nd, s, GA ? slope(nd, K, L, k - 1) : 1.f, Sp, Hn[st]);
+              h_stream<GA>(nd, s, GA ? slope(nd, K, L, k - 1) : 1.f, Sp, Hn);
             } else if (s == 0 && hf) {
 #pragma unroll
               for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                   float t, s1;
-                  tanh_s1(Hn[st][mb][i], t, s1);
-                  Hn[st][mb][i] = t;
+                  tanh_s1(Hn[mb][i], t, s1);
+                  Hn[mb][i] = t;
                 }
             }
-            stage_put(sS + 3 * PART, st * TP + tp, g, Hn[st]);
+            stage_put(sS + 3 * PART, tp, g, Hn);
             if constexpr (!KEEP) {
-              if (s0 + SN < 4) stash_load_stream(rs, hlayer, wave, lane, s + SN, Hn[st]);
+              if (s < 3) stash_load_stream(rs, hlayer, wave, lane, s + 1, Hn);
             }
-          }
-          // every wave is past W^{k+1 T}: W^{kT} streams in during dW^k (issued here,
-          // behind the waits for the stash)
-          if (!stage_over_weights(WP) && s0 == 0 && k < D) fetch_wt(sW, K, L, k, wave, lane);
-          __syncthreads();
-          // fragments are read one block ahead of their MFMAs
-#pragma unroll (MB <= 2 ? SROWS / 32 : 1)
-          for (int c = 0; c < SROWS / 32; ++c) {
-            const bool value = s0 == 0 && c < TP / 32;   // rows of the value stream: db^k
+            // every wave is past W^{k+1 T}: W^{kT} streams in during dW^k (issued here,
+            // behind the waits for the stash)
+            if (!stage_over_weights(WP) && s == 0 && k < D) fetch_wt(sW, K, L, k, wave, lane);
+            __syncthreads();
+            // fragments are read one block ahead of their MFMAs
+            constexpr int NC = SROWS / 32;
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
-              const Frag a = stage_parts(sS, c, 4 * r + wave, lane);
-              Frag h = stage_parts(sS + 3 * PART, c, 0, lane);
-              if (value) dbias[r] = row_sums(a, dbias[r]);
+              Frag a = stage_parts(sS, 0, 4 * r + wave, lane), h = stage_parts(sS + 3 * PART, 0, 0, lane);
 #pragma unroll
-              for (int jb = 0; jb < MB; ++jb) {
-                Frag hn = h;
-                if (jb + 1 < MB) hn = stage_parts(sS + 3 * PART, c, jb + 1, lane);
+              for (int c = 0; c < NC; ++c) {
+                if (s == 0) dbias[r] = row_sums(a, dbias[r]);
+#pragma unroll
+                for (int jb = 0; jb < MB; ++jb) {
+                  Frag an = a, hn = h;
+                  if (jb + 1 < MB) {
+                    hn = stage_parts(sS + 3 * PART, c, jb + 1, lane);
+                  } else if (c + 1 < NC) {
+                    an = stage_parts(sS, c + 1, 4 * r + wave, lane);
+                    hn = stage_parts(sS + 3 * PART, c + 1, 0, lane);
+                  }
+                  __builtin_amdgcn_sched_barrier(0);
+                  dacc[r][jb] = mma6(a, h, dacc[r][jb]);
+                  a = an;
+                  h = hn;
+                }
+              }
+            }
+            if constexpr (NREM > 0) {
+              Frag a = stage_parts(sS, 0, 4 * ROWS + left_over(0) / MB, lane);
+              Frag h = stage_parts(sS + 3 * PART, 0, left_over(0) % MB, lane);
+#pragma unroll
+              for (int t = 0; t < NREM * NC; ++t) {
+                Frag an = a, hn = h;
+                if (t + 1 < NREM * NC) {
+                  const int b = left_over((t + 1) / NC);
+                  an = stage_parts(sS, (t + 1) % NC, 4 * ROWS + b / MB, lane);
+                  hn = stage_parts(sS + 3 * PART, (t + 1) % NC, b % MB, lane);
+                }
                 __builtin_amdgcn_sched_barrier(0);
-                dacc[r][jb] = mma6(a, h, dacc[r][jb]);
+                if (s == 0) dbrem[t / NC] = row_sums(a, dbrem[t / NC]);
+                drem[t / NC] = mma6(a, h, drem[t / NC]);
+                a = an;
                 h = hn;
               }
             }
+          }
+          if constexpr (stage_over_weights(WP)) {
+            __syncthreads();   // every wave is done with the staging area, which now receives W^{kT}
+            fetch_wt(sW, K, L, k, wave, lane);
+          }
+          auto block_store = [&](int mb, int jb, f4 v) {
 #pragma unroll
-            for (int r = 0; r < NREM; ++r) {
-              const int b = wave + r * kWaves;
-              if (b < REM) {
-                const Frag a = stage_parts(sS, c, 4 * ROWS + b / MB, lane);
-                const Frag h = stage_parts(sS + 3 * PART, c, b % MB, lane);
-                if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);
-                if (value) dbrem[r] = row_sums(a, dbrem[r]);
-                drem[r] = mma6(a, h, drem[r]);
-              }
+            for (int i = 0; i < 4; ++i) Rw[(16 * mb + 4 * g + i) * WP + 16 * jb + pc] = v[i];
+          };
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+            for (int jb = 0; jb < MB; ++jb) block_store(4 * r + wave, jb, dacc[r][jb]);
+            if (pc == 0) *reinterpret_cast<f4*>(Rb + 16 * (4 * r + wave) + 4 * g) = dbias[r];
+          }
+#pragma unroll
+          for (int r = 0; r < NREM; ++r) {
+            const int b = wave + r * kWaves;
+            if (b < REM) {
+              const int mb = 4 * ROWS + b / MB;
+              block_store(mb, b % MB, drem[r]);
+              if (b % MB == 0 && pc == 0) *reinterpret_cast<f4*>(Rb + 16 * mb + 4 * g) = dbrem[r];
             }
           }
+          dma_landed();
+          __syncthreads();   // W^{kT} is in LDS
         }
-        if constexpr (stage_over_weights(WP)) {
-          __syncthreads();   // every wave is done with the staging area, which now receives W^{kT}
-          fetch_wt(sW, K, L, k, wave, lane);
-        }
-        auto block_store = [&](int mb, int jb, f4 v) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) Rw[(16 * mb + 4 * g + i) * WP + 16 * jb + pc] = v[i];
-        };
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-#pragma unroll
-          for (int jb = 0; jb < MB; ++jb) block_store(4 * r + wave, jb, dacc[r][jb]);
-          if (pc == 0) *reinterpret_cast<f4*>(Rb + 16 * (4 * r + wave) + 4 * g) = dbias[r];
-        }
-#pragma unroll
-        for (int r = 0; r < NREM; ++r) {
-          const int b = wave + r * kWaves;
-          if (b < REM) {
-            const int mb = 4 * ROWS + b / MB;
-            block_store(mb, b % MB, drem[r]);
-            if (b % MB == 0 && pc == 0) *reinterpret_cast<f4*>(Rb + 16 * mb + 4 * g) = dbrem[r];
-          }
-        }
-        dma_landed();
-        __syncthreads();   // W^{kT} is in LDS
         {
           if constexpr (MB >= 4) pin(G);   // else the parts just staged are kept for W^T abar, half as many registers again
           Streams Gn;
@@ -1366,13 +1489,15 @@ struct Tile {
           } else {
             contract<0, 2>(sW, lane, G, Gn);
             contract<2, 2>(sW, lane, G, Gn);
-            __builtin_amdgcn_sched_barrier(0);
-            if (k > 2) stash_load(rs, k - 1, wave, lane, Sk);
           }
 #pragma unroll
           for (int s = 0; s < 4; ++s)
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) G[s][mb] = Gn[s][mb];
+        }
+        if constexpr (PRIV) {
+          __syncthreads();   // every wave is done with W^{kT} and with the sums
+          if (k > 2) fetch_wt(sW, K, L, k - 1, wave, lane);
         }
       }
 
