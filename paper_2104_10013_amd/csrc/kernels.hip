@@ -524,11 +524,6 @@ struct Tile {
   __device__ static void fetch_wt(char* sW, const float* K, const Layout& L, int k, int wave, int lane) {
     dma_to_lds(reinterpret_cast<float*>(sW), K + L.k_wt(k), WBYTES / 16, wave, lane);
   }
-  __device__ static void stage_wb(char* sW, const float* src, int tid) {
-    f4* d4 = reinterpret_cast<f4*>(sW);
-    for (int idx = tid; idx < BUF / 16; idx += NT) d4[idx] = reinterpret_cast<const f4*>(src)[idx];
-  }
-
   // Y_s += W X_s for streams S0 .. S0 + NS - 1 (w: a split matrix in LDS, in
   // fragment order, so every read is 16 bytes a lane without bank conflicts).
   // Each weight fragment read feeds 6 NS MFMAs; a stream's values are split
@@ -829,6 +824,9 @@ struct Tile {
     }
   }
 
+  // the point's forcing (residual points) or target values, loaded at the top
+  // of the tile
+  static constexpr int NTGT = DO > NEQ ? DO : NEQ;
   // loss contributions and output seeds of one point (the derivative of the
   // item's share of J_q with respect to the output streams)
   //
@@ -837,8 +835,8 @@ struct Tile {
   // L = K Lap u + K_x u_x + K_y u_y (Eq. heq expanded), and kb receives the
   // seeds of (K, K_x, K_y).  EPI_SEED: the seeds come from inv + 3 TP.
   template <int MODE>
-  __device__ __forceinline__ static void epilogue(const KArgs& ka, const Item& it, const NetDesc& nd, int pt, int tp, bool valid,
-                                  const float* nb, const float* inv, const float (&u)[DO][4], float (&ub)[DO][4],
+  __device__ __forceinline__ static void epilogue(const KArgs& ka, const Item& it, const NetDesc& nd, int tp, bool valid,
+                                  const float (&tgt)[NTGT], const float* nb, const float* inv, const float (&u)[DO][4], float (&ub)[DO][4],
                                   float (&loss)[kLossTerms], float (&kb)[3]) {
 #pragma unroll
     for (int c = 0; c < DO; ++c)
@@ -849,7 +847,6 @@ struct Tile {
     kb[0] = kb[1] = kb[2] = 0.f;
     if (!valid) return;
     const float inv_n = it.inv_n;
-    const int gp = it.begin + pt;
     if constexpr (MODE == EPI_SEED) {
 #pragma unroll
       for (int s = 0; s < 3; ++s) ub[0][s] = inv[3 * TP + 3 * tp + s];
@@ -859,7 +856,7 @@ struct Tile {
       const float L = fmaf(K, u[0][3], fmaf(Kx, u[0][1], Ky * u[0][2]));
       float c;
       if (it.kind == KIND_RES) {
-        const float F = L - ka.res_f[gp];
+        const float F = L - tgt[0];
         loss[1] += F * F;
         c = 2.f * nd.loss_w[1] * F * inv_n;
       } else {
@@ -880,7 +877,7 @@ struct Tile {
     }
     if (it.kind == KIND_RES) {
       float F[NEQ];
-      Op<PDE>::residual(u, ka.res_f + (int64_t)gp * ka.n_eq, ka.coef0, F);
+      Op<PDE>::residual(u, tgt, ka.coef0, F);
       float c[NEQ];
 #pragma unroll
       for (int e = 0; e < NEQ; ++e) {
@@ -889,10 +886,9 @@ struct Tile {
       }
       Op<PDE>::residual_adj(u, c, ka.coef0, ub);
     } else if (it.kind == KIND_DATA || it.kind == KIND_AUX) {
-      const float* tg = it.kind == KIND_DATA ? ka.dat_g : ka.aux_g;
 #pragma unroll
       for (int c = 0; c < DO; ++c) {
-        const float d = u[c][0] - tg[(int64_t)gp * DO + c];
+        const float d = u[c][0] - tgt[c];
         loss[0] += d * d;
         ub[c][0] += 2.f * nd.loss_w[0] * d * inv_n;
       }
@@ -967,6 +963,7 @@ struct Tile {
     const int gp = it.begin + t0 + tp;
     const float x = valid ? xyv[2 * (int64_t)gp] : 0.f;
     const float y = valid ? xyv[2 * (int64_t)gp + 1] : 0.f;
+    if (nd.depth >= 2) fetch_wb(wbuf(sW, nd.depth, 2), K, L, 2, wave, lane);   // (the caller's barrier freed the buffers)
     Streams H;
     {
       Streams A;
@@ -975,10 +972,10 @@ struct Tile {
     }
     const __amdgpu_buffer_rsrc_t none = __builtin_amdgcn_make_buffer_rsrc(lds, 0, 0, 0x00020000);  // unused
     for (int k = 2; k <= nd.depth; ++k) {
+      dma_landed();
       __syncthreads();
-      stage_wb(sW, K + L.k_w(k), tid);
-      __syncthreads();
-      hidden_layer<false, GA>(sW, g, H, none, k, wave, lane, nd, slope(nd, K, L, k));
+      if (k < nd.depth) fetch_wb(wbuf(sW, nd.depth, k + 1), K, L, k + 1, wave, lane);
+      hidden_layer<false, GA>(wbuf(sW, nd.depth, k), g, H, none, k, wave, lane, nd, slope(nd, K, L, k));
     }
     float u[DO][4];
     out_fwd(K + L.k_out(), K + L.k_bout(), g, H, u);
@@ -1016,7 +1013,7 @@ struct Tile {
 
   template <int MODE, int PHASE, bool GA>
   __device__ __forceinline__ static void run_train(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds,
-                                   float* slot, int64_t slot_floats, const float* sNb, float* sInv, int t_lo,
+                                   float* slot, int64_t slot_floats, const float* sNb, float* sInv, float* sOW, int t_lo,
                                    int t_hi, int roff) {
     char* sW = reinterpret_cast<char*>(lds);
     float* sA = reinterpret_cast<float*>(sW + sums_offset(WP));   // sums of the output layer and of layer 1
@@ -1046,8 +1043,17 @@ struct Tile {
       const int gp = it.begin + pt;
       const float x = valid ? xy[2 * (int64_t)gp] : 0.f;
       const float y = valid ? xy[2 * (int64_t)gp + 1] : 0.f;
+      float tgt[NTGT] = {};
+      if (valid && MODE != EPI_SEED && it.kind != KIND_IFACE) {
+        const float* tg = it.kind == KIND_RES ? ka.res_f : it.kind == KIND_DATA ? ka.dat_g : ka.aux_g;
+        const int nt = it.kind == KIND_RES ? NEQ : DO;
+#pragma unroll
+        for (int c = 0; c < NTGT; ++c)
+          if (c < nt) tgt[c] = tg[(int64_t)gp * nt + c];
+      }
       __syncthreads();  // previous tile done with LDS
-      // the first hidden layer's weights stream in during layer 1
+      // the output layer's weights and the first hidden layer's stream in during layer 1
+      dma_to_lds(sOW, K + L.k_out(), DO * WP / 4 + 1, wave, lane);
       if (PHASE != PH_BWD && D >= 2) fetch_wb(wbuf(sW, D, 2), K, L, 2, wave, lane);
 
       // ---- forward: Taylor streams through every layer, stashing what the
@@ -1081,12 +1087,16 @@ struct Tile {
         if (k < D) fetch_wb(wbuf(sW, D, k + 1), K, L, k + 1, wave, lane);
         hidden_layer<true, GA>(wbuf(sW, D, k), g, H, rs, k, wave, lane, nd, slope(nd, K, L, k));
       }
+      if (PHASE == PH_BWD || D < 2) {   // else a hidden layer's barrier has published the output weights
+        dma_landed();
+        __syncthreads();
+      }
       float u[DO][4];
       if constexpr (PHASE == PH_BWD) {
 #pragma unroll
         for (int c = 0; c < DO; ++c) u[c][0] = u[c][1] = u[c][2] = u[c][3] = 0.f;   // seeds come from LDS
       } else {
-        out_fwd(K + L.k_out(), K + L.k_bout(), g, H, u);
+        out_fwd(sOW, sOW + DO * WP, g, H, u);
       }
       if constexpr (PHASE == PH_FWD) {
         if (g == 0) {
@@ -1098,7 +1108,7 @@ struct Tile {
 
       // ---- loss terms and output seeds
       float ub[DO][4], loss[kLossTerms], kb[3];
-      epilogue<MODE>(ka, it, nd, pt, tp, valid, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss, kb);
+      epilogue<MODE>(ka, it, nd, tp, valid, tgt, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss, kb);
 #pragma unroll
       for (int t = 0; t < kLossTerms; ++t) {
         const float v = row_sum16(loss[t]);   // (the same in every lane group)
@@ -1138,7 +1148,7 @@ struct Tile {
       Streams G;
       __builtin_amdgcn_sched_barrier(0);
       {
-        const float* WL = K + L.k_out();
+        const float* WL = sOW;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
           f4 wl[DO];
@@ -1576,7 +1586,7 @@ constexpr int lds_tile_floats() {
 }
 template <int WP, int PDE>
 constexpr int lds_train_floats() {
-  return lds_tile_floats<WP, PDE>() + 6 * TP + (PDE == PDE_INV ? 9 * TP : 0);
+  return lds_tile_floats<WP, PDE>() + 6 * TP + (PDE == PDE_INV ? 9 * TP : 0) + Op<PDE>::DO * WP + 4;
 }
 
 // bytes of dynamic LDS the train kernel is launched with: the tile buffers and
@@ -1596,6 +1606,7 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
                                          float* slot) {
   float* sNb = lds + lds_tile_floats<WPMAX, PDE>();
   float* sInv = sNb + 6 * TP;
+  float* sOW = sInv + (PDE == PDE_INV ? 9 * TP : 0);   // output-layer weights and biases of the network in training
 #define DDP_CASE(WPV, ...)                                    \
   case WPV:                                                   \
     if constexpr (WPV <= WPMAX) Tile<WPV, PDE>::__VA_ARGS__;  \
@@ -1634,11 +1645,11 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
           __syncthreads();
         }
         DDP_SWITCH(ndk.wclass, template run_train<EPI_SEED, PH_FWD, GA>(ka, it, ndk, lds, slot + half, half,
-                                                                            sNb, sInv, t0, t0 + 1, nd.gsize))
+                                                                            sNb, sInv, sOW, t0, t0 + 1, nd.gsize))
         DDP_SWITCH(nd.wclass,
-                   template run_train<EPI_INV_U, PH_ALL, GA>(ka, it, nd, lds, slot, half, sNb, sInv, t0, t0 + 1, 0))
+                   template run_train<EPI_INV_U, PH_ALL, GA>(ka, it, nd, lds, slot, half, sNb, sInv, sOW, t0, t0 + 1, 0))
         DDP_SWITCH(ndk.wclass, template run_train<EPI_SEED, PH_BWD, GA>(ka, it, ndk, lds, slot + half, half,
-                                                                            sNb, sInv, t0, t0 + 1, nd.gsize))
+                                                                            sNb, sInv, sOW, t0, t0 + 1, nd.gsize))
       }
       return;
     }
@@ -1651,7 +1662,7 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
   }
   DDP_SWITCH(nd.wclass, template run_train<EPI_OWN, PH_ALL, GA>(ka, it, nd, lds, slot,
                                                        PDE == PDE_INV ? ka.scratch_slot / 2 : ka.scratch_slot, sNb,
-                                                       sInv, 0, it.count, 0))
+                                                       sInv, sOW, 0, it.count, 0))
 #undef DDP_SWITCH
 #undef DDP_CASE
 }
