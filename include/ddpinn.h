@@ -82,15 +82,16 @@ enum { DDP_RESIDUAL = 0, DDP_DATA = 1, DDP_DATA_AUX = 2 };
 enum {
   DDP_OPT_CHUNK_POINTS = 0, /* upper bound of points per work item (default 1024) */
   DDP_OPT_BLOCKS_PER_CU = 1, /* persistent workgroups per compute unit (0 = as many as fit) */
-  DDP_OPT_ITEMS_PER_SLOT = 2, /* work items per resident workgroup the plan aims for (default 4) */
+  DDP_OPT_ITEMS_PER_SLOT = 2, /* work items per resident workgroup the plan aims for (default 2) */
   DDP_OPT_RECOMPUTE = 3, /* 0 (default) or 1, taken and reported as given; it selects nothing any
                            more: the forward pass stores what both former policies need, the value
                            pre-activation and the post-activation derivative streams of a layer */
   DDP_OPT_CONCURRENT = 4, /* fused step whose items need two train kernels (networks both at most
                             80 and wider than 80): 1 = the two persistent launches run side by
                             side on two streams (each with its own activation stash), so the
-                            second takes the compute units the first's drained workgroups free;
-                            0 (default) = one after the other.  No effect with one launch. */
+                            second takes the compute units the first's drained workgroups free
+                            (default: 2.1 instead of 2.4 ms on the inverse diffusion problem);
+                            0 = one after the other.  No effect with one launch. */
   DDP_OPT_TAIL = 5 /* fused step: percent (0..100, default 0) of each subdomain's residual points
                       cut into one-tile (64-point) work items instead of the plan's longer ones;
                       the cost-ordered work queue hands them out last, so the workgroups that

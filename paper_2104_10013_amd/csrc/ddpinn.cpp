@@ -81,9 +81,9 @@ struct ddp_problem {
   std::vector<HostIf> ifs;
   int64_t chunk_points = 1024;  // upper bound of points per work item
   int blocks_per_cu = 0;         // 0: from the occupancy query
-  int items_per_slot = 4;        // work items per resident workgroup the plan aims for
+  int items_per_slot = 2;        // work items per resident workgroup the plan aims for
   int recompute = 0;             // DDP_OPT_RECOMPUTE as given (selects nothing)
-  int concurrent = 0;            // fused step with several train launches: 1 = they run side by side
+  int concurrent = 1;            // fused step with several train launches: 1 = they run side by side
   int tail_pct = 0;              // percent of each subdomain's residual points in one-tile items
 
   // plan
@@ -222,6 +222,17 @@ double item_cost(const std::vector<NetDesc>& nets, const Item& it) {
   return c;
 }
 
+// Kilocycles of one 64-point tile of a network, as measured per class with the
+// workgroups per compute unit of its kernel (two; one from 96 wide): a share
+// per tile and a share per hidden-to-hidden product.  Class 80 costs 4 times
+// class 32, not the 6 times of its matrix work: narrow networks are bound by
+// the activation rule and by latency.
+double tile_time(const NetDesc& nd) {
+  static const double fixed[7] = {14, 17, 23, 28, 33, 36, 40}, layer[7] = {11, 17, 28, 42, 65, 58, 76};
+  const int b = nd.wclass / 16 - 1;
+  return fixed[b] + layer[b] * (nd.depth - 1);
+}
+
 int build_plan(ddp_problem* p) {
   const int n_sd = (int)p->sds.size();
   if (n_sd == 0) return fail(DDP_EINVAL, "no subdomains");
@@ -322,12 +333,15 @@ int build_plan(ddp_problem* p) {
   // items carry similar work (about 1/items_per_slot of an even share per
   // workgroup), between one 64-point tile and chunk_max points: cheap networks
   // get long items, expensive ones short.
+  //
+  // The lengths follow the measured time of a point (tile_time), the queue
+  // order the matrix work.  With the lengths after the matrix work too, and 4
+  // items a workgroup instead of 2, narrow networks got items that outlasted
+  // the launch: the 16-subdomain benchmark took 523 instead of 465 us a step,
+  // steady Navier-Stokes 393 / 377, space-time Burgers 143 / 128.
   auto point_cost = [&](int q) {
-    Item one{};
-    one.q = p->sd_net[q];
-    one.kind = KIND_RES;
-    one.count = 1;
-    return item_cost(p->nets, one);
+    const NetDesc& nd = p->nets[p->sd_net[q]];
+    return tile_time(nd) + (nd.pair >= 0 ? tile_time(p->nets[nd.pair]) : 0.0);
   };
   double total_cost = 0.0;
   for (int q = 0; q < n_sd; ++q) {
