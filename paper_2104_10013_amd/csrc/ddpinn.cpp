@@ -73,6 +73,8 @@ int width_class(int w) { return ((w + 15) / 16) * 16; }
 
 }  // namespace
 
+constexpr int kGraphSteps = 10;   // steps of the longer step graph
+
 struct ddp_problem {
   int method = 0, pde = 0;
   double coef[4] = {0, 0, 0, 0};
@@ -143,8 +145,10 @@ struct ddp_problem {
   int* d_sd_net = nullptr;
   int *d_net_row_ptr = nullptr, *d_sd_loss_ptr = nullptr, *d_loss_rows = nullptr;
   int64_t* d_row_prow = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
+  // the fused step as graphs: one step, and kGraphSteps in a row (a graph
+  // launch costs 8.6 us between two steps)
+  hipGraph_t graph[2] = {nullptr, nullptr};
+  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
   std::vector<void*> allocations;       // static buffers
   std::vector<void*> plan_allocations;  // buffers that depend on the work plan
   int n_cu = 0, occupancy = 0;
@@ -642,11 +646,17 @@ int enqueue_step(ddp_problem* p, hipStream_t st, int do_adam, float* grad_out, f
   return DDP_OK;
 }
 
+void release_graphs(ddp_problem* p) {
+  for (int i = 0; i < 2; ++i) {
+    if (p->graph_exec[i]) hipGraphExecDestroy(p->graph_exec[i]);
+    if (p->graph[i]) hipGraphDestroy(p->graph[i]);
+    p->graph_exec[i] = nullptr;
+    p->graph[i] = nullptr;
+  }
+}
+
 void release(ddp_problem* p) {
-  if (p->graph_exec) hipGraphExecDestroy(p->graph_exec);
-  if (p->graph) hipGraphDestroy(p->graph);
-  p->graph_exec = nullptr;
-  p->graph = nullptr;
+  release_graphs(p);
   for (void* a : p->allocations) hipFree(a);
   p->allocations.clear();
   for (void* a : p->plan_allocations) hipFree(a);
@@ -877,14 +887,11 @@ namespace {
 
 // Build the work plan for the current options and (re)create everything that
 // depends on it: work items, gradient / loss partial rows, row lists, the
-// activation stash, work counters and the step graph.
-int install_plan(ddp_problem* p) {
+// activation stash, work counters and (graphs) the step graphs.
+int install_plan(ddp_problem* p, bool graphs = true) {
   const int n_sd = (int)p->sds.size();
   p->plan_ok = false;
-  if (p->graph_exec) hipGraphExecDestroy(p->graph_exec);
-  if (p->graph) hipGraphDestroy(p->graph);
-  p->graph_exec = nullptr;
-  p->graph = nullptr;
+  release_graphs(p);
   if (p->stream) HIP_TRY(hipStreamSynchronize(p->stream));
   for (void* a : p->plan_allocations) hipFree(a);
   p->plan_allocations.clear();
@@ -930,21 +937,24 @@ int install_plan(ddp_problem* p) {
   HIP_TRY(hipMemset(p->d_partial, 0, (size_t)std::max<int64_t>(1, p->partial_floats) * sizeof(float)));
   HIP_TRY(hipMemset(p->d_loss_part, 0, std::max<size_t>(1, p->titems.size() * kLossTerms) * sizeof(float)));
   HIP_TRY(hipDeviceSynchronize());
-  if (p->fused) {
-    // one training step as a graph: captured on a private stream, replayed on
+  if (p->fused && graphs) {
+    // the training step as graphs: captured on a private stream, replayed on
     // the caller's stream
     if (!p->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
-    HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-    rc = enqueue_step(p, p->cap_stream, 1, nullptr, p->d_loss);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(p->cap_stream, &g);
-    if (rc) {
-      if (g) hipGraphDestroy(g);
-      return rc;
+    for (int i = 0; i < 2; ++i) {
+      HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
+      for (int s = 0; s < (i == 0 ? 1 : kGraphSteps) && rc == DDP_OK; ++s)
+        rc = enqueue_step(p, p->cap_stream, 1, nullptr, p->d_loss);
+      hipGraph_t g = nullptr;
+      hipError_t e = hipStreamEndCapture(p->cap_stream, &g);
+      if (rc) {
+        if (g) hipGraphDestroy(g);
+        return rc;
+      }
+      if (e != hipSuccess) return fail(DDP_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
+      p->graph[i] = g;
+      HIP_TRY(hipGraphInstantiate(&p->graph_exec[i], p->graph[i], nullptr, nullptr, 0));
     }
-    if (e != hipSuccess) return fail(DDP_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-    p->graph = g;
-    HIP_TRY(hipGraphInstantiate(&p->graph_exec, p->graph, nullptr, nullptr, 0));
   }
   p->plan_ok = true;
   return DDP_OK;
@@ -1054,7 +1064,7 @@ namespace {
 
 // The autotuner's search: every candidate plan timed over iters passes, the
 // three fastest again over three interleaved rounds; best receives the
-// winner.  Leaves the last candidate installed.
+// winner.  Leaves the last candidate installed, without its step graphs.
 int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, float* best_ms) {
   const int64_t chunks[] = {256, 512, 1024, 2048};
   const int ipss[] = {1, 2, 4, 8};
@@ -1072,7 +1082,7 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
     p->blocks_per_cu = k.bpc;
     p->concurrent = k.conc;
     p->tail_pct = k.tail;
-    if (int rc = install_plan(p)) return rc;
+    if (int rc = install_plan(p, false)) return rc;
     if (int rc = enqueue_step(p, p->stream, 0, nullptr, p->d_loss)) return rc;
     HIP_TRY(hipEventRecord(ev[0], p->stream));
     for (int i = 0; i < n; ++i)
@@ -1089,7 +1099,7 @@ int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, fl
     p->recompute = 0;
     p->concurrent = 0;
     p->tail_pct = 0;
-    if (int rc = install_plan(p)) return rc;
+    if (int rc = install_plan(p, false)) return rc;
     int max_occ = p->occupancy;
     for (const ddp_problem::Launch& l : p->launches) max_occ = std::max(max_occ, l.occupancy);
     // side-by-side launches only where the step has more than one
@@ -1202,9 +1212,9 @@ int ddp_set_params(ddp_problem* p, int sd, const float* flat, int on_device) {
   if (int rc = check_final(p)) return rc;
   if (sd < 0 || sd >= (int)p->sds.size() || !flat) return fail(DDP_EINVAL, "bad subdomain or null pointer");
   const size_t n = (size_t)(p->sd_poff[sd + 1] - p->sd_poff[sd]);
-  HIP_TRY(hipMemcpyAsync(p->d_params + p->sd_poff[sd], flat, n * sizeof(float),
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, p->stream));
-  HIP_TRY(launch_pack(p->d_params, p->d_kparams, p->d_nets, p->d_net_poff, p->sd_net[sd], p->sd_net[sd + 1],
+  float* own = p->d_params + p->sd_poff[sd];
+  if (!on_device) HIP_TRY(hipMemcpyAsync(own, flat, n * sizeof(float), hipMemcpyHostToDevice, p->stream));
+  HIP_TRY(launch_pack(on_device ? flat : own, p->d_params, p->d_kparams, p->d_nets, p->d_net_poff, p->sd_net[sd], p->sd_net[sd + 1],
                       (int64_t)n, p->stream));
   if (!on_device) HIP_TRY(hipStreamSynchronize(p->stream));
   return DDP_OK;
@@ -1250,10 +1260,13 @@ int ddp_loss_and_grad_static(ddp_problem* p, float* loss_terms, float* grad) {
 int ddp_step(ddp_problem* p, int n_steps, float* loss_terms) {
   if (int rc = check_final(p)) return rc;
   if (n_steps < 0) return fail(DDP_EINVAL, "negative step count");
-  for (int s = 0; s < n_steps; ++s) {
+  for (int s = 0; s < n_steps;) {
     if (p->fused) {
-      HIP_TRY(hipGraphLaunch(p->graph_exec, p->stream));
+      const int many = n_steps - s >= kGraphSteps;
+      HIP_TRY(hipGraphLaunch(p->graph_exec[many], p->stream));
+      s += many ? kGraphSteps : 1;
     } else {
+      ++s;
       if (int rc = enqueue_step(p, p->stream, 1, nullptr, p->d_loss)) return rc;
     }
   }

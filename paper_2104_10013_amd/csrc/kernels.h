@@ -21,8 +21,9 @@ hipError_t launch_train(int pde, int wpmax, bool ga, const KArgs& ka, int grid, 
 hipError_t launch_reset_counter(int* c, hipStream_t st);
 // gradient reduction, loss reduction and optional Adam; re-arms ra.counter_reset
 hipError_t launch_reduce(const RArgs& ra, int grid, hipStream_t st);
-// refresh the kernel-layout parameter copy of networks [n_begin, n_end)
-hipError_t launch_pack(const float* params, float* kparams, const NetDesc* nets, const int64_t* net_poff,
+// take the canonical parameters of networks [n_begin, n_end) from src (device;
+// may be their place in params) and refresh the kernel-layout copy
+hipError_t launch_pack(const float* src, float* params, float* kparams, const NetDesc* nets, const int64_t* net_poff,
                        int n_begin, int n_end, int64_t n, hipStream_t st);
 // stitched evaluation from the kernel-layout copies: n_cols outputs per point
 // from each owner's networks

@@ -1812,6 +1812,16 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
     if (i < ra.net_poff[q + 1]) {
       const ParamPos pp = param_map(nd, (int)(i - ra.net_poff[q]));
       const float* P = ra.partial + pp.g;
+      // the optimiser's state is on its way while the rows are summed
+      float m0 = 0.f, v0 = 0.f, th0 = 0.f, bc1 = 1.f, bc2 = 1.f;
+      if (ra.do_adam) {
+        m0 = ra.adam_m[i];
+        v0 = ra.adam_v[i];
+        th0 = ra.params[i];
+        const float tstep = (float)(ra.tstate[0] + 1);
+        bc1 = 1.f - powf(b1, tstep);
+        bc2 = 1.f - powf(b2, tstep);
+      }
       float a[kRedLanes];
 #pragma unroll
       for (int j = 0; j < kRedLanes; ++j) a[j] = 0.f;
@@ -1830,16 +1840,13 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
       const float s = pp.sc * a[0];
       if (ra.grad_out) ra.grad_out[i] = s;
       if (ra.do_adam) {
-        const float tstep = (float)(ra.tstate[0] + 1);
-        const float bc1 = 1.f - powf(b1, tstep);
-        const float bc2 = 1.f - powf(b2, tstep);
-        const float m = b1 * ra.adam_m[i] + (1.f - b1) * s;
-        const float v = b2 * ra.adam_v[i] + (1.f - b2) * s * s;
+        const float m = b1 * m0 + (1.f - b1) * s;
+        const float v = b2 * v0 + (1.f - b2) * s * s;
         ra.adam_m[i] = m;
         ra.adam_v[i] = v;
         const float mh = m / bc1;
         const float vh = v / bc2;
-        const float th = ra.params[i] - nd.lr * mh / (sqrtf(vh) + eps);
+        const float th = th0 - nd.lr * mh / (sqrtf(vh) + eps);
         ra.params[i] = th;
         put_param(ra.kparams + nd.koff, pp, th);
       }
@@ -1875,16 +1882,19 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
 
 __global__ void k_reset_counter(int* c) { *c = 0; }
 
-// Rewrite the kernel-layout copy of networks [n_begin, n_end) from their
-// canonical parameters (after the caller sets them).
-__global__ __launch_bounds__(256) void k_pack(const float* params, float* kparams, const NetDesc* nets,
+// Take the canonical parameters of networks [n_begin, n_end) from src (the
+// caller's, or params itself) and write their kernel-layout copy: one launch
+// per subdomain where a copy and a launch were two.
+__global__ __launch_bounds__(256) void k_pack(const float* src, float* params, float* kparams, const NetDesc* nets,
                                               const int64_t* net_poff, int n_begin, int n_end) {
   const int64_t p0 = net_poff[n_begin], p1 = net_poff[n_end];
   for (int64_t i = p0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p1;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int q = find_net(net_poff, n_begin, i);
     const NetDesc nd = nets[q];
-    put_param(kparams + nd.koff, param_map(nd, (int)(i - net_poff[q])), params[i]);
+    const float v = src[i - p0];
+    params[i] = v;
+    put_param(kparams + nd.koff, param_map(nd, (int)(i - net_poff[q])), v);
   }
 }
 
@@ -2204,11 +2214,11 @@ hipError_t launch_reduce(const RArgs& ra, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_pack(const float* params, float* kparams, const NetDesc* nets, const int64_t* net_poff,
+hipError_t launch_pack(const float* src, float* params, float* kparams, const NetDesc* nets, const int64_t* net_poff,
                        int n_begin, int n_end, int64_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int grid = (int)std::min<int64_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pack, dim3(grid), dim3(256), 0, st, params, kparams, nets, net_poff, n_begin, n_end);
+  hipLaunchKernelGGL(k_pack, dim3(grid), dim3(256), 0, st, src, params, kparams, nets, net_poff, n_begin, n_end);
   return hipGetLastError();
 }
 

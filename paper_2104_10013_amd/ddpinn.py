@@ -195,6 +195,7 @@ class Problem:
             self.stream = stream
             _check(L.ddp_finalize(self._h, ctypes.c_void_p(stream.cuda_stream), 1 if fused else 0))
             self.set_params([s.params for s in prob.subdomains])
+            self._sd_of = None
             self._loss = torch.zeros(self.n_sd, 5, dtype=torch.float32, device=self.device)
         except Exception:
             L.ddp_destroy(self._h)
@@ -215,7 +216,7 @@ class Problem:
     def set_params_flat(self, flat):
         t = flat.detach().to(torch.float32).contiguous()
         for q in range(self.n_sd):
-            _check(_lib.ddp_set_params(self._h, q, ctypes.c_void_p(t[self.offsets[q]:].data_ptr()), 1))
+            _check(_lib.ddp_set_params(self._h, q, t.data_ptr() + 4 * int(self.offsets[q]), 1))
 
     def get_params(self):
         out = []
@@ -224,6 +225,12 @@ class Problem:
             _check(_lib.ddp_get_params(self._h, q, _ptr(a), 0))
             out.append(a)
         return out
+
+    def subdomain_of_param(self):
+        """The subdomain of every flat parameter (device tensor)."""
+        if self._sd_of is None:
+            self._sd_of = torch.as_tensor(np.repeat(np.arange(self.n_sd), self.n_params), device=self.device)
+        return self._sd_of
 
     def split(self, flat):
         return [flat[self.offsets[q]:self.offsets[q + 1]] for q in range(self.n_sd)]
@@ -325,6 +332,4 @@ class DDPLoss(torch.autograd.Function):
     def backward(ctx, gJ):
         g, = ctx.saved_tensors
         pb = ctx.problem
-        counts = torch.as_tensor(pb.n_params, device=g.device)
-        scale = torch.repeat_interleave(gJ.to(g.dtype), counts)
-        return g * scale, None
+        return g * gJ.to(g.dtype).index_select(0, pb.subdomain_of_param()), None

@@ -828,3 +828,45 @@ def test_eval_owners_in_any_order(n):
         got = pb.eval(xy, owner).cpu().numpy()
         np.testing.assert_allclose(got, _eval_by_slots(prob, params, xy, owner), rtol=1e-5, atol=1e-6)
         pb.close()
+
+
+@pytest.mark.parametrize("name,scale", [("c1_cpinn_poisson", 0.2), ("c5_xpinn_inverse_diffusion", 0.01)])
+def test_steps_in_one_call_equal_single_steps(name, scale):
+    """23 steps in one call (graphs of several steps, then single ones) leave
+    the bits of 23 calls of one step, with one train launch and with two."""
+    prob = W.make_problem(name, seed=0, scale=scale)
+    ends = []
+    for calls in ([23], [1] * 23, [9, 14]):
+        pb = ddpinn.Problem(prob, fused=True)
+        for n in calls:
+            lt = pb.step(n).clone()
+        st = pb.get_state()
+        ends.append((lt.cpu().numpy(), np.concatenate(st["params"]), st["m"], st["v"], st["t"]))
+        pb.close()
+    for other in ends[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(ends[0], other))
+
+
+@pytest.mark.parametrize("name,scale", [("c2_xpinn_poisson", 0.05), ("c5_xpinn_inverse_diffusion", 0.01)])
+def test_gradients_captured_by_the_caller(name, scale):
+    """loss_and_grad inside a caller's graph, with one train launch and with
+    two side by side: every replay gives the eager bits, with eager calls in
+    between."""
+    prob = W.make_problem(name, seed=0, scale=scale)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        pb = ddpinn.Problem(prob, fused=True, stream=stream)
+        lt, g = (x.clone() for x in pb.loss_and_grad())
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            clt, cg = pb.loss_and_grad()
+        for _ in range(3):
+            clt.zero_(), cg.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(clt, lt) and torch.equal(cg, g)
+            elt, eg = pb.loss_and_grad()
+            assert torch.equal(elt, lt) and torch.equal(eg, g)
+    torch.cuda.synchronize()
+    pb.close()
