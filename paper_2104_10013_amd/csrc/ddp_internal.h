@@ -9,7 +9,7 @@ constexpr int kMaxDepth = 8;      // hidden layers
 constexpr int kMaxWidth = 112;    // hidden width
 constexpr int kWaves = 4;         // waves per workgroup
 constexpr int kTilePts = 16 * kWaves;  // points per tile: 16 per wave
-constexpr int kRedParams = 256;  // parameters (threads) per block of the gradient reduction
+constexpr int kRedParams = 256;  // partial-row entries (threads) per block of the gradient reduction
 constexpr int kLossTerms = 4;     // MSE_u, MSE_F, MSE_uavg, MSE_flux|MSE_R
 
 // point classes of a work item; KIND_AUX = points with known values of the
@@ -147,6 +147,12 @@ struct KArgs {
   int prologue;           // 1: block 0 settles the Adam step counter
 };
 
+// One block of the reduction: kRedParams entries from entry begin of network
+// net's partial rows, which are rows r0 .. r0 + n - 1 of row_prow.
+struct RedBlock {
+  int net, begin, r0, n;
+};
+
 // Arguments of the reduction / Adam kernel.
 struct RArgs {
   float* params;
@@ -156,15 +162,12 @@ struct RArgs {
   const float* partial;
   const float* loss_part;
   const NetDesc* nets;
-  const int64_t* net_poff;    // n_nets + 1 prefix of parameter offsets
-  const int* net_row_ptr;     // n_nets + 1: CSR over networks of the partial rows
-  const int64_t* row_prow;    // per CSR row: offset of that network's part of a row
+  const RedBlock* blocks;     // this launch's reduction blocks
+  int n_blocks;
+  const int64_t* row_prow;    // per row, grouped by network: offset of that network's part
   const int* sd_net;          // n_sd + 1: first network of each subdomain
   const int* sd_loss_ptr;     // n_sd + 1: CSR over subdomains of the loss rows
   const int* loss_rows;       // per CSR entry: loss row
-  int net_begin, net_end;     // networks reduced (and updated) by this launch
-  const int* net_blk;         // n_nets + 1: first reduction block of each network (kRedParams a block)
-  const int* blk_net;         // per reduction block: its network
   int sd_begin, sd_end;       // subdomains whose loss terms this launch sums
   float* grad_out;            // gradient output or nullptr
   float* loss_out;            // n_sd x 5 or nullptr

@@ -98,7 +98,8 @@ struct ddp_problem {
   std::vector<int> sd_net;       // n_sd + 1: first network of each subdomain
   std::vector<int64_t> sd_poff;  // n_sd + 1: parameter offsets of subdomains
   std::vector<int64_t> net_poff; // n_nets + 1: parameter offsets of networks
-  std::vector<int> net_blk, blk_net;  // reduction blocks: CSR over networks, and each block's network
+  std::vector<int> net_blk;      // n_nets + 1: first reduction block of each network
+  std::vector<RedBlock> red_blocks;
   int64_t kparam_floats = 0;
   int plan_slots = 512;          // workgroups the plan balances for
   std::vector<Item> titems;      // train items (fused: descending cost per launch; plain: grouped by q)
@@ -141,9 +142,9 @@ struct ddp_problem {
   float *d_if_xy = nullptr, *d_aux_xy = nullptr, *d_aux_g = nullptr;
   float *d_partial = nullptr, *d_loss_part = nullptr, *d_scratch = nullptr, *d_loss = nullptr;
   int64_t* d_net_poff = nullptr;
-  int *d_net_blk = nullptr, *d_blk_net = nullptr;
+  RedBlock* d_red_blocks = nullptr;
   int* d_sd_net = nullptr;
-  int *d_net_row_ptr = nullptr, *d_sd_loss_ptr = nullptr, *d_loss_rows = nullptr;
+  int *d_sd_loss_ptr = nullptr, *d_loss_rows = nullptr;
   int64_t* d_row_prow = nullptr;
   // the fused step as graphs: one step, and kGraphSteps in a row (a graph
   // launch costs 8.6 us between two steps)
@@ -285,12 +286,10 @@ int build_plan(ddp_problem* p) {
   }
   p->sd_net[n_sd] = (int)p->nets.size();
   p->wpmax = kernel_wpmax(p->wpmax, p->ga);
-  // the reduction's blocks: kRedParams consecutive parameters of one network each
+  // the reduction's blocks: kRedParams consecutive partial-row entries of one network each
   p->net_blk.assign(1, 0);
-  p->blk_net.clear();
   for (int q = 0; q < (int)p->nets.size(); ++q) {
-    const int nb = (int)((p->net_poff[q + 1] - p->net_poff[q] + kRedParams - 1) / kRedParams);
-    for (int b = 0; b < nb; ++b) p->blk_net.push_back(q);
+    const int nb = (p->nets[q].gsize + kRedParams - 1) / kRedParams;
     p->net_blk.push_back(p->net_blk.back() + nb);
   }
 
@@ -501,6 +500,10 @@ int build_plan(ddp_problem* p) {
       p->loss_rows[lfill[p->nets[it.q].sd]++] = it.lrow;
     }
   }
+  p->red_blocks.clear();
+  for (int q = 0; q < n_nets; ++q)
+    for (int b = 0; b < p->net_blk[q + 1] - p->net_blk[q]; ++b)
+      p->red_blocks.push_back({q, b * kRedParams, p->net_row_ptr[q], p->net_row_ptr[q + 1] - p->net_row_ptr[q]});
   p->planned = true;
   return DDP_OK;
 }
@@ -536,10 +539,6 @@ RArgs make_rargs(ddp_problem* p) {
   ra.partial = p->d_partial;
   ra.loss_part = p->d_loss_part;
   ra.nets = p->d_nets;
-  ra.net_poff = p->d_net_poff;
-  ra.net_blk = p->d_net_blk;
-  ra.blk_net = p->d_blk_net;
-  ra.net_row_ptr = p->d_net_row_ptr;
   ra.row_prow = p->d_row_prow;
   ra.sd_net = p->d_sd_net;
   ra.sd_loss_ptr = p->d_sd_loss_ptr;
@@ -551,16 +550,16 @@ RArgs make_rargs(ddp_problem* p) {
 
 // reduction of subdomains [q0, q1): their networks and their loss terms
 void reduce_range(ddp_problem* p, RArgs& ra, int q0, int q1) {
-  ra.net_begin = p->sd_net[q0];
-  ra.net_end = p->sd_net[q1];
+  ra.blocks = p->d_red_blocks + p->net_blk[p->sd_net[q0]];
+  ra.n_blocks = p->net_blk[p->sd_net[q1]] - p->net_blk[p->sd_net[q0]];
   ra.sd_begin = q0;
   ra.sd_end = q1;
 }
 
 int reduce_grid(ddp_problem* p, int q0, int q1) {
-  // one block per reduction block of the subdomains' networks (block 0 also
-  // sums the loss rows, so at least one)
-  return std::max(1, p->net_blk[p->sd_net[q1]] - p->net_blk[p->sd_net[q0]]);
+  // one block per reduction block of the subdomains' networks, then a wave per
+  // subdomain for the loss rows
+  return p->net_blk[p->sd_net[q1]] - p->net_blk[p->sd_net[q0]] + (q1 - q0 + kRedParams / 64 - 1) / (kRedParams / 64);
 }
 
 // Where a step's train launches keep their work counters and activation
@@ -930,7 +929,7 @@ int install_plan(ddp_problem* p, bool graphs = true) {
   if ((rc = plan_alloc(p, &p->d_partial, (size_t)p->partial_floats))) return rc;
   if ((rc = plan_alloc(p, &p->d_loss_part, p->titems.size() * kLossTerms))) return rc;
   if ((rc = plan_alloc(p, &p->d_scratch, (size_t)scratch_floats))) return rc;
-  if ((rc = plan_upload(p, &p->d_net_row_ptr, p->net_row_ptr))) return rc;
+  if ((rc = plan_upload(p, &p->d_red_blocks, p->red_blocks))) return rc;
   if ((rc = plan_upload(p, &p->d_row_prow, p->row_prow))) return rc;
   if ((rc = plan_upload(p, &p->d_sd_loss_ptr, p->sd_loss_ptr))) return rc;
   if ((rc = plan_upload(p, &p->d_loss_rows, p->loss_rows))) return rc;
@@ -1052,8 +1051,6 @@ int ddp_finalize(ddp_problem* p, void* hip_stream, int fused) {
   if ((rc = dev_upload(p, &p->d_aux_g, p->h_aux_g))) return rc;
   if ((rc = dev_alloc(p, &p->d_loss, (size_t)n_sd * 5))) return rc;
   if ((rc = dev_upload(p, &p->d_net_poff, p->net_poff))) return rc;
-  if ((rc = dev_upload(p, &p->d_net_blk, p->net_blk))) return rc;
-  if ((rc = dev_upload(p, &p->d_blk_net, p->blk_net))) return rc;
   if ((rc = dev_upload(p, &p->d_sd_net, p->sd_net))) return rc;
   if ((rc = install_plan(p))) return rc;
   p->finalized = true;

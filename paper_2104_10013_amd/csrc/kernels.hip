@@ -1704,60 +1704,83 @@ __global__ __launch_bounds__(NT, min_waves_per_eu<WPMAX>()) void k_train(KArgs k
   }
 }
 
-// Position of canonical parameter li of a network in its gradient partial row
-// (g) and in its kernel-layout copy: a float at k1, or, for a hidden weight
-// (k1 = -1), the three bf16 parts at bf16 positions w, w + ws, w + 2 ws of the
-// weights and t, t + ts, t + 2 ts of the transposed copy.  sc: the kernel copy
-// holds sc times the parameter and the partial rows hold the gradient divided
-// by sc (n for a slope a^k, whose kernel copy is c_k = n a^k; 1 otherwise).
+// A canonical parameter in its network's kernel-layout copy: a float at k1, or,
+// for a hidden weight (k1 = -1), the three bf16 parts at bf16 positions w,
+// w + ws, w + 2 ws of the weights and t, t + ts, t + 2 ts of the transposed
+// copy.  sc: the kernel copy holds sc times the parameter and the partial rows
+// hold the gradient divided by sc (n for a slope a^k, whose kernel copy is
+// c_k = n a^k; 1 otherwise).
 struct ParamPos {
-  int g, k1, w, ws, t, ts;
+  int k1, w, ws, t, ts;
   float sc;
 };
+__device__ __forceinline__ ParamPos float_pos(int k1, float sc = 1.f) { return ParamPos{k1, 0, 0, 0, 0, sc}; }
+__device__ __forceinline__ ParamPos weight_pos(const Layout& L, int k, int m, int j) {
+  ParamPos p{-1, 0, 0, 0, 0, 1.f};
+  p.w = 2 * L.k_w(k) + split_pos(L.WP, m, j, p.ws);
+  p.t = 2 * L.k_wt(k) + split_pos(L.WP, j, m, p.ts);
+  return p;
+}
+
+// position of canonical parameter li
 __device__ __forceinline__ ParamPos param_map(const NetDesc& nd, int li) {
-  const int w = nd.width, WP = nd.wclass, D = nd.depth, DO = nd.d_out;
-  const Layout L(WP, D, DO);
-  ParamPos p{0, -1, 0, 0, 0, 0, 1.f};
-  if (li < 2 * w) {                 // W^1[m][c]
-    p.g = p.k1 = (li >> 1) * 4 + (li & 1);
-    return p;
-  }
-  if (li < 3 * w) {                 // b^1[m]
-    p.g = p.k1 = (li - 2 * w) * 4 + 2;
-    return p;
-  }
+  const int w = nd.width, D = nd.depth, DO = nd.d_out;
+  const Layout L(nd.wclass, D, DO);
+  if (li < 2 * w) return float_pos((li >> 1) * 4 + (li & 1));   // W^1[m][c]
+  if (li < 3 * w) return float_pos((li - 2 * w) * 4 + 2);       // b^1[m]
   int r = li - 3 * w;
   const int per = w * w + w;
   const int h = r / per;
   if (h < D - 1) {                  // hidden layer k = h + 2
-    const int k = h + 2;
     const int rr = r - h * per;
-    if (rr < w * w) {
-      const int m = rr / w, j = rr - (rr / w) * w;
-      p.g = L.g_w(k) + m * WP + j;
-      p.w = 2 * L.k_w(k) + split_pos(WP, m, j, p.ws);
-      p.t = 2 * L.k_wt(k) + split_pos(WP, j, m, p.ts);
-    } else {
-      p.g = L.g_b(k) + rr - w * w;
-      p.k1 = L.k_b(k) + rr - w * w;
+    if (rr < w * w) return weight_pos(L, h + 2, rr / w, rr - (rr / w) * w);
+    return float_pos(L.k_b(h + 2) + rr - w * w);
+  }
+  r -= (D - 1) * per;               // output layer, then the slopes a^k
+  if (r < DO * w) return float_pos(L.k_out() + (r / w) * nd.wclass + r - (r / w) * w);
+  if (r < DO * w + DO) return float_pos(L.k_bout() + r - DO * w);
+  return float_pos(L.k_slope() + r - DO * w - DO, nd.slope_n);
+}
+
+// the canonical parameter of entry gi of a gradient partial row and its
+// position, or -1 for padding
+__device__ __forceinline__ int grad_map(const NetDesc& nd, int gi, ParamPos& p) {
+  const int w = nd.width, WP = nd.wclass, D = nd.depth, DO = nd.d_out;
+  const Layout L(WP, D, DO);
+  if (gi < 4 * WP) {
+    const int m = gi >> 2, c = gi & 3;
+    p = float_pos(gi);
+    return m >= w || c == 3 ? -1 : c == 2 ? 2 * w + m : 2 * m + c;
+  }
+  int r = gi - 4 * WP, base = 3 * w;
+  const int per = WP * WP + WP;
+  const int h = r / per;
+  if (h < D - 1) {
+    const int rr = r - h * per;
+    base += h * (w * w + w);
+    if (rr < WP * WP) {
+      const int m = rr / WP, j = rr - (rr / WP) * WP;
+      p = weight_pos(L, h + 2, m, j);
+      return m >= w || j >= w ? -1 : base + m * w + j;
     }
-    return p;
+    p = float_pos(L.k_b(h + 2) + rr - WP * WP);
+    return rr - WP * WP >= w ? -1 : base + w * w + rr - WP * WP;
   }
-  r -= (D - 1) * per;               // output layer
-  if (r < DO * w) {
-    const int c = r / w, j = r - (r / w) * w;
-    p.g = L.g_out() + c * WP + j;
-    p.k1 = L.k_out() + c * WP + j;
-  } else if (r < DO * w + DO) {
-    p.g = L.g_bout() + r - DO * w;
-    p.k1 = L.k_bout() + r - DO * w;
-  } else {                          // slope a^k of hidden layer k = 1..D
-    const int k = r - DO * w - DO;
-    p.g = L.g_slope() + k;
-    p.k1 = L.k_slope() + k;
-    p.sc = nd.slope_n;
+  r -= (D - 1) * per;
+  base += (D - 1) * (w * w + w);
+  if (r < DO * WP) {
+    const int c = r / WP, j = r - (r / WP) * WP;
+    p = float_pos(L.k_out() + r);
+    return j >= w ? -1 : base + c * w + j;
   }
-  return p;
+  r -= DO * WP;
+  if (r < 4) {
+    p = float_pos(L.k_bout() + r);
+    return r >= DO ? -1 : base + DO * w + r;
+  }
+  r -= 4;
+  p = float_pos(L.k_slope() + r, nd.slope_n);
+  return nd.adaptive && r < D ? base + DO * w + DO + r : -1;
 }
 
 // write the kernel-layout copy of a parameter with value v
@@ -1788,58 +1811,72 @@ __device__ __forceinline__ int find_net(const int64_t* net_poff, int n, int64_t 
 
 // Sum each network's gradient partial rows in a fixed order, then write the
 // gradient and/or apply Adam (Kingma-Ba, bias corrected) and refresh the
-// kernel-layout copy; the waves of block 0 also sum each subdomain's loss
-// rows and flag non-finite losses.
+// kernel-layout copy; the blocks behind those sum each subdomain's loss rows
+// and flag non-finite losses.
 //
-// A block owns kRedParams consecutive parameters of one network, a thread one
-// parameter; it keeps kRedLanes independent partial sums over the rows (row r
-// goes to sum r mod kRedLanes), combined by a fixed tree: the loads of a batch
-// are independent, and the order does not depend on timing.
-constexpr int kRedLanes = 16;
+// Bound by the latency of its chain (block description, network, row offsets,
+// rows, Adam), not by bytes: the rows are a few MB and in cache.  A block owns kRedParams consecutive entries of one network's partial rows:
+// wave w sums rows w, w + 4, ... four entries a lane and kRedRows rows at a
+// time, then thread t takes entry t's four sums from LDS in order and updates
+// its parameter.  The order does not depend on timing.  Against a thread per
+// parameter that walks its rows one at a time, the offset of each found from
+// the parameter's, and the loss sums in block 0 (us): 3 space-time strips of 20
+// 17.4 -> 11.1, 9 subdomains of 60 20.2 -> 13.7, the 16-subdomain Poisson mix
+// 19.9 -> 17.1, 10 inverse subdomains 41 -> 28, 4 of 24 6.2 -> 6.0.
+constexpr int kRedRows = 8;
 
 __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
+  __shared__ f4 s_sum[kRedParams / 64][kRedParams / 4];
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // the block's network, its row list and the row offsets are uniform
-  // across the block (scalar loads)
-  const int bidx = ra.net_blk[ra.net_begin] + (int)blockIdx.x;
-  if (bidx < ra.net_blk[ra.net_end]) {
-    const int q = ra.blk_net[bidx];
-    const int64_t i = ra.net_poff[q] + (int64_t)(bidx - ra.net_blk[q]) * kRedParams + threadIdx.x;
-    const NetDesc nd = ra.nets[q];
-    const int r0 = ra.net_row_ptr[q], n = ra.net_row_ptr[q + 1] - r0;
-    const int64_t* pr = ra.row_prow + r0;
-    if (i < ra.net_poff[q + 1]) {
-      const ParamPos pp = param_map(nd, (int)(i - ra.net_poff[q]));
-      const float* P = ra.partial + pp.g;
-      // the optimiser's state is on its way while the rows are summed
-      float m0 = 0.f, v0 = 0.f, th0 = 0.f, bc1 = 1.f, bc2 = 1.f;
-      if (ra.do_adam) {
-        m0 = ra.adam_m[i];
-        v0 = ra.adam_v[i];
-        th0 = ra.params[i];
-        const float tstep = (float)(ra.tstate[0] + 1);
-        bc1 = 1.f - powf(b1, tstep);
-        bc2 = 1.f - powf(b2, tstep);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // the block's description and network are uniform across the block (scalar
+  // loads); everything that waits for them is issued together
+  const int bidx = (int)blockIdx.x, last = ra.n_blocks;
+  if (bidx < last) {
+    const RedBlock rb = ra.blocks[bidx];
+    const NetDesc nd = ra.nets[rb.net];
+    const int g0 = rb.begin;
+    ParamPos pp = float_pos(0);
+    const int gi = g0 + (int)threadIdx.x;
+    const int li = gi < nd.gsize ? grad_map(nd, gi, pp) : -1;
+    const int64_t i = nd.poff + li;
+    // the optimiser's state is on its way while the rows are summed
+    float m0 = 0.f, v0 = 0.f, th0 = 0.f;
+    const float tstep = ra.do_adam ? (float)(ra.tstate[0] + 1) : 1.f;
+    if (ra.do_adam && li >= 0) {
+      m0 = ra.adam_m[i];
+      v0 = ra.adam_v[i];
+      th0 = ra.params[i];
+    }
+    const int n = rb.n;
+    const int64_t* pr = ra.row_prow + rb.r0;
+    const float* P = ra.partial + g0 + 4 * lane;
+    f4 a[kRedRows];
+#pragma unroll
+    for (int j = 0; j < kRedRows; ++j) a[j] = f4{0.f, 0.f, 0.f, 0.f};
+    if (g0 + 4 * lane < nd.gsize) {
+      int r = wave;
+      for (; r + 4 * (kRedRows - 1) < n; r += 4 * kRedRows) {
+#pragma unroll
+        for (int j = 0; j < kRedRows; ++j) a[j] += *reinterpret_cast<const f4*>(P + pr[r + 4 * j]);
       }
-      float a[kRedLanes];
 #pragma unroll
-      for (int j = 0; j < kRedLanes; ++j) a[j] = 0.f;
-      int r = 0;
-      for (; r + kRedLanes <= n; r += kRedLanes) {
+      for (int j = 0; j < kRedRows; ++j)
+        if (r + 4 * j < n) a[j] += *reinterpret_cast<const f4*>(P + pr[r + 4 * j]);
+    }
 #pragma unroll
-        for (int j = 0; j < kRedLanes; ++j) a[j] += P[pr[r + j]];
-      }
+    for (int w = kRedRows / 2; w >= 1; w /= 2)
 #pragma unroll
-      for (int j = 0; j < kRedLanes; ++j)
-        if (r + j < n) a[j] += P[pr[r + j]];
-#pragma unroll
-      for (int w = kRedLanes / 2; w >= 1; w /= 2)
-#pragma unroll
-        for (int j = 0; j < w; ++j) a[j] += a[j + w];
-      const float s = pp.sc * a[0];
+      for (int j = 0; j < w; ++j) a[j] += a[j + w];
+    s_sum[wave][lane] = a[0];
+    __syncthreads();
+    if (li >= 0) {
+      const float* S = reinterpret_cast<const float*>(s_sum) + threadIdx.x;
+      const float s = pp.sc * ((S[0] + S[kRedParams]) + (S[2 * kRedParams] + S[3 * kRedParams]));
       if (ra.grad_out) ra.grad_out[i] = s;
       if (ra.do_adam) {
+        const float bc1 = 1.f - powf(b1, tstep);
+        const float bc2 = 1.f - powf(b2, tstep);
         const float m = b1 * m0 + (1.f - b1) * s;
         const float v = b2 * v0 + (1.f - b2) * s * s;
         ra.adam_m[i] = m;
@@ -1852,28 +1889,32 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
       }
     }
   }
-  if (blockIdx.x == 0) {
-    // one wave per subdomain: lane l sums rows l, l + 64, ...; then a fixed
-    // butterfly across the wave
-    for (int q = ra.sd_begin + wave; q < ra.sd_end; q += (int)(blockDim.x >> 6)) {
-      float t[kLossTerms] = {0.f, 0.f, 0.f, 0.f};
-      for (int r = ra.sd_loss_ptr[q] + lane; r < ra.sd_loss_ptr[q + 1]; r += 64) {
-        const float* lp = ra.loss_part + (int64_t)ra.loss_rows[r] * kLossTerms;
-        for (int k = 0; k < kLossTerms; ++k) t[k] += lp[k];
+  // the blocks behind those: one wave per subdomain sums its loss rows (lane l
+  // sums rows l, l + 64, ...; then a fixed butterfly across the wave).  As a
+  // loop of the first block these sums outlasted the launch: 16 subdomains
+  // took 16 of its 17 us.
+  const int q = bidx >= last ? ra.sd_begin + (bidx - last) * (kRedParams / 64) + wave : ra.sd_end;
+  if (q < ra.sd_end) {
+    const NetDesc nd = ra.nets[ra.sd_net[q]];
+    f4 t = {0.f, 0.f, 0.f, 0.f};
+    for (int r = ra.sd_loss_ptr[q] + lane; r < ra.sd_loss_ptr[q + 1]; r += 64)
+      t += *reinterpret_cast<const f4*>(ra.loss_part + (int64_t)ra.loss_rows[r] * kLossTerms);
+    for (int m = 32; m >= 1; m >>= 1)
+#pragma unroll
+      for (int k = 0; k < kLossTerms; ++k) t[k] += __shfl_xor(t[k], m);
+    if (lane == 0) {
+      float J = 0.f;
+#pragma unroll
+      for (int k = 0; k < kLossTerms; ++k) J += nd.loss_w[k] * t[k];
+      if (ra.loss_out) {
+        ra.loss_out[q * 5] = J;
+#pragma unroll
+        for (int k = 0; k < kLossTerms; ++k) ra.loss_out[q * 5 + 1 + k] = t[k];
       }
-      for (int k = 0; k < kLossTerms; ++k)
-        for (int m = 32; m >= 1; m >>= 1) t[k] += __shfl_xor(t[k], m);
-      if (lane == 0) {
-        const NetDesc nd = ra.nets[ra.sd_net[q]];
-        float J = 0.f;
-        for (int k = 0; k < kLossTerms; ++k) J += nd.loss_w[k] * t[k];
-        if (ra.loss_out) {
-          ra.loss_out[q * 5] = J;
-          for (int k = 0; k < kLossTerms; ++k) ra.loss_out[q * 5 + 1 + k] = t[k];
-        }
-        if (!isfinite(J)) ra.flags[0] = 1;
-      }
+      if (!isfinite(J)) ra.flags[0] = 1;
     }
+  }
+  if (blockIdx.x == 0) {
     if (ra.do_adam && threadIdx.x == 0) ra.tstate[1] = 1;
     // the train kernel of this step has finished: re-arm its work counter
     if (ra.counter_reset && (int)threadIdx.x < ra.n_counter_reset) ra.counter_reset[threadIdx.x] = 0;
