@@ -884,6 +884,43 @@ int ddp_plan(ddp_problem* p) {
 
 namespace {
 
+// A stream for the launches beside those on p->stream.  Streams share the
+// device's few hardware queues (4 a process), and which one a stream gets
+// depends on the streams made before it; two on one queue run their kernels
+// one after the other.  So up to kSideTries streams are tried until a kernel on
+// one is seen to run beside a kernel on p->stream (w: two device ints).  Fixed
+// by chance instead: 5 ragged boxes of 20 to 100 took 121 us side by side, or 173
+// on one queue, by the number of streams in the process.
+constexpr int kSideTries = 4;
+
+int make_side_stream(ddp_problem* p, int* w) {
+  std::vector<hipStream_t> tried;
+  hipError_t e = hipSuccess;
+  int seen = 0;
+  while (!seen && (int)tried.size() < kSideTries && e == hipSuccess) {
+    hipStream_t s = nullptr;
+    if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess) break;
+    tried.push_back(s);
+    // the new stream's first launch, out of the way of the meeting
+    e = launch_reset_counter(w, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = launch_await(w, p->stream);
+    if (e == hipSuccess) e = launch_arrive(w, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+    if (e == hipSuccess) e = hipMemcpy(&seen, w + 1, sizeof(int), hipMemcpyDeviceToHost);
+  }
+  for (int i = 0; i < 2 && e == hipSuccess; ++i) e = launch_reset_counter(w + i, p->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+  // none seen: any will do
+  const size_t keep = e != hipSuccess ? tried.size() : tried.size() - 1;
+  for (size_t i = 0; i < tried.size(); ++i)
+    if (i != keep) hipStreamDestroy(tried[i]);
+  HIP_TRY(e);
+  p->side_stream = tried[keep];
+  return DDP_OK;
+}
+
 // Build the work plan for the current options and (re)create everything that
 // depends on it: work items, gradient / loss partial rows, row lists, the
 // activation stash, work counters and (graphs) the step graphs.
@@ -917,7 +954,6 @@ int install_plan(ddp_problem* p, bool graphs = true) {
   }
   if (side) {
     scratch_floats = std::max(scratch_floats, side_floats);
-    if (!p->side_stream) HIP_TRY(hipStreamCreateWithFlags(&p->side_stream, hipStreamNonBlocking));
     if (!p->ev_fork) HIP_TRY(hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming));
     if (!p->ev_join) HIP_TRY(hipEventCreateWithFlags(&p->ev_join, hipEventDisableTiming));
   }
@@ -925,6 +961,8 @@ int install_plan(ddp_problem* p, bool graphs = true) {
   p->n_counters = (int)p->launches.size() + n_sd;
   int rc = 0;
   if ((rc = plan_upload(p, &p->d_counters, std::vector<int>(p->n_counters, 0)))) return rc;
+  // (a plan with two launches has more counters than the two the meeting uses)
+  if (side && !p->side_stream && (rc = make_side_stream(p, p->d_counters))) return rc;
   if ((rc = plan_upload(p, &p->d_titems, p->titems))) return rc;
   if ((rc = plan_alloc(p, &p->d_partial, (size_t)p->partial_floats))) return rc;
   if ((rc = plan_alloc(p, &p->d_loss_part, p->titems.size() * kLossTerms))) return rc;

@@ -19,6 +19,10 @@ hipError_t train_occupancy(int pde, int wpmax, bool ga, int* blocks_per_cu);
 hipError_t launch_train(int pde, int wpmax, bool ga, const KArgs& ka, int grid, hipStream_t st);
 // set a work counter to zero
 hipError_t launch_reset_counter(int* c, hipStream_t st);
+// a bounded wait on one stream for a mark set on another (w: two ints, w[0] 0;
+// w[1] tells whether it was seen)
+hipError_t launch_await(int* w, hipStream_t st);
+hipError_t launch_arrive(int* w, hipStream_t st);
 // gradient reduction, loss reduction and optional Adam; re-arms ra.counter_reset
 hipError_t launch_reduce(const RArgs& ra, int grid, hipStream_t st);
 // take the canonical parameters of networks [n_begin, n_end) from src (device;

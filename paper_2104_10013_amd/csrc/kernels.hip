@@ -1923,6 +1923,21 @@ __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
 
 __global__ void k_reset_counter(int* c) { *c = 0; }
 
+// Two streams meet: k_await polls w[0] for at most kAwaitPolls loads and
+// leaves in w[1] what it saw; k_arrive sets w[0].  With k_arrive launched
+// behind k_await on another stream, k_await sees it only if the two kernels
+// can run at the same time; both end either way.
+constexpr int kAwaitPolls = 512;   // about 0.3 ms
+
+__global__ void k_await(int* w) {
+  int seen = 0;
+  for (int i = 0; i < kAwaitPolls && !seen; ++i)
+    seen = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  w[1] = seen;
+}
+
+__global__ void k_arrive(int* w) { __hip_atomic_store(w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // Take the canonical parameters of networks [n_begin, n_end) from src (the
 // caller's, or params itself) and write their kernel-layout copy: one launch
 // per subdomain where a copy and a launch were two.
@@ -2247,6 +2262,16 @@ hipError_t train_occupancy(int pde, int wpmax, bool ga, int* blocks_per_cu) {
 
 hipError_t launch_reset_counter(int* c, hipStream_t st) {
   hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, st, c);
+  return hipGetLastError();
+}
+
+hipError_t launch_await(int* w, hipStream_t st) {
+  hipLaunchKernelGGL(k_await, dim3(1), dim3(1), 0, st, w);
+  return hipGetLastError();
+}
+
+hipError_t launch_arrive(int* w, hipStream_t st) {
+  hipLaunchKernelGGL(k_arrive, dim3(1), dim3(1), 0, st, w);
   return hipGetLastError();
 }
 

@@ -677,6 +677,29 @@ def test_general_activation_kernels_match_plain_bitwise():
     pb.close()
 
 
+@pytest.mark.parametrize("others", [0, 1, 2, 3])
+def test_second_stream_beside_any_caller_stream(others):
+    """The stream of the second train launch is chosen by what runs beside the
+    caller's; whichever hardware queue the caller's stream has, after any
+    number of other streams, the bits are those of one launch after the other."""
+    prob = W.c5_xpinn_inverse_diffusion(seed=0, scale=0.05)
+    params = _params(prob, 7)
+    streams = [torch.cuda.Stream() for _ in range(others + 1)]
+    for s in streams:
+        with torch.cuda.stream(s):
+            torch.zeros(8, device="cuda").add_(1)
+    out = []
+    for conc in (0, 1):
+        _say(f"{others} other streams, concurrent {conc}")
+        with torch.cuda.stream(streams[-1]):
+            pb, lt, g = run(prob, params, concurrent=conc)
+        out.append((lt, g))
+        pb.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    for a, b in zip(out[0][1], out[1][1]):
+        assert np.array_equal(a, b)
+
+
 def test_phase_timing_of_the_fused_step():
     """Train time split by point kind on the 16-subdomain problem: residual
     items dominate, every phase is timed, and the phases add up to at least
