@@ -140,7 +140,7 @@ struct KArgs {
   float* loss_part;       // kLossTerms per loss row
   float* scratch;         // per-workgroup activation stash
   int64_t scratch_slot;   // floats per workgroup slot
-  int* counter;           // work counter of this launch (zero at launch)
+  int* counter;           // items pulled behind the grid's first ones (zero at launch)
   int* tstate;            // [0] completed Adam steps, [1] pending increment
   int n_eq;
   float coef0;
