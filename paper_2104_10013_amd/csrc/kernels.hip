@@ -614,6 +614,13 @@ struct Tile {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(X[s][mb]));
   }
+  // any values
+  __device__ __forceinline__ static void forget(Streams& X) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) asm volatile("" : "=v"(X[s][mb]));
+  }
   // all four streams: at once where the registers allow it (half the weight
   // reads), else in two pairs
   template <bool PAIRS>
@@ -637,9 +644,10 @@ struct Tile {
   }
   template <bool GA>
   __device__ static void stash_put_layer(const NetDesc& nd, __amdgpu_buffer_rsrc_t rs, int layer, int wave, int lane,
-                                         const Streams& A, const Streams& H) {
+                                         const Streams& A, const Streams& H, bool values_only = false) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) stash_put(A[0][mb], rs, lane * 16, stash_off(layer, wave, 0, mb));
+    if (values_only) return;
     const bool hf = h_form<GA>(nd);
 #pragma unroll
     for (int s = 1; s < 4; ++s)
@@ -674,10 +682,11 @@ struct Tile {
       }
   }
   // One hidden layer in place: a^k = W^k h^{k-1} (+ b^k on the value stream)
-  // for all four streams, the activation rule, and what the reverse pass keeps.
+  // for all four streams, the activation rule, and what the reverse pass keeps
+  // (values_only: of the pre-activations' value stream alone).
   template <bool STASH, bool GA>
   __device__ static void hidden_layer(const char* w, int g, Streams& H, __amdgpu_buffer_rsrc_t rs, int layer, int wave,
-                                      int lane, const NetDesc& nd, float c) {
+                                      int lane, const NetDesc& nd, float c, bool values_only = false) {
     const float* bias = reinterpret_cast<const float*>(w + WBYTES);
     Streams A;
 #pragma unroll
@@ -689,7 +698,9 @@ struct Tile {
     }
     contract4<MB == 5>(w, lane, H, A);
     activate<GA>(A, H, nd.act, c);
-    if constexpr (STASH) stash_put_layer<GA>(nd, rs, layer, wave, lane, A, H);
+    if constexpr (STASH) {
+      stash_put_layer<GA>(nd, rs, layer, wave, lane, A, H, values_only);
+    }
   }
 
   // Staging area of dW (one per wave where PRIV): [operand abar, h][part][row]
@@ -1020,6 +1031,10 @@ struct Tile {
     char* sS = sW + (stage_over_weights(WP) ? 0 : WBYTES);   // staging area of dW
     float* sRed = reinterpret_cast<float*>(sW + tile_bytes(WP, DO));   // [kWaves][kLossTerms]
     float* sSl = sRed + kWaves * kLossTerms;   // [kWaves] slope-gradient sums
+    // the reverse pass follows the forward one here, and what it needs of the
+    // last hidden layer is h^D, at hand, and a^D: of that layer, the value
+    // stream alone is stashed
+    constexpr bool HOLD = PHASE == PH_ALL && !GA;
     const int D = nd.depth;
     const Layout L(WP, D, DO);
     const float* K = ka.kparams + nd.koff;
@@ -1085,7 +1100,7 @@ struct Tile {
         dma_landed();
         __syncthreads();
         if (k < D) fetch_wb(wbuf(sW, D, k + 1), K, L, k + 1, wave, lane);
-        hidden_layer<true, GA>(wbuf(sW, D, k), g, H, rs, k, wave, lane, nd, slope(nd, K, L, k));
+        hidden_layer<true, GA>(wbuf(sW, D, k), g, H, rs, k, wave, lane, nd, slope(nd, K, L, k), HOLD && k == D);
       }
       if (PHASE == PH_BWD || D < 2) {   // else a hidden layer's barrier has published the output weights
         dma_landed();
@@ -1167,10 +1182,19 @@ struct Tile {
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      // what was kept of layer k; the last layer's is loaded while the output
-      // layer's sums run
+      // what was kept of layer k; what is not in registers (HOLD) of the last
+      // layer's is loaded while the output layer's sums run
       Streams Sk;
-      if (KEEP && D >= 2) stash_load(rs, D, wave, lane, Sk);
+      if constexpr (HOLD) {
+        if (KEEP && D >= 2) stash_load_stream(rs, D, wave, lane, 0, Sk[0]);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+          for (int s = 1; s < 4; ++s) Sk[s][mb] = H[s][mb];
+        }
+      } else if (KEEP && D >= 2) {
+        stash_load(rs, D, wave, lane, Sk);
+      }
       __syncthreads();
       // every wave is past the last forward layer: W^{D T} streams into the
       // first buffer (where the staging area of dW does not cover it)
@@ -1219,7 +1243,10 @@ struct Tile {
         // class 80 has no registers to hold it, loads h^{k-1} stream by
         // stream and the whole again at the end
         Streams Sp;
-        if constexpr (!KEEP) stash_load(rs, k, wave, lane, Sk);
+        if constexpr (!KEEP) {
+          if (HOLD && k == D) stash_load_stream(rs, k, wave, lane, 0, Sk[0]);
+          else stash_load(rs, k, wave, lane, Sk);
+        }
         // abar^k from what was kept of layer k and the incoming g^k (in place of
         // g^k); with a general activation also the layer's slope gradient
         {
@@ -1499,6 +1526,7 @@ struct Tile {
           } else {
             contract<0, 2>(sW, lane, G, Gn);
             contract<2, 2>(sW, lane, G, Gn);
+            if constexpr (HOLD) forget(Sk);   // loaded at the top, not carried there
           }
 #pragma unroll
           for (int s = 0; s < 4; ++s)
