@@ -416,7 +416,8 @@ constexpr int split_matrix_bytes(int wp) { return 6 * wp * wp; }
 // registers, one sum over the waves at the end of the layer) instead of a
 // share of the blocks over all 64 points: classes up to 48, where the blocks
 // take at most 36 registers.  No barriers between the streams, and each
-// fragment read from LDS serves a row or column of blocks.
+// fragment read from LDS serves a row or column of blocks.  (3 strips of 20:
+// 169 us a step with shared blocks, 159 with private ones.)
 constexpr bool private_dw(int wp) { return wp <= 48; }
 constexpr int stage_bytes(int wp) { return 2 * 3 * 2 * TP * (wp + 4); }
 // Whether the staging area takes the place of W^T, which is then loaded after
@@ -1033,7 +1034,9 @@ struct Tile {
     float* sSl = sRed + kWaves * kLossTerms;   // [kWaves] slope-gradient sums
     // the reverse pass follows the forward one here, and what it needs of the
     // last hidden layer is h^D, at hand, and a^D: of that layer, the value
-    // stream alone is stashed
+    // stream alone is stashed.  (Three space-time strips of 20 wide 147 -> 130
+    // us a step, 50 wide 208 -> 203; a^D in registers as well spills and takes
+    // that back.)
     constexpr bool HOLD = PHASE == PH_ALL && !GA;
     const int D = nd.depth;
     const Layout L(WP, D, DO);
@@ -1695,6 +1698,16 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
 #undef DDP_CASE
 }
 
+// What bounds it: for widths from 48 the matrix cores and the vector unit in
+// turn (per hidden layer, wave and tile of class 64: 582 MFMAs of 16.8 cycles
+// and 1960 vector instructions, a third of them splitting float32 into bf16
+// parts; two waves share a SIMD and overlap only in part), for narrow networks
+// the stash traffic (3 strips of 20 wide: about 4 of the 5 TB/s a copy
+// reaches) and latency, for a few tiles latency alone.  Train + reduce a step,
+// with float32 MFMAs and everything stashed twice -> now: 16-subdomain mix of
+// 143,157 points 716 -> 460 us, 9 subdomains of 60 wide 537 -> 332, 3 strips of
+// 20 185 -> 130, 4 of 24 38 -> 28.5.
+//
 // Persistent kernel: workgroup b starts with item b of the list (descending
 // cost), then workgroups pull items from a device counter until it is drained;
 // where every item has a workgroup the counter is not touched.  A first pull
