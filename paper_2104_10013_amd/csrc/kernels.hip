@@ -167,12 +167,25 @@ __device__ __forceinline__ void split4(f4 x, b4& h, b4& m, b4& l) {
 __device__ __forceinline__ b8 join(b4 x, b4 y) { return b8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]}; }
 
 // tanh(a) and sech^2(a) from e = exp(-2|a|):  t = sign(a)(1-e)/(1+e),
-// s1 = 4e/(1+e)^2 (no cancellation for large |a|).
+// s1 = 4e/(1+e)^2 (no cancellation for large |a|); below 0.7, where 1 - e
+// cancels, t = |a| + |a|^3 P(a^2) (as in tanh_value) and s1 = 1 - t^2.  Without
+// that branch a step is 4 to 10 % faster, but the error of one gradient against 64
+// bits is 1.3e-7 instead of 7e-8 (strips of 50) and, repeating at every step,
+// it adds up: after 20 Adam steps of the 16-subdomain mix 1.57 against 0.89 times
+// the float32-MFMA step's (geometric means of 7 seeds).
 __device__ __forceinline__ void tanh_s1(float a, float& t, float& s1) {
-  const float e = __expf(-2.f * fabsf(a));
+  const float b = fabsf(a), u = b * b;
+  const float e = __expf(-2.f * b);
   const float r = __builtin_amdgcn_rcpf(1.f + e);
-  t = copysignf((1.f - e) * r, a);
-  s1 = 4.f * e * r * r;
+  float p = -0.0051385928f;
+  p = fmaf(p, u, 0.020091895f);
+  p = fmaf(p, u, -0.053558834f);
+  p = fmaf(p, u, 0.13329111f);
+  p = fmaf(p, u, -0.33333191f);
+  const float s = fmaf(b * u, p, b);
+  const bool small = b < 0.7f;
+  t = copysignf(small ? s : (1.f - e) * r, a);
+  s1 = small ? fmaf(-s, s, 1.f) : 4.f * e * r * r;
 }
 
 template <bool S2>
