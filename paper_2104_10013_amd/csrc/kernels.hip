@@ -1718,8 +1718,8 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
 // the stash traffic (3 strips of 20 wide: about 4 of the 5 TB/s a copy
 // reaches) and latency, for a few tiles latency alone.  Train + reduce a step,
 // with float32 MFMAs and everything stashed twice -> now: 16-subdomain mix of
-// 143,157 points 716 -> 460 us, 9 subdomains of 60 wide 537 -> 332, 3 strips of
-// 20 185 -> 130, 4 of 24 38 -> 28.5.
+// 143,157 points 719 -> 499 us, 9 subdomains of 60 wide 536 -> 364, 3 strips of
+// 20 184 -> 145, 4 of 24 38.6 -> 30.5.
 //
 // Persistent kernel: workgroup b starts with item b of the list (descending
 // cost), then workgroups pull items from a device counter until it is drained;
