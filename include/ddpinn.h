@@ -192,7 +192,9 @@ int ddp_autotune(ddp_problem* p, int iters, const char* cache_path, int64_t* cho
 int ddp_param_count(const ddp_problem* p, int sd, int64_t* n);
 
 /* Copy subdomain sd's parameters in (set) or out (get), canonical layout.
- * Stream-ordered after ddp_finalize. */
+ * Stream-ordered after ddp_finalize.  With on_device = 1 flat may be any
+ * memory that a device-to-device copy takes: memory of the problem's device is
+ * read where it lies, all other (host, peer) is copied first. */
 int ddp_set_params(ddp_problem* p, int sd, const float* flat, int on_device);
 int ddp_get_params(ddp_problem* p, int sd, float* flat, int on_device);
 

@@ -1243,14 +1243,45 @@ int ddp_param_count(const ddp_problem* p, int sd, int64_t* n) {
   return DDP_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Whether the problem's kernels may read n floats at ptr: device memory of its
+// own device, all of it inside one allocation.  Host, managed and peer memory,
+// which the runtime's copies resolve, would fault a kernel or be read over the
+// bus.
+bool kernel_may_read(const ddp_problem* p, const float* ptr, size_t n) {
+  hipPointerAttribute_t at{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if ((uintptr_t)ptr % sizeof(float) != 0) return false;
+  if (hipPointerGetAttributes(&at, ptr) == hipSuccess) {
+    if (at.type != hipMemoryTypeDevice || at.device != p->device) return false;
+    if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)ptr) == hipSuccess) {
+      const size_t at_byte = (size_t)((const char*)ptr - (const char*)base);
+      return at_byte <= size && n * sizeof(float) <= size - at_byte;
+    }
+  }
+  (void)hipGetLastError();   // not the next launch's error
+  return false;
+}
+
+}  // namespace
+
+extern "C" {
+
 int ddp_set_params(ddp_problem* p, int sd, const float* flat, int on_device) {
   if (int rc = check_final(p)) return rc;
   if (sd < 0 || sd >= (int)p->sds.size() || !flat) return fail(DDP_EINVAL, "bad subdomain or null pointer");
   const size_t n = (size_t)(p->sd_poff[sd + 1] - p->sd_poff[sd]);
   float* own = p->d_params + p->sd_poff[sd];
-  if (!on_device) HIP_TRY(hipMemcpyAsync(own, flat, n * sizeof(float), hipMemcpyHostToDevice, p->stream));
-  HIP_TRY(launch_pack(on_device ? flat : own, p->d_params, p->d_kparams, p->d_nets, p->d_net_poff, p->sd_net[sd], p->sd_net[sd + 1],
-                      (int64_t)n, p->stream));
+  const bool direct = on_device && kernel_may_read(p, flat, n);
+  if (!direct)
+    HIP_TRY(hipMemcpyAsync(own, flat, n * sizeof(float), on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
+                           p->stream));
+  HIP_TRY(launch_pack(direct ? flat : own, p->d_params, p->d_kparams, p->d_nets, p->d_net_poff, p->sd_net[sd],
+                      p->sd_net[sd + 1], (int64_t)n, p->stream));
   if (!on_device) HIP_TRY(hipStreamSynchronize(p->stream));
   return DDP_OK;
 }

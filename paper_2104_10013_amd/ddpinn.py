@@ -203,10 +203,17 @@ class Problem:
             raise
 
     # -- parameters -------------------------------------------------------
+    @staticmethod
+    def _refuse_short(have, need):
+        if have < need:
+            raise DDPError(DDP_EINVAL, f"{need} parameters needed, {have} given")
+
     def set_params(self, params):
         for q, p in enumerate(params):
             if isinstance(p, torch.Tensor) and p.is_cuda:
                 t = p.detach().to(torch.float32).contiguous()
+                if 0 <= q < self.n_sd:
+                    self._refuse_short(t.numel(), self.n_params[q])
                 _check(_lib.ddp_set_params(self._h, q, _ptr(t), 1))
             else:
                 a = _host_f32(p)
@@ -214,9 +221,11 @@ class Problem:
                 _check(_lib.ddp_set_params(self._h, q, _ptr(a), 0))
 
     def set_params_flat(self, flat):
+        """All subdomains' parameters concatenated: a tensor on any device."""
         t = flat.detach().to(torch.float32).contiguous()
+        self._refuse_short(min(t.numel(), t.shape[0] + self.n_params[-1] - 1), int(self.offsets[-1]))
         for q in range(self.n_sd):
-            _check(_lib.ddp_set_params(self._h, q, t.data_ptr() + 4 * int(self.offsets[q]), 1))
+            _check(_lib.ddp_set_params(self._h, q, t.data_ptr() + 4 * int(self.offsets[q]), int(t.is_cuda)))
 
     def get_params(self):
         out = []

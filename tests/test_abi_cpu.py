@@ -242,3 +242,39 @@ def test_create_rejects_bad_combinations():
     assert L.ddp_add_subdomain(h, 1, one, w1, lw, 1e-3, None) == 0
     assert L.ddp_set_points(h, 0, 2, 1, xy.ctypes.data_as(ct.c_void_p), v.ctypes.data_as(ct.c_void_p), 0) == ddpinn.DDP_EINVAL
     assert L.ddp_destroy(h) == 0
+
+
+class _Recorder:
+    """The library, with ddp_set_params recorded instead of called."""
+
+    def __init__(self, lib):
+        self.lib, self.calls = lib, []
+
+    def __getattr__(self, name):
+        return getattr(self.lib, name)
+
+    def ddp_set_params(self, h, q, ptr, on_device):
+        self.calls.append((q, ptr, on_device))
+        return ddpinn.DDP_OK
+
+
+def test_flat_parameters_of_the_host_take_the_host_path(monkeypatch):
+    """A flat vector in host memory is handed over as host memory, subdomain by
+    subdomain, and one that is too short reaches no call at all."""
+    import torch
+    pb = ddpinn.Problem(W.make_problem("c1_cpinn_poisson", seed=0, scale=0.1), plan_only=True)
+    rec = _Recorder(ddpinn.load_library())
+    monkeypatch.setattr(ddpinn, "_lib", rec)
+    total = int(pb.offsets[-1])
+    for n in (total, total + 5):
+        rec.calls.clear()
+        t = torch.arange(n, dtype=torch.float32)
+        pb.set_params_flat(t)
+        assert rec.calls == [(q, t.data_ptr() + 4 * int(pb.offsets[q]), 0) for q in range(pb.n_sd)]
+    rec.calls.clear()
+    for bad in (torch.zeros(0), torch.zeros(1), torch.zeros(total - 1), torch.zeros(1, total)):
+        with pytest.raises(ddpinn.DDPError) as e:
+            pb.set_params_flat(bad)
+        assert e.value.code == ddpinn.DDP_EINVAL
+    assert not rec.calls
+    pb.close()

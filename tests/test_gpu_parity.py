@@ -893,3 +893,73 @@ def test_gradients_captured_by_the_caller(name, scale):
             assert torch.equal(elt, lt) and torch.equal(eg, g)
     torch.cuda.synchronize()
     pb.close()
+
+
+def test_parameters_from_any_memory():
+    """Device, pageable and pinned host parameters leave the same bits through
+    the flat and the per-subdomain call, short ones are refused, and a pointer
+    that is not the device's own, or is not a float's address, is copied (or
+    refused by the runtime) and never read by a kernel."""
+    prob = W.c1_cpinn_poisson(seed=0, scale=0.1)
+    params = _params(prob, 3)
+    flat = torch.from_numpy(np.concatenate(params))
+    total = flat.numel()
+    pb = ddpinn.Problem(prob, fused=True)
+    zeros = torch.zeros(total, device="cuda")
+
+    def now():
+        pb.sync()
+        return np.concatenate(pb.get_params())
+
+    pb.set_params([p for p in params])
+    lt, g = (x.clone() for x in pb.loss_and_grad())
+    for kind, t in (("device", flat.cuda()), ("pageable", flat), ("pinned", flat.pin_memory()),
+                    ("double", flat.double()), ("longer", torch.cat([flat, flat]).cuda())):
+        _say(f"flat parameters: {kind}")
+        pb.set_params_flat(zeros)
+        pb.set_params_flat(t)
+        assert np.array_equal(now(), flat.numpy()), kind
+        lt2, g2 = pb.loss_and_grad()
+        assert torch.equal(lt, lt2) and torch.equal(g, g2), kind
+    short = flat.cuda()[:total - 1]
+    with pytest.raises(ddpinn.DDPError):
+        pb.set_params_flat(short)
+    with pytest.raises(ddpinn.DDPError):
+        pb.set_params([torch.zeros(int(pb.n_params[0]) - 1, device="cuda")])
+    assert np.array_equal(now(), flat.numpy())
+    # the C entry with on_device = 1
+    lib = ddpinn.load_library()
+    host = np.ascontiguousarray(params[1], np.float32)
+    raw = torch.zeros(4 * len(host) + 4, dtype=torch.uint8, device="cuda")
+    raw[2:2 + 4 * len(host)] = torch.from_numpy(host.view(np.uint8)).cuda()
+    torch.cuda.synchronize()
+    for kind, ptr in (("pageable", host.ctypes.data), ("odd address", raw.data_ptr() + 2)):
+        _say(f"on_device = 1 with {kind} memory")
+        pb.set_params_flat(zeros)
+        rc = lib.ddp_set_params(pb._h, 1, ptr, 1)
+        torch.cuda.synchronize()
+        got = pb.get_params()[1]
+        assert np.array_equal(got, host if rc == ddpinn.DDP_OK else np.zeros_like(host)), (kind, rc)
+    pb.close()
+
+
+def test_parameters_captured_by_the_caller():
+    """Device parameters taken inside a caller's graph: every replay takes what
+    the buffer then holds."""
+    prob = W.c1_cpinn_poisson(seed=0, scale=0.1)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        pb = ddpinn.Problem(prob, fused=True, stream=stream)
+        buf = torch.zeros(int(pb.offsets[-1]), device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            pb.set_params_flat(buf)
+        for r in range(3):
+            want = np.concatenate(_params(prob, r))
+            buf.copy_(torch.from_numpy(want))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(np.concatenate(pb.get_params()), want)
+    torch.cuda.synchronize()
+    pb.close()
