@@ -137,6 +137,8 @@ __device__ __forceinline__ float group_sum(float v) {
 // float64 is smaller too (2-norm of 16x16 blocks: K = 32 3.6e-8 against
 // 1.05e-7, K = 96 1.2e-7 / 1.8e-7, K = 256 2.7e-7 / 3.0e-7).
 __device__ __forceinline__ f4 mma(b8 a, b8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+// (the same output layout: lane group g holds element g of the four terms)
+__device__ __forceinline__ f4 mma_f32(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // The split of two values: the remainders x - hi come from the bf16 dot
 // product x + (hi0, hi1) . (-1, 0), exact like the subtraction (checked on
@@ -618,6 +620,39 @@ struct Tile {
         for (int s = 0; s < NS; ++s) Y[S0 + s][mb] = mma(f[0], hh[s], Y[S0 + s][mb]);
         f[0] = fn[0];
         f[1] = fn[1];
+      }
+    }
+  }
+  // The same Y_s += W X_s in float32, on the 16x16x4 float32 MFMA, for values
+  // that are no sum of three bf16 (infinities, and NaN beside them): the parts
+  // of a weight are added up again, element e of a fragment being the A operand
+  // of the step that takes element e of the streams.  2.7 times the matrix
+  // cycles; taken only where contract's result turned out not finite.
+  template <int S0, int NS>
+  __device__ __forceinline__ static void contract_f32(const char* w, int lane, const Streams& X, Streams& Y) {
+    auto weight = [](__bf16 m, __bf16 h, __bf16 l) { return (float)h + ((float)m + (float)l); };
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const b8* p = reinterpret_cast<const b8*>(w + mb * 96 * WP + kb * 3072) + lane;
+        const b8 fm = p[0], fh = p[64], fl = p[128];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = weight(fm[e], fh[e], fl[e]);
+#pragma unroll
+          for (int s = S0; s < S0 + NS; ++s) Y[s][mb] = mma_f32(v, X[s][2 * kb + (e >> 2)][e & 3], Y[s][mb]);
+        }
+      }
+      if constexpr (TAIL) {
+        const b4* p = reinterpret_cast<const b4*>(w + mb * 96 * WP + KB * 3072) + lane;
+        const b4 fm = p[0], fh = p[64], fl = p[128];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float v = weight(fm[e], fh[e], fl[e]);
+#pragma unroll
+          for (int s = S0; s < S0 + NS; ++s) Y[s][mb] = mma_f32(v, X[s][MB - 1][e], Y[s][mb]);
+        }
       }
     }
   }
@@ -1841,19 +1876,32 @@ __device__ __forceinline__ int grad_map(const NetDesc& nd, int gi, ParamPos& p) 
   return nd.adaptive && r < D ? base + DO * w + DO + r : -1;
 }
 
+// The split of one value over the whole range of float32: an infinite one is
+// its first part alone, and one that rounds to infinity (from 3.3961e38) has the
+// largest finite bf16 there, so the parts always add up to the value (down to
+// the last bit of the smallest bf16, 2^-133).
+__device__ __forceinline__ void split_any(float x, __bf16& h, __bf16& m, __bf16& l) {
+  const float top = __uint_as_float(0x7f7f0000u);   // largest finite bf16
+  const float hf = isinf(x) ? x : fminf(fmaxf(x, -top), top);
+  h = (__bf16)(isnan(x) ? x : hf);
+  const float r = isinf(x) ? 0.f : x - (float)h;
+  m = (__bf16)r;
+  l = (__bf16)(r - (float)m);
+}
+
 // write the kernel-layout copy of a parameter with value v
 __device__ __forceinline__ void put_param(float* K, const ParamPos& p, float v) {
   if (p.k1 >= 0) {
     K[p.k1] = p.sc * v;
     return;
   }
-  b2 h, m, l;
-  split2(v, v, h, m, l);
+  __bf16 h, m, l;
+  split_any(v, h, m, l);
   __bf16* W = reinterpret_cast<__bf16*>(K) + p.w;
   __bf16* T = reinterpret_cast<__bf16*>(K) + p.t;
-  W[0] = T[0] = m[0];
-  W[p.ws] = T[p.ts] = h[0];
-  W[2 * p.ws] = T[2 * p.ts] = l[0];
+  W[0] = T[0] = m;
+  W[p.ws] = T[p.ts] = h;
+  W[2 * p.ws] = T[2 * p.ts] = l;
 }
 
 // network holding flat parameter i, searching upward from network n
@@ -2050,8 +2098,10 @@ __device__ __forceinline__ float sin_cos_value(int act, float y) {
 }
 
 // one network at up to 16 NG points: xs, ys the lane's points (16 i + pc of
-// each of the NG groups), val(i, c, u) takes output c of group i's point
-template <int WP, int NG, class F>
+// each of the NG groups), val(i, c, u) takes output c of group i's point.
+// EXACT: contractions in float32, the padding's activations 0 whatever the
+// point and the slope
+template <int WP, int NG, bool EXACT, class F>
 __device__ __forceinline__ void eval_net(const float* K, const NetDesc& nd, int lane, const float (&xs)[4],
                                          const float (&ys)[4], F val) {
   using T = Tile<WP, PDE_POISSON>;
@@ -2077,7 +2127,9 @@ __device__ __forceinline__ void eval_net(const float* K, const NetDesc& nd, int 
 #pragma unroll
         for (int j = 0; j < NG; ++j) A[j][mb] = b;
       }
-      T::template contract<0, NG>(reinterpret_cast<const char*>(K + L.k_w(k)), lane, H, A);
+      const char* w = reinterpret_cast<const char*>(K + L.k_w(k));
+      if constexpr (EXACT) T::template contract_f32<0, NG>(w, lane, H, A);
+      else T::template contract<0, NG>(w, lane, H, A);
     }
     if (nd.act == ACT_TANH) {
 #pragma unroll
@@ -2093,6 +2145,14 @@ __device__ __forceinline__ void eval_net(const float* K, const NetDesc& nd, int 
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) H[j][mb][i] = sin_cos_value(nd.act, c * A[j][mb][i]);
+    }
+    if constexpr (EXACT) {
+#pragma unroll
+      for (int j = 0; j < NG; ++j)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) H[j][mb][i] = 16 * mb + 4 * g + i < nd.width ? H[j][mb][i] : 0.f;
     }
   }
   for (int o = 0; o < nd.d_out; ++o) {
@@ -2165,12 +2225,22 @@ __global__ __launch_bounds__(NT, 2) void k_eval(const float* kparams, const NetD
   }
   __syncthreads();
   // work units of up to 64 pairs of one subdomain, dealt out to the waves
+  struct Seg {
+    int q, b, e, step;
+  };
+  auto segment = [&](int sg) {
+    Seg s;
+    s.q = __builtin_amdgcn_readfirstlane(s_seg[sg][0]);
+    s.b = __builtin_amdgcn_readfirstlane(s_seg[sg][1]);
+    s.e = sg + 1 < n_seg ? __builtin_amdgcn_readfirstlane(s_seg[sg + 1][1]) : filled;
+    const int groups = min(4, (s.e - s.b + 63) / 64);   // 16-point groups a unit: every wave gets a share first
+    s.step = 16 * (groups == 3 ? 4 : groups);
+    return s;
+  };
+  bool again = false;   // an output of this wave was not finite
   int unit = 0;
   for (int sg = 0; sg < n_seg; ++sg) {
-    const int q = __builtin_amdgcn_readfirstlane(s_seg[sg][0]), b = __builtin_amdgcn_readfirstlane(s_seg[sg][1]);
-    const int e = sg + 1 < n_seg ? __builtin_amdgcn_readfirstlane(s_seg[sg + 1][1]) : filled;
-    const int groups = min(4, (e - b + 63) / 64);   // 16-point groups a unit: every wave gets a share first
-    const int step = 16 * (groups == 3 ? 4 : groups);
+    const auto [q, b, e, step] = segment(sg);
     for (int u0 = b; u0 < e; u0 += step, ++unit) {
       if ((unit & (kWaves - 1)) != wave) continue;
       const int end = min(e, u0 + step);
@@ -2190,10 +2260,12 @@ __global__ __launch_bounds__(NT, 2) void k_eval(const float* kparams, const NetD
             xs[j] = s_xy[2 * (pr[j] >> 2)];
             ys[j] = s_xy[2 * (pr[j] >> 2) + 1];
           }
+          bool finite = true;
           auto val = [&](int j, int o, float v) {
+            finite = finite && fabsf(v) < INFINITY;
             if (lane < 16 && 16 * j + lane < left && col + o < n_cols) s_val[pr[j]][col + o] = v;
           };
-#define DDP_EVAL(WPV, NGV) eval_net<WPV, NGV>(K, nd, lane, xs, ys, val)
+#define DDP_EVAL(WPV, NGV) eval_net<WPV, NGV, false>(K, nd, lane, xs, ys, val)
 #define DDP_EVAL_CASE(WPV, BIG)                \
   case WPV:                                    \
     if (left <= 16) DDP_EVAL(WPV, 1);          \
@@ -2212,8 +2284,54 @@ __global__ __launch_bounds__(NT, 2) void k_eval(const float* kparams, const NetD
           }
 #undef DDP_EVAL_CASE
 #undef DDP_EVAL
+          again = again || __any(!finite);
         }
         col += nd.d_out;
+      }
+    }
+  }
+  // An infinite weight or point saturates its neurons, but is no sum of bf16
+  // parts, and at an infinite point the padding's 0 times infinity reaches
+  // every neuron: the wave's outputs that are not finite, and only they, are
+  // computed again in float32, 16 points at a time.
+  if (again) {
+    wave_fence();
+    unit = 0;
+    for (int sg = 0; sg < n_seg; ++sg) {
+      const auto [q, b, e, step] = segment(sg);
+      for (int u0 = b; u0 < e; u0 += step, ++unit) {
+        if ((unit & (kWaves - 1)) != wave) continue;
+        for (int u1 = u0; u1 < min(e, u0 + step); u1 += 16) {
+          const int k = u1 + (lane & 15), last = min(e, u0 + step) - 1;
+          const int pr = s_order[min(k, last)];
+          const float xs[4] = {s_xy[2 * (pr >> 2)]}, ys[4] = {s_xy[2 * (pr >> 2) + 1]};
+          int col = 0;
+          for (int net = sd_net[q]; net < sd_net[q + 1]; ++net) {
+            const NetDesc nd = nets[net];
+            const float* K = kparams + nd.koff;
+            auto val = [&](int, int o, float v) {
+              if (lane >= 16 || k > last || col + o >= n_cols) return;
+              float& had = s_val[pr][col + o];
+              if (!(fabsf(had) < INFINITY)) had = v;
+            };
+#define DDP_EVAL_CASE(WPV)                            \
+  case WPV:                                           \
+    eval_net<WPV, 1, true>(K, nd, lane, xs, ys, val); \
+    break;
+            switch (nd.wclass) {
+              DDP_EVAL_CASE(16)
+              DDP_EVAL_CASE(32)
+              DDP_EVAL_CASE(48)
+              DDP_EVAL_CASE(64)
+              DDP_EVAL_CASE(80)
+              DDP_EVAL_CASE(96)
+              DDP_EVAL_CASE(112)
+              default: break;
+            }
+#undef DDP_EVAL_CASE
+            col += nd.d_out;
+          }
+        }
       }
     }
   }

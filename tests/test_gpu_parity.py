@@ -963,3 +963,67 @@ def test_parameters_captured_by_the_caller():
             assert np.array_equal(np.concatenate(pb.get_params()), want)
     torch.cuda.synchronize()
     pb.close()
+
+
+def _hidden(widths, k):
+    """Offset of hidden matrix W^k in a network's flat parameters, and the width."""
+    w = widths[1]
+    return 3 * w + (k - 2) * (w * w + w), w
+
+
+def _extremes():
+    """Hidden weights out of the ordinary range: name -> (value, layer, row,
+    column) of what is written."""
+    inf, nan = np.inf, np.nan
+    return {"none": [], "inf in W2": [(inf, 2, 1, 5)], "-inf in W3": [(-inf, 3, 2, 1)],
+            "inf and -inf": [(inf, 3, 0, 0), (-inf, 3, 0, 1)], "largest": [(3.4028235e38, 2, 4, 3)],
+            "rounds up in bf16": [(-3.397e38, 3, 1, 1)], "1e30": [(1e30, 3, 1, 2)], "nan": [(nan, 2, 1, 1)],
+            "1e-36": [(1e-36, 2, 1, 1)]}
+
+
+def _with_extremes(prob, params, muts):
+    out = [p.copy() for p in params]
+    for p, s in zip(out, prob.subdomains):
+        for v, k, m, j in muts:
+            off, w = _hidden(s.widths, k)
+            p[off + m * w + j] = v
+    return out
+
+
+@pytest.mark.parametrize("widths", [(5, 16, 20, 32), (33, 48, 60, 64), (70, 80, 90, 112)])
+@pytest.mark.parametrize("adaptive", [False, True])
+def test_eval_beyond_the_ordinary_range(widths, adaptive):
+    """Infinite and very large weights and points at infinity saturate the
+    neurons they feed, as in float32 arithmetic, and NaN stays with its point
+    or network: the same finite points as the oracle's, and the bound of the
+    grid evaluations there; a finite point's bits do not depend on the points
+    beside it."""
+    prob = W.custom_box_problem("xpinn", "poisson2d", 2, 2, [[2] + [w] * 3 + [1] for w in widths], [9] * 4,
+                                n_bnd_seg=3, n_iface=3, seed=sum(widths))
+    if adaptive:
+        W.with_activations(prob, ("tanh",))
+    params = _params(prob, 23)
+    rng = np.random.default_rng(7)
+    n = 333
+    xy = rng.uniform(0.0, 1.0, (n, 2)).astype(np.float32)
+    owner = np.full((n, 4), -1, np.int32)
+    owner[:, 0] = rng.integers(0, 4, n)
+    owner[::5, 1] = (owner[::5, 0] + 1) % 4
+    far = xy.copy()
+    far[::17, 0] = [np.inf, -np.inf, np.nan, 3e38] * 5
+    pb = ddpinn.Problem(prob, fused=True)
+    for name, muts in _extremes().items():
+        _say(f"eval, widths {widths}, adaptive {adaptive}: {name}")
+        q = _with_extremes(prob, params, muts)
+        if adaptive and name == "none":
+            q[1][-2] = np.inf   # a slope
+        pb.set_params(q)
+        near, got = (pb.eval(x, owner).cpu().numpy() for x in (xy, far))
+        with np.errstate(all="ignore"):
+            want = oracle.eval_stitched(prob, q, far, owner)
+        assert np.array_equal(np.isfinite(got), np.isfinite(want)), name
+        ok = np.isfinite(want)
+        np.testing.assert_allclose(got[ok], want[ok], rtol=1e-5, atol=1e-6, err_msg=name)
+        same = np.isfinite(far).all(1) & (far[:, 0] == xy[:, 0])
+        assert np.array_equal(near[same], got[same], equal_nan=True), name
+    pb.close()
