@@ -44,6 +44,7 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
 constexpr int TP = kTilePts;      // points per tile
+constexpr float kTinySeed = 0x1p-80f;   // items with nonzero output seeds below this run in float32 (Plain)
 constexpr int NT = 64 * kWaves;   // threads per workgroup
 
 // One 16-byte-per-lane store into the activation stash, followed by wait
@@ -864,6 +865,24 @@ struct Tile {
     }
   }
 
+  __device__ __forceinline__ static bool finite4(const float (&v)[4]) {
+    return fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, v[3] * 0.f))) == 0.f;
+  }
+  __device__ __forceinline__ static bool finite_streams(const float (&u)[DO][4]) {
+    bool f = finite4(u[0]);
+#pragma unroll
+    for (int c = 1; c < DO; ++c) f = f && finite4(u[c]);
+    return f;
+  }
+  __device__ __forceinline__ static bool tiny_seeds(const float (&ub)[DO][4]) {
+    float top = 0.f;
+#pragma unroll
+    for (int c = 0; c < DO; ++c)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) top = fmaxf(top, fabsf(ub[c][s]));
+    return top > 0.f && top < kTinySeed;
+  }
+
   // values this network contributes on an interface: u (DO) then the normal
   // flux (cPINN) or the operator value L_x(u) without forcing (XPINN)
   __device__ static void own_values(int method, const float (&u)[DO][4], float nx, float ny, float coef,
@@ -1073,8 +1092,8 @@ struct Tile {
 
   template <int MODE, int PHASE, bool GA>
   __device__ __forceinline__ static void run_train(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds,
-                                   float* slot, int64_t slot_floats, const float* sNb, float* sInv, float* sOW, int t_lo,
-                                   int t_hi, int roff) {
+                                   float* slot, int64_t slot_floats, const float* sNb, float* sInv, float* sOW, int* sBad,
+                                   int t_lo, int t_hi, int roff) {
     char* sW = reinterpret_cast<char*>(lds);
     float* sA = reinterpret_cast<float*>(sW + sums_offset(WP));   // sums of the output layer and of layer 1
     char* sS = sW + (stage_over_weights(WP) ? 0 : WBYTES);   // staging area of dW
@@ -1165,6 +1184,7 @@ struct Tile {
         out_fwd(sOW, sOW + DO * WP, g, H, u);
       }
       if constexpr (PHASE == PH_FWD) {
+        if (!finite_streams(u)) *sBad = 1;
         if (g == 0) {
 #pragma unroll
           for (int s = 0; s < 3; ++s) sInv[3 * tp + s] = u[0][s];
@@ -1175,6 +1195,7 @@ struct Tile {
       // ---- loss terms and output seeds
       float ub[DO][4], loss[kLossTerms], kb[3];
       epilogue<MODE>(ka, it, nd, tp, valid, tgt, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss, kb);
+      if (!finite_streams(u) || !finite4(loss) || tiny_seeds(ub)) *sBad = 1;
 #pragma unroll
       for (int t = 0; t < kLossTerms; ++t) {
         const float v = row_sum16(loss[t]);   // (the same in every lane group)
@@ -1642,6 +1663,8 @@ struct Tile {
             dw1 += sOut[(wv * 3 + 1) * WP + tid];
             db += sOut[(wv * 3 + 2) * WP + tid];
           }
+          // whatever is not finite in the reverse pass arrives here
+          if (!(fmaf(dw0, 0.f, fmaf(dw1, 0.f, db * 0.f)) == 0.f)) *sBad = 1;
           R[4 * tid] = dw0;
           R[4 * tid + 1] = dw1;
           R[4 * tid + 2] = db;
@@ -1651,6 +1674,467 @@ struct Tile {
     }
   }
 
+};
+
+// Whether the network's first hidden matrix begins with NaN, as all of a
+// network's parameters are after one step on a gradient of NaN: every output
+// and gradient entry is NaN in any arithmetic.
+__device__ __forceinline__ bool nan_network(const KArgs& ka, const NetDesc& nd) {
+  const Layout L(nd.wclass, nd.depth, nd.d_out);
+  return nd.depth >= 2 && isnan((float)*reinterpret_cast<const __bf16*>(ka.kparams + nd.koff + L.k_w(2)));
+}
+
+// ---------------------------------------------------------------------------
+// The same item in float32 throughout, with sizes known at run time, for what
+// is no sum of three bf16 parts: infinities (a split one is infinity and NaN,
+// and the dot products of the split carry the NaN to the neuron beside it),
+// values from 3.3961e38 on, and below 2^-109 the last bits.  Tile notes when a
+// tile's outputs, losses or first-layer gradients are not finite, where all
+// such values end up, or its output seeds are all below kTinySeed; the
+// workgroup then runs the item again here, over the rows it has written.
+//
+// Rare, so short and light on registers rather than fast: a wave takes its 16
+// points from layer to layer, pre-activations and adjoints through the stash
+// slot (Tile's layout, layer 1's place taken by the adjoints), weights from the
+// kernel copy in the L2 cache, contractions on the 16x16x4 float32 MFMA.
+template <int PDE, bool GA>
+struct Plain {
+  using T = Tile<16, PDE>;   // for what does not depend on the width
+  typedef __attribute__((address_space(4))) KArgs Args;   // the kernel's arguments where they lie
+  typedef __attribute__((address_space(3))) float Lds;
+  static constexpr int DO = Op<PDE>::DO, NEQ = Op<PDE>::NEQ;
+  static constexpr bool S2 = Op<PDE>::S2;
+
+  const KArgs& ka;
+  const Item& it;
+  const NetDesc& nd;
+  float* st;        // the network's stash
+  const int t0;     // the tile's first point
+  const int WP, MB, D;
+  const Layout L;
+  const float* K;
+  const float* xy;
+  int tid, lane, wave, g, pc;
+
+  __device__ Plain(const KArgs& ka_, const Item& it_, const NetDesc& nd_, float* st_, int t0_)
+      : ka(ka_), it(it_), nd(nd_), st(st_), t0(t0_), WP(nd_.wclass), MB(nd_.wclass / 16), D(nd_.depth),
+        L(nd_.wclass, nd_.depth, DO), K(ka_.kparams + nd_.koff) {
+    xy = it.kind == KIND_RES ? ka.res_xy : it.kind == KIND_DATA ? ka.dat_xy : it.kind == KIND_AUX ? ka.aux_xy : ka.if_xy;
+    tid = item_tid();
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    g = lane >> 4;
+    pc = lane & 15;
+  }
+
+  __device__ float coord(int p, int c) const { return t0 + p < it.count ? xy[2 * (int64_t)(it.begin + t0 + p) + c] : 0.f; }
+  // place of (layer, wave, stream, block, lane) in the stash, 4 neurons each
+  __device__ float* place(int layer, int wv, int s, int mb, int ln) const {
+    return st + ((((int64_t)(layer - 1) * kWaves + wv) * 4 + s) * MB + mb) * 256 + 4 * ln;
+  }
+  __device__ f4 load4(int layer, int s, int mb) const {
+    const float* p = place(layer, wave, s, mb, lane);
+    f4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = T::device_load(p + i);
+    return v;
+  }
+  __device__ void store4(int layer, int s, int mb, f4 v) const {
+    *reinterpret_cast<f4*>(place(layer, wave, s, mb, lane)) = v;
+  }
+  // pre-activation streams of layer 1, neuron n, at (x, y)
+  __device__ void first_layer(int n, float x, float y, float (&a)[4]) const {
+    const f4 c = *reinterpret_cast<const f4*>(K + 4 * n);
+    a[0] = fmaf(c[0], x, fmaf(c[1], y, c[2]));
+    a[1] = c[0];
+    a[2] = c[1];
+    a[3] = 0.f;
+  }
+  // the lane's four neurons of block mb of layer k: pre-activation streams
+  __device__ void pre(int k, int mb, float x, float y, f4 (&A)[4]) const {
+    if (k == 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float a[4];
+        first_layer(16 * mb + 4 * g + i, x, y, a);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) A[s][i] = a[s];
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) A[s] = load4(k, s, mb);
+    }
+  }
+  __device__ void rule(float c, float a, float ax, float ay, float al, float (&h)[4]) const {
+    if constexpr (GA) act_rule<S2>(nd.act, c, a, ax, ay, al, h[0], h[1], h[2], h[3]);
+    else tanh_rule<S2>(a, ax, ay, al, h[0], h[1], h[2], h[3]);
+  }
+  __device__ void post(int k, int mb, float x, float y, f4 (&H)[4]) const {
+    f4 A[4];
+    pre(k, mb, x, y, A);
+    const float c = T::slope(nd, K, L, k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float h[4];
+      rule(c, A[0][i], A[1][i], A[2][i], A[3][i], h);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) H[s][i] = h[s];
+    }
+  }
+  __device__ void adjoint(float c, float a, float ax, float ay, float al, f4 (&G)[4], int i, float& dc) const {
+    float b[4];
+    if constexpr (GA)
+      act_adj<S2>(nd.act, c, a, ax, ay, al, G[0][i], G[1][i], G[2][i], G[3][i], b[0], b[1], b[2], b[3], dc);
+    else
+      tanh_adj<S2>(a, ax, ay, al, G[0][i], G[1][i], G[2][i], G[3][i], b[0], b[1], b[2], b[3]);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) G[s][i] = b[s];
+  }
+  // acc_s += (rows of block rb) x (columns of block cb) of split matrix M times X_s
+  __device__ void block(const float* M, int rb, int cb, const f4 (&X)[4], f4 (&acc)[4]) const {
+    int ps;
+    const __bf16* p = reinterpret_cast<const __bf16*>(M) + split_pos(WP, 16 * rb + pc, 16 * cb + 4 * g, ps);
+    const b4 m = *reinterpret_cast<const b4*>(p), h = *reinterpret_cast<const b4*>(p + ps),
+             l = *reinterpret_cast<const b4*>(p + 2 * ps);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float w = (float)h[i] + ((float)m[i] + (float)l[i]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[s] = mma_f32(w, X[s][i], acc[s]);
+    }
+  }
+  // the wave's own stores have arrived before its next loads
+  __device__ void settle() const {
+    wave_fence();
+    dma_landed();
+    wave_fence();
+  }
+
+  // hidden layers 2 .. D, pre-activations to the stash
+  __device__ void forward(float x, float y) const {
+#pragma unroll 1
+    for (int k = 2; k <= D; ++k) {
+#pragma unroll 1
+      for (int mb = 0; mb < MB; ++mb) {
+        f4 acc[4] = {};
+        acc[0] = *reinterpret_cast<const f4*>(K + L.k_b(k) + 16 * mb + 4 * g);
+#pragma unroll 1
+        for (int jb = 0; jb < MB; ++jb) {
+          f4 H[4];
+          post(k - 1, jb, x, y, H);
+          block(K + L.k_w(k), mb, jb, H, acc);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) store4(k, s, mb, acc[s]);
+      }
+      settle();
+    }
+  }
+  __device__ void outputs(float x, float y, float (&u)[DO][4]) const {
+    float acc[DO][4] = {};
+#pragma unroll 1
+    for (int mb = 0; mb < MB; ++mb) {
+      f4 H[4];
+      post(D, mb, x, y, H);
+#pragma unroll
+      for (int c = 0; c < DO; ++c) {
+        const f4 w = *reinterpret_cast<const f4*>(K + L.k_out() + c * WP + 16 * mb + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc[c][s] = fmaf(w[i], H[s][i], acc[c][s]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < DO; ++c)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) u[c][s] = group_sum(acc[c][s]) + (s == 0 ? K[L.k_bout() + c] : 0.f);
+  }
+
+  // values_tile
+  template <int VMODE>
+  __device__ void values(float* dst, const float* kin) const {
+    const int tp = wave * 16 + pc;
+    const float x = coord(tp, 0), y = coord(tp, 1);
+    float u[DO][4];
+    forward(x, y);
+    outputs(x, y, u);
+    if (g != 0) return;
+    if constexpr (VMODE == VAL_OWN) {
+      const IfaceDesc ifd = ka.ifaces[it.iface];
+      float ov[DO + NEQ];
+      T::own_values(ifd.method, u, ifd.nx, ifd.ny, ka.coef0, ov);
+#pragma unroll
+      for (int v = 0; v < DO + NEQ; ++v) dst[tp * (DO + NEQ) + v] = ov[v];
+    } else if constexpr (VMODE == VAL_STREAMS) {
+#pragma unroll
+      for (int s = 0; s < 3; ++s) dst[3 * tp + s] = u[0][s];
+    } else {
+      const float Kv = kin[3 * tp], Kx = kin[3 * tp + 1], Ky = kin[3 * tp + 2];
+      dst[3 * tp] = u[0][0];
+      dst[3 * tp + 1] = Kv;
+      dst[3 * tp + 2] = fmaf(Kv, u[0][3], fmaf(Kx, u[0][1], Ky * u[0][2]));
+    }
+  }
+
+  // run_train on one tile (red: LDS for the sums over the waves)
+  template <int MODE, int PHASE>
+  __device__ void train(float* red, const float* sNb, float* sInv, int roff) const {
+    const int tp = wave * 16 + pc;
+    const bool first = t0 == 0, valid = t0 + tp < it.count;
+    const float x = coord(tp, 0), y = coord(tp, 1);
+    float* R = ka.partial + it.prow + roff;
+    float* sSl = red;                                        // [kMaxDepth][kWaves] slope-gradient sums
+    float* sLoss = sSl + kMaxDepth * kWaves;                 // [kWaves][kLossTerms]
+    float* sOutB = sLoss + kWaves * kLossTerms;              // [kWaves][DO]
+    float* sOut = sOutB + kWaves * DO;                       // [kWaves][DO or 3][WP]
+    float u[DO][4] = {};
+    if constexpr (PHASE != PH_BWD) {
+      forward(x, y);
+      outputs(x, y, u);
+    }
+    if constexpr (PHASE == PH_FWD) {
+      if (g == 0) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) sInv[3 * tp + s] = u[0][s];
+      }
+      return;
+    }
+    __syncthreads();   // the K streams are there, and the sums' place is free
+    float tgt[NTGT] = {};
+    if (valid && MODE != EPI_SEED && it.kind != KIND_IFACE) {
+      const float* tg = it.kind == KIND_RES ? ka.res_f : it.kind == KIND_DATA ? ka.dat_g : ka.aux_g;
+      const int nt = it.kind == KIND_RES ? NEQ : DO;
+#pragma unroll
+      for (int c = 0; c < NTGT; ++c)
+        if (c < nt) tgt[c] = tg[(int64_t)(it.begin + t0 + tp) * nt + c];
+    }
+    float ub[DO][4], loss[kLossTerms], kb[3];
+    T::template epilogue<MODE>(ka, it, nd, tp, valid, tgt, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss,
+                               kb);
+#pragma unroll
+    for (int t = 0; t < kLossTerms; ++t) {
+      const float v = row_sum16(loss[t]);
+      if (lane == 0) sLoss[wave * kLossTerms + t] = v;
+    }
+    if constexpr (MODE == EPI_INV_U) {
+      if (g == 0) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) sInv[3 * TP + 3 * tp + s] = kb[s];
+      }
+    }
+    // output layer: its gradient, and g^D into layer 1's place
+    int at = 1;
+#pragma unroll 1
+    for (int mb = 0; mb < MB; ++mb) {
+      f4 H[4], G[4] = {};
+      post(D, mb, x, y, H);
+#pragma unroll
+      for (int c = 0; c < DO; ++c) {
+        const f4 w = *reinterpret_cast<const f4*>(K + L.k_out() + c * WP + 16 * mb + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float v = ub[c][0] * H[0][i];
+#pragma unroll
+          for (int s = 1; s < 4; ++s) v = fmaf(ub[c][s], H[s][i], v);
+          v = row_sum16(v);
+          if (pc == 0) sOut[(wave * DO + c) * WP + 16 * mb + 4 * g + i] = v;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) G[s][i] = fmaf(w[i], ub[c][s], G[s][i]);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) store4(at, s, mb, G[s]);
+    }
+#pragma unroll
+    for (int c = 0; c < DO; ++c) {
+      const float v = row_sum16(ub[c][0]);
+      if (lane == 0) sOutB[wave * DO + c] = v;
+    }
+    settle();
+    __syncthreads();
+    for (int t = tid; t < DO * WP; t += NT) {
+      float v = T::prior(R + L.g_out() + t, first);
+      for (int w = 0; w < kWaves; ++w) v += sOut[w * DO * WP + t];
+      R[L.g_out() + t] = v;
+    }
+    if (tid < DO) {
+      float v = T::prior(R + L.g_bout() + tid, first);
+      for (int w = 0; w < kWaves; ++w) v += sOutB[w * DO + tid];
+      R[L.g_bout() + tid] = v;
+    }
+    if (MODE != EPI_SEED && tid < kLossTerms) {
+      float v = 0.f;
+      for (int w = 0; w < kWaves; ++w) v += sLoss[w * kLossTerms + tid];
+      T::accum(ka.loss_part + (int64_t)it.lrow * kLossTerms + tid, v * it.inv_n, first);
+    }
+
+    // hidden layers: the adjoint in place of g^k (place at), dW^k and db^k from
+    // all waves' shares, then g^{k-1} in layer k's place
+#pragma unroll 1
+    for (int k = D; k >= 2; --k) {
+      const float c = T::slope(nd, K, L, k);
+      float dc = 0.f;
+#pragma unroll 1
+      for (int mb = 0; mb < MB; ++mb) {
+        f4 A[4], G[4];
+        pre(k, mb, x, y, A);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) G[s] = load4(at, s, mb);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) adjoint(c, A[0][i], A[1][i], A[2][i], A[3][i], G, i, dc);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) store4(at, s, mb, G[s]);
+      }
+      if constexpr (GA) T::slope_wave_sum(dc, sSl + (k - 1) * kWaves, lane, wave);
+      settle();
+      __syncthreads();
+      if constexpr (GA) {
+        if (nd.adaptive && tid == 0) slope_grad(R, sSl, k, first);
+      }
+      const float c1 = T::slope(nd, K, L, k - 1);
+#pragma unroll 1
+      for (int b = wave; b < MB * MB; b += kWaves) {
+        const int mb = b / MB, jb = b % MB;
+        float* Rw = R + L.g_w(k) + (16 * mb + 4 * g) * WP + 16 * jb + pc;
+        float* Rb = R + L.g_b(k) + 16 * mb + 4 * g;
+        f4 acc, accb;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[i] = T::prior(Rw + i * WP, first);
+          accb[i] = T::prior(Rb + i, first);
+        }
+#pragma unroll 1
+        for (int p = g; p < TP; p += 4) {   // neuron pc of the blocks at point p
+          const int ln = 16 * (pc >> 2) + (p & 15), i = pc & 3;
+          float a[4], h[4];
+          if (k == 2) {
+            first_layer(16 * jb + pc, coord(p, 0), coord(p, 1), a);
+          } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) a[s] = T::device_load(place(k - 1, p >> 4, s, jb, ln) + i);
+          }
+          rule(c1, a[0], a[1], a[2], a[3], h);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) a[s] = T::device_load(place(at, p >> 4, s, mb, ln) + i);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc = mma_f32(a[s], h[s], acc);
+          accb = mma_f32(a[0], 1.f, accb);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Rw[i * WP] = acc[i];
+        if (jb == 0 && pc == 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) Rb[i] = accb[i];
+        }
+      }
+#pragma unroll 1
+      for (int jb = 0; jb < MB; ++jb) {
+        f4 acc[4] = {};
+#pragma unroll 1
+        for (int mb = 0; mb < MB; ++mb) {
+          f4 G[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) G[s] = load4(at, s, mb);
+          block(K + L.k_wt(k), jb, mb, G, acc);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) store4(k, s, jb, acc[s]);
+      }
+      at = k;
+      settle();
+    }
+
+    // layer 1
+    float dc = 0.f;
+    const float c = T::slope(nd, K, L, 1);
+    __syncthreads();   // the output layer's sums have been read
+#pragma unroll 1
+    for (int mb = 0; mb < MB; ++mb) {
+      f4 A[4], G[4];
+      pre(1, mb, x, y, A);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) G[s] = load4(at, s, mb);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        adjoint(c, A[0][i], A[1][i], A[2][i], A[3][i], G, i, dc);
+        const float r0 = row_sum16(fmaf(G[0][i], x, G[1][i])), r1 = row_sum16(fmaf(G[0][i], y, G[2][i])),
+                    r2 = row_sum16(G[0][i]);
+        if (pc == 0) {
+          const int n = 16 * mb + 4 * g + i;
+          sOut[(wave * 3 + 0) * WP + n] = r0;
+          sOut[(wave * 3 + 1) * WP + n] = r1;
+          sOut[(wave * 3 + 2) * WP + n] = r2;
+        }
+      }
+    }
+    if constexpr (GA) T::slope_wave_sum(dc, sSl, lane, wave);
+    __syncthreads();
+    if constexpr (GA) {
+      if (nd.adaptive && tid == 0) slope_grad(R, sSl, 1, first);
+    }
+    if (tid < WP) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        float v = T::prior(R + 4 * tid + q, first);
+        for (int w = 0; w < kWaves; ++w) v += sOut[(w * 3 + q) * WP + tid];
+        R[4 * tid + q] = v;
+      }
+      if (first) R[4 * tid + 3] = 0.f;
+    }
+    __syncthreads();   // the sums have been read
+  }
+  static constexpr int NTGT = DO > NEQ ? DO : NEQ;
+  __device__ void slope_grad(float* R, const float* sSl, int k, bool first) const {
+    const float* v = sSl + (k - 1) * kWaves;
+    T::accum(R + L.g_slope() + k - 1, (v[0] + v[1]) + (v[2] + v[3]), first);
+  }
+
+  // dispatch of item idx (lds: the tile buffers; lds + nb_at: sNb and what
+  // follows it as there).  Not inlined, and everything read again from the
+  // kernel's arguments, for the registers of the path that matters: inlined a
+  // step of 4 networks of 20 took 31.9 instead of 30.3 us, as a switch inside
+  // Tile 32.6 (and 3 strips of 50 wide 275 instead of 216); so it takes 30.8
+  // (and the strips 212).
+  __device__ __attribute__((noinline, cold)) static void item(const Args* args, int index, Lds* lds, int nb_at,
+                                                              float* slot) {
+    const KArgs& ka = *(const KArgs*)args;
+    const int idx = __builtin_amdgcn_readfirstlane(index);
+    float* red = (float*)lds;
+    float* sNb = (float*)(lds + nb_at);
+    const Item& it = ka.items[idx];
+    const NetDesc& nd = ka.nets[it.q];
+    if (nan_network(ka, nd)) return;
+    dma_landed();   // the rows are written again by other waves
+    __syncthreads();
+    float* sInv = sNb + 6 * TP;
+    const IfaceDesc& ifd = ka.ifaces[it.kind == KIND_IFACE ? it.iface : 0];
+    const NetDesc& nb = it.kind == KIND_IFACE ? ka.nets[it.side == 0 ? ifd.b_net : ifd.a_net] : nd;
+#pragma unroll 1
+    for (int t0 = 0; t0 < it.count; t0 += TP) {
+      if constexpr (PDE == PDE_INV) {
+        if (nd.pair >= 0 && (it.kind == KIND_RES || it.kind == KIND_IFACE)) {
+          const NetDesc& ndk = ka.nets[nd.pair];
+          const int64_t half = ka.scratch_slot / 2;
+          if (it.kind == KIND_IFACE) {
+            const NetDesc& nbk = ka.nets[nb.pair];
+            Plain(ka, it, nbk, slot, t0).template values<VAL_STREAMS>(sInv + 6 * TP, nullptr);
+            __syncthreads();
+            Plain(ka, it, nb, slot, t0).template values<VAL_INV_NB>(sNb, sInv + 6 * TP);
+          }
+          const Plain k(ka, it, ndk, slot + half, t0);
+          k.template train<EPI_SEED, PH_FWD>(red, sNb, sInv, nd.gsize);
+          Plain(ka, it, nd, slot, t0).template train<EPI_INV_U, PH_ALL>(red, sNb, sInv, 0);
+          k.template train<EPI_SEED, PH_BWD>(red, sNb, sInv, nd.gsize);
+          continue;
+        }
+      } else if (it.kind == KIND_IFACE) {
+        Plain(ka, it, nb, slot, t0).template values<VAL_OWN>(sNb, nullptr);
+      }
+      Plain(ka, it, nd, slot, t0).template train<EPI_OWN, PH_ALL>(red, sNb, sInv, 0);
+    }
+    __syncthreads();
+  }
 };
 
 // LDS floats of a train kernel for classes up to WP: the tile buffers of
@@ -1682,7 +2166,7 @@ constexpr int lds_train_bytes() {
 // train pass (loss, u seeds, K seeds), then the K-network's train pass.
 template <int WPMAX, int PDE, bool GA>
 __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const NetDesc& nd, float* lds,
-                                         float* slot) {
+                                         float* slot, int* sBad) {
   float* sNb = lds + lds_tile_floats<WPMAX, PDE>();
   float* sInv = sNb + 6 * TP;
   float* sOW = sInv + (PDE == PDE_INV ? 9 * TP : 0);   // output-layer weights and biases of the network in training
@@ -1724,11 +2208,12 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
           __syncthreads();
         }
         DDP_SWITCH(ndk.wclass, template run_train<EPI_SEED, PH_FWD, GA>(ka, it, ndk, lds, slot + half, half,
-                                                                            sNb, sInv, sOW, t0, t0 + 1, nd.gsize))
+                                                                            sNb, sInv, sOW, sBad, t0, t0 + 1, nd.gsize))
         DDP_SWITCH(nd.wclass,
-                   template run_train<EPI_INV_U, PH_ALL, GA>(ka, it, nd, lds, slot, half, sNb, sInv, sOW, t0, t0 + 1, 0))
+                   template run_train<EPI_INV_U, PH_ALL, GA>(ka, it, nd, lds, slot, half, sNb, sInv, sOW, sBad, t0, t0 + 1,
+                                                                 0))
         DDP_SWITCH(ndk.wclass, template run_train<EPI_SEED, PH_BWD, GA>(ka, it, ndk, lds, slot + half, half,
-                                                                            sNb, sInv, sOW, t0, t0 + 1, nd.gsize))
+                                                                            sNb, sInv, sOW, sBad, t0, t0 + 1, nd.gsize))
       }
       return;
     }
@@ -1741,7 +2226,7 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
   }
   DDP_SWITCH(nd.wclass, template run_train<EPI_OWN, PH_ALL, GA>(ka, it, nd, lds, slot,
                                                        PDE == PDE_INV ? ka.scratch_slot / 2 : ka.scratch_slot, sNb,
-                                                       sInv, sOW, 0, it.count, 0))
+                                                       sInv, sOW, sBad, 0, it.count, 0))
 #undef DDP_SWITCH
 #undef DDP_CASE
 }
@@ -1779,6 +2264,7 @@ __global__ __launch_bounds__(NT, min_waves_per_eu<WPMAX>()) void k_train(KArgs k
   // accesses of the tile buffers stay 16-byte aligned)
   extern __shared__ __attribute__((aligned(16))) float lds[];
   int& s_item = *reinterpret_cast<int*>(lds + lds_train_floats<WPMAX, PDE>());
+  int& s_bad = *(&s_item + 1);   // the item has met values that Tile does not hold in full
   float* slot = ka.scratch + (int64_t)blockIdx.x * ka.scratch_slot;
   if (ka.prologue && blockIdx.x == 0 && threadIdx.x == 0) {
     // settle the Adam step counter of the previous update (k_reduce reads it)
@@ -1788,9 +2274,15 @@ __global__ __launch_bounds__(NT, min_waves_per_eu<WPMAX>()) void k_train(KArgs k
   for (int idx = blockIdx.x; idx < ka.n_items;) {
     const Item it = ka.items[idx];
     const NetDesc nd = ka.nets[it.q];
-    dispatch<WPMAX, PDE, GA>(ka, it, nd, lds, slot);
-    if ((int)gridDim.x >= ka.n_items) break;
+    if (threadIdx.x == 0) s_bad = 0;   // (set behind dispatch's first barrier)
+    dispatch<WPMAX, PDE, GA>(ka, it, nd, lds, slot, &s_bad);
     __syncthreads();
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(s_bad), 0)) {
+      using P = Plain<PDE, GA>;
+      P::item((const typename P::Args*)__builtin_amdgcn_kernarg_segment_ptr(), idx, (typename P::Lds*)lds,
+              lds_tile_floats<WPMAX, PDE>(), slot);
+    }
+    if ((int)gridDim.x >= ka.n_items) break;
     if (threadIdx.x == 0) s_item = (int)gridDim.x + atomicAdd(ka.counter, 1);
     __syncthreads();
     idx = __builtin_amdgcn_readfirstlane(s_item);

@@ -1027,3 +1027,80 @@ def test_eval_beyond_the_ordinary_range(widths, adaptive):
         same = np.isfinite(far).all(1) & (far[:, 0] == xy[:, 0])
         assert np.array_equal(near[same], got[same], equal_nan=True), name
     pb.close()
+
+
+@pytest.mark.parametrize("widths", [(20, 32, 60, 16), (80, 100, 48, 112)])
+@pytest.mark.parametrize("adaptive", [False, True])
+def test_gradients_beyond_the_ordinary_range(widths, adaptive):
+    """An infinite, NaN or very large weight in subdomain 0: the loss terms and
+    gradient entries that the oracle finds finite are finite (large finite
+    weights: the value terms, whose derivatives exceed float32), the terms
+    within 1e-5 of it, and the subdomain that shares no interface with it keeps
+    its bits."""
+    prob = W.custom_box_problem("xpinn", "poisson2d", 2, 2, [[2] + [w] * 3 + [1] for w in widths],
+                                [150, 70, 64, 130], n_bnd_seg=9, n_iface=17, seed=sum(widths))
+    if adaptive:
+        W.with_activations(prob, ("tanh",))
+    params = _params(prob, 5)
+    pb, lt0, g0 = run(prob, params)
+    for name, muts in _extremes().items():
+        _say(f"gradients, widths {widths}, adaptive {adaptive}: {name}")
+        q = [params[0].copy()] + params[1:]
+        q[0] = _with_extremes(prob, params, muts)[0]
+        pb.set_params(q)
+        lt, g = (x.cpu().numpy() for x in pb.loss_and_grad())
+        g = pb.split(g)
+        assert np.array_equal(lt[3], lt0[3]) and np.array_equal(g[3], g0[3]), name
+        with np.errstate(all="ignore"):
+            want, wg = oracle.loss_and_grad(prob, q)
+        value_only = any(np.isfinite(m[0]) and abs(m[0]) > 1 for m in muts)
+        cols = [1, 3] if value_only else [0, 1, 2, 3, 4]
+        ok = np.isfinite(want[:, cols])
+        assert np.array_equal(np.isfinite(lt[:, cols]), ok), name
+        np.testing.assert_allclose(lt[:, cols][ok], want[:, cols][ok], rtol=1e-5, err_msg=name)
+        if not value_only and len(muts) < 2:
+            assert all(np.array_equal(np.isfinite(a), np.isfinite(b)) for a, b in zip(g, wg)), name
+    pb.close()
+
+
+@pytest.mark.parametrize("widths", [(20, 32, 60, 16), (80, 100, 48, 112)])
+@pytest.mark.parametrize("adaptive", [False, True])
+def test_gradients_of_tiny_losses(widths, adaptive):
+    """Loss weights of 2^-90 and 2^-100: the gradient scales with them as float32
+    does.  An entry is a sum of at most 1e5 terms that may round at 2^-149, the
+    spacing of the subnormals, and the norm is above 2^-104, so the difference is
+    below 1e5 * 2^-45 < 2^-28 of it."""
+    out = []
+    for k in (90, 100):
+        prob = W.custom_box_problem("xpinn", "poisson2d", 2, 2, [[2] + [w] * 3 + [1] for w in widths],
+                                    [150, 70, 64, 130], n_bnd_seg=9, n_iface=17, seed=sum(widths),
+                                    loss_w=(2.0 ** -k,) * 4)
+        if adaptive:
+            W.with_activations(prob, ("tanh",))
+        _say(f"widths {widths}, adaptive {adaptive}: loss weights 2^-{k}")
+        pb, lt, g = run(prob, _params(prob, 5))
+        out.append(np.concatenate(g).astype(np.float64) * 2.0 ** k)
+        pb.close()
+    assert np.linalg.norm(out[0]) > 2.0 ** -4
+    assert np.linalg.norm(out[0] - out[1]) < 2.0 ** -28 * np.linalg.norm(out[0])
+
+
+@pytest.mark.parametrize("name", ["c5_xpinn_inverse_diffusion", "burgers_st_xpinn_4x4", "ns_cpinn_kovasznay"])
+def test_items_run_in_float32_against_oracle(name):
+    """Loss weights of 2^-90 send every work item through the float32 run, on
+    every operator and kind of item: the gradient against the oracle's, scaled
+    by 2^90, within the bars of compare."""
+    prob = W.make_problem(name, seed=0, scale=0.02 if name.startswith("c5") else 0.2)
+    params = _params(prob, 11)
+    ref = oracle.loss_and_grad(prob, params)
+    w = [s.loss_w for s in prob.subdomains]
+    for s in prob.subdomains:
+        s.loss_w = tuple(float(np.float32(v)) * 2.0 ** -90 for v in s.loss_w)
+    _say(f"{name}: loss weights times 2^-90")
+    pb, lt, g = run(prob, params)
+    lt = lt.astype(np.float64)
+    lt[:, 0] *= 2.0 ** 90
+    for s, v in zip(prob.subdomains, w):
+        s.loss_w = v
+    compare(prob, params, lt, [x.astype(np.float64) * 2.0 ** 90 for x in g], ref=ref)
+    pb.close()
