@@ -239,6 +239,8 @@ class Problem:
         """The subdomain of every flat parameter (device tensor)."""
         if self._sd_of is None:
             self._sd_of = torch.as_tensor(np.repeat(np.arange(self.n_sd), self.n_params), device=self.device)
+        # read on whichever stream the backward pass runs: its memory waits for that too
+        self._sd_of.record_stream(torch.cuda.current_stream(self.device))
         return self._sd_of
 
     def split(self, flat):

@@ -1104,3 +1104,29 @@ def test_items_run_in_float32_against_oracle(name):
         s.loss_w = v
     compare(prob, params, lt, [x.astype(np.float64) * 2.0 ** 90 for x in g], ref=ref)
     pb.close()
+
+
+def test_backward_on_another_stream_outlives_the_problem():
+    """The index that scales the gradient is kept by the problem and read on the
+    stream of the backward pass: once the problem is gone its memory is not
+    given out again before that stream has read it."""
+    prob = W.c1_cpinn_poisson(seed=0, scale=0.1)
+    pb = ddpinn.Problem(prob, fused=True)
+    flat = torch.from_numpy(np.concatenate(_params(prob, 3))).cuda().requires_grad_(True)
+    ddpinn.DDPLoss.apply(flat, pb).sum().backward()
+    index = pb.subdomain_of_param()
+    ptr, n, want = index.data_ptr(), index.numel(), flat.grad.clone()
+    flat.grad = None
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        loss = ddpinn.DDPLoss.apply(flat, pb).sum()
+        torch.cuda.synchronize()
+        pb.close()
+        torch.cuda._sleep(200_000_000)
+        loss.backward()
+    del index, loss, pb
+    got = [torch.empty(n, dtype=torch.int64, device="cuda") for _ in range(4)]
+    assert ptr not in [t.data_ptr() for t in got]
+    torch.cuda.synchronize()
+    assert torch.equal(flat.grad, want)
