@@ -165,8 +165,9 @@ int ddp_set_option(ddp_problem* p, int option, int64_t value);
  * one GPU (the paper's one rank per subdomain becomes one persistent launch
  * over all of them).
  * Validate, pack points and parameters into device memory, build the work
- * list, and (fused = 1) capture one training step as a HIP graph on
- * hip_stream (a hipStream_t, or NULL for the null stream).  fused = 0 selects
+ * list, and (fused = 1) capture one training step as a HIP graph for
+ * hip_stream (a hipStream_t, or NULL for the null stream); a graph of ten steps
+ * is captured by the first ddp_step of ten or more.  fused = 0 selects
  * the per-subdomain path: the same kernels launched once per subdomain,
  * without the persistent schedule or a graph.  Parameters start at zero;
  * set them with ddp_set_params.  Topology calls fail with DDP_ESTATE after. */

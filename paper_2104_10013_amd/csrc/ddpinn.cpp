@@ -146,8 +146,8 @@ struct ddp_problem {
   int* d_sd_net = nullptr;
   int *d_sd_loss_ptr = nullptr, *d_loss_rows = nullptr;
   int64_t* d_row_prow = nullptr;
-  // the fused step as graphs: one step, and kGraphSteps in a row (a graph
-  // launch costs 8.6 us between two steps)
+  // the fused step as graphs: one step, and (made on first use) kGraphSteps in
+  // a row (a graph launch costs 8.6 us between two steps)
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
   std::vector<void*> allocations;       // static buffers
@@ -921,9 +921,29 @@ int make_side_stream(ddp_problem* p, int* w) {
   return DDP_OK;
 }
 
+// Training steps as a graph: captured on a private stream, replayed on the
+// caller's stream.
+int make_graph(ddp_problem* p, int i) {
+  if (!p->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
+  HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
+  int rc = DDP_OK;
+  for (int s = 0; s < (i == 0 ? 1 : kGraphSteps) && rc == DDP_OK; ++s)
+    rc = enqueue_step(p, p->cap_stream, 1, nullptr, p->d_loss);
+  hipGraph_t g = nullptr;
+  hipError_t e = hipStreamEndCapture(p->cap_stream, &g);
+  if (rc) {
+    if (g) hipGraphDestroy(g);
+    return rc;
+  }
+  if (e != hipSuccess) return fail(DDP_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
+  p->graph[i] = g;
+  HIP_TRY(hipGraphInstantiate(&p->graph_exec[i], p->graph[i], nullptr, nullptr, 0));
+  return DDP_OK;
+}
+
 // Build the work plan for the current options and (re)create everything that
 // depends on it: work items, gradient / loss partial rows, row lists, the
-// activation stash, work counters and (graphs) the step graphs.
+// activation stash, work counters and (graphs) the graph of one step.
 int install_plan(ddp_problem* p, bool graphs = true) {
   const int n_sd = (int)p->sds.size();
   p->plan_ok = false;
@@ -975,23 +995,7 @@ int install_plan(ddp_problem* p, bool graphs = true) {
   HIP_TRY(hipMemset(p->d_loss_part, 0, std::max<size_t>(1, p->titems.size() * kLossTerms) * sizeof(float)));
   HIP_TRY(hipDeviceSynchronize());
   if (p->fused && graphs) {
-    // the training step as graphs: captured on a private stream, replayed on
-    // the caller's stream
-    if (!p->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
-    for (int i = 0; i < 2; ++i) {
-      HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-      for (int s = 0; s < (i == 0 ? 1 : kGraphSteps) && rc == DDP_OK; ++s)
-        rc = enqueue_step(p, p->cap_stream, 1, nullptr, p->d_loss);
-      hipGraph_t g = nullptr;
-      hipError_t e = hipStreamEndCapture(p->cap_stream, &g);
-      if (rc) {
-        if (g) hipGraphDestroy(g);
-        return rc;
-      }
-      if (e != hipSuccess) return fail(DDP_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-      p->graph[i] = g;
-      HIP_TRY(hipGraphInstantiate(&p->graph_exec[i], p->graph[i], nullptr, nullptr, 0));
-    }
+    if ((rc = make_graph(p, 0))) return rc;
   }
   p->plan_ok = true;
   return DDP_OK;
@@ -1099,7 +1103,7 @@ namespace {
 
 // The autotuner's search: every candidate plan timed over iters passes, the
 // three fastest again over three interleaved rounds; best receives the
-// winner.  Leaves the last candidate installed, without its step graphs.
+// winner.  Leaves the last candidate installed, without its step graph.
 int autotune_search(ddp_problem* p, int iters, hipEvent_t* ev, int64_t* best, float* best_ms) {
   const int64_t chunks[] = {256, 512, 1024, 2048};
   const int ipss[] = {1, 2, 4, 8};
@@ -1323,12 +1327,33 @@ int ddp_loss_and_grad_static(ddp_problem* p, float* loss_terms, float* grad) {
   return enqueue_step(p, p->stream, 0, grad, loss_terms ? loss_terms : p->d_loss, &b);
 }
 
+}  // extern "C"
+
+namespace {
+
+// The graph of several steps is made by the first call that has that many, so
+// that a problem whose gradients alone are asked for does not pay for it; not
+// while the caller's stream is capturing, when the launch itself is refused.
+bool may_take_long_graph(const ddp_problem* p) {
+  if (p->graph_exec[1]) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(p->stream, &st) == hipSuccess) return st == hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+}  // namespace
+
+extern "C" {
+
 int ddp_step(ddp_problem* p, int n_steps, float* loss_terms) {
   if (int rc = check_final(p)) return rc;
   if (n_steps < 0) return fail(DDP_EINVAL, "negative step count");
   for (int s = 0; s < n_steps;) {
     if (p->fused) {
-      const int many = n_steps - s >= kGraphSteps;
+      const int many = n_steps - s >= kGraphSteps && may_take_long_graph(p);
+      if (many && !p->graph_exec[1])
+        if (int rc = make_graph(p, 1)) return rc;
       HIP_TRY(hipGraphLaunch(p->graph_exec[many], p->stream));
       s += many ? kGraphSteps : 1;
     } else {

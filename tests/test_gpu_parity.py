@@ -1130,3 +1130,25 @@ def test_backward_on_another_stream_outlives_the_problem():
     assert ptr not in [t.data_ptr() for t in got]
     torch.cuda.synchronize()
     assert torch.equal(flat.grad, want)
+
+
+def test_long_steps_after_a_new_plan():
+    """The graph of several steps belongs to the plan it was made under: after
+    autotune the next long call makes its own, and the bits are those of single
+    steps under the same plan."""
+    prob = W.c1_cpinn_poisson(seed=0, scale=0.1)
+    pb = ddpinn.Problem(prob, fused=True)
+    pb.step(12)
+    at = pb.get_state()
+    plan = pb.autotune(iters=1)
+    other = ddpinn.Problem(prob, fused=True, **plan)
+    other.set_state(at)
+    pb.step(25)
+    for _ in range(25):
+        other.step(1)
+    a, b = pb.get_state(), other.get_state()
+    assert a["t"] == b["t"] == 37
+    assert np.array_equal(np.concatenate(a["params"]), np.concatenate(b["params"]))
+    assert np.array_equal(a["m"], b["m"]) and np.array_equal(a["v"], b["v"])
+    pb.close()
+    other.close()
