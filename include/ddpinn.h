@@ -182,11 +182,13 @@ int ddp_finalize(ddp_problem* p, void* hip_stream, int fused);
  * fastest and rebuild the step graph with it.  Parameters and Adam state are
  * not changed.  cache_path (may be NULL) is a JSON-lines file of earlier
  * choices keyed by a signature of the problem (operator, interface methods, fused or
- * per-subdomain path, widths, depths, point counts, CU count): a hit skips
+ * per-subdomain path, widths, depths, point counts, CU count) and of the
+ * library's kernels and plan rules: a hit skips
  * the search, a miss appends the new choice.  choice (may be NULL) receives
  * the 6 chosen values (points per item, items per workgroup, workgroups per
- * compute unit, DDP_OPT_RECOMPUTE (0), concurrent launches, tail share).  Not safe to call while the caller's stream runs other
- * work on this problem. */
+ * compute unit, DDP_OPT_RECOMPUTE (0), concurrent launches, tail share).
+ * Not safe to call while the caller's stream runs other work on this
+ * problem. */
 int ddp_autotune(ddp_problem* p, int iters, const char* cache_path, int64_t* choice);
 
 /* Number of parameters of subdomain sd (its networks' canonical layouts, concatenated). */

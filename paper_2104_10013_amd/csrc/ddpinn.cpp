@@ -1001,6 +1001,12 @@ int install_plan(ddp_problem* p, bool graphs = true) {
   return DDP_OK;
 }
 
+// To be raised whenever the train kernels, the rule for the items' lengths or
+// the meaning of an option changes, so that plans found before are searched for
+// again (1, not hashed: float32 MFMA kernels, 4 items a workgroup, one launch
+// after the other).
+constexpr int kPlanRevision = 2;
+
 // FNV-1a hash of everything the best plan depends on
 uint64_t problem_signature(const ddp_problem* p) {
   uint64_t h = 1469598103934665603ull;
@@ -1010,6 +1016,9 @@ uint64_t problem_signature(const ddp_problem* p) {
       h *= 1099511628211ull;
     }
   };
+  mix(kPlanRevision);
+  mix(p->occupancy);
+  for (const ddp_problem::Launch& l : p->launches) mix(l.occupancy);
   mix(p->pde);
   mix(p->method);
   mix(p->fused);

@@ -1152,3 +1152,42 @@ def test_long_steps_after_a_new_plan():
     assert np.array_equal(a["m"], b["m"]) and np.array_equal(a["v"], b["v"])
     pb.close()
     other.close()
+
+
+def _signature_before_revisions(prob, fused):
+    """The autotune cache key of libraries that did not hash their revision."""
+    h = 1469598103934665603
+
+    def mix(v):
+        nonlocal h
+        for b in int(v).to_bytes(8, "little", signed=True):
+            h = (h ^ b) * 1099511628211 % 2 ** 64
+
+    for v in (ddpinn._PDE[prob.pde], ddpinn._METHOD[prob.method], fused,
+              torch.cuda.get_device_properties(0).multi_processor_count, prob.n_sd):
+        mix(v)
+    for s in prob.subdomains:
+        aux = s.aux_widths is not None
+        for w in list(s.widths) + (list(s.aux_widths) if aux else []):
+            mix(w)
+        for v in (ddpinn._ACT[s.act], s.adaptive, len(s.res_xy), len(s.bnd_xy), len(s.aux_xy) if aux else 0):
+            mix(v)
+    for e in prob.interfaces:
+        for v in (e.a, e.b, len(e.xy), ddpinn._METHOD[e.method or prob.method]):
+            mix(v)
+    return h
+
+
+def test_autotune_does_not_take_a_plan_found_for_other_kernels(tmp_path):
+    """A choice cached by a library with other kernels is searched for again."""
+    prob = W.c1_cpinn_poisson(seed=0, scale=0.1)
+    cache = tmp_path / "tune.jsonl"
+    cache.write_text('{"signature": "%016x", "chunk_points": 4096, "items_per_slot": 3, "blocks_per_cu": 1, '
+                     '"recompute": 1, "concurrent": 0, "tail": 7, "ms": 0.1}\n' % _signature_before_revisions(prob, 1))
+    pb = ddpinn.Problem(prob, fused=True)
+    choice = pb.autotune(iters=1, cache_path=cache)
+    assert choice["chunk_points"] != 4096 and choice["tail"] != 7
+    lines = cache.read_text().splitlines()
+    assert len(lines) == 2
+    assert pb.autotune(iters=1, cache_path=cache) == choice and cache.read_text().splitlines() == lines
+    pb.close()
