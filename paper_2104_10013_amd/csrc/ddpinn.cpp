@@ -889,7 +889,7 @@ namespace {
 // depends on the streams made before it; two on one queue run their kernels
 // one after the other.  So up to kSideTries streams are tried until a kernel on
 // one is seen to run beside a kernel on p->stream (w: two device ints).  Fixed
-// by chance instead: 5 ragged boxes of 20 to 100 took 121 us side by side, or 173
+// by chance instead: 6 ragged boxes of 9 to 112 took 121 us side by side, or 173
 // on one queue, by the number of streams in the process.
 constexpr int kSideTries = 4;
 

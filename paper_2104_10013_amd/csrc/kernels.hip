@@ -129,24 +129,26 @@ __device__ __forceinline__ float group_sum(float v) {
 // FP32 contractions on the bf16 matrix cores.  A float32 x is the sum of three
 // bf16 values, hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid) (both
 // differences are exact), and a product of two such sums keeps the six terms
-// of relative size 2^-16 and up:
+// of relative size 2^-17 and up:
 //     hi hi + (hi mid + mid hi) + (mid mid + hi lo + lo hi),
-// accumulated in float32; what is left out is below 2^-25 of the product,
-// under half a float32 rounding.  Six 16x16x32 bf16 MFMAs (16.8 cycles each,
-// measured) replace eight 16x16x4 float32 ones (32 cycles each) per 32 terms,
-// and with eight times fewer float32 additions the measured error against
-// float64 is smaller too (2-norm of 16x16 blocks: K = 32 3.6e-8 against
-// 1.05e-7, K = 96 1.2e-7 / 1.8e-7, K = 256 2.7e-7 / 3.0e-7).
+// accumulated in float32; what is left out, mostly mid lo + lo mid, is at most
+// about 2^-24 of the product, as much as one float32 rounding.  Six 16x16x32
+// bf16 MFMAs (16.8 cycles each, measured) replace eight 16x16x4 float32 ones (32
+// cycles each) per 32 terms, and with eight times fewer float32 additions the
+// measured error against float64 is smaller too (2-norm of 16x16 blocks: K = 32
+// 3.6e-8 against 1.05e-7, K = 96 1.2e-7 / 1.8e-7, K = 256 2.7e-7 / 3.0e-7).
+// What is no such sum (infinities, and the last bits of values below 2^-109) is
+// left to the float32 run of Plain.
 __device__ __forceinline__ f4 mma(b8 a, b8 b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 // (the same output layout: lane group g holds element g of the four terms)
 __device__ __forceinline__ f4 mma_f32(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // The split of two values: the remainders x - hi come from the bf16 dot
 // product x + (hi0, hi1) . (-1, 0), exact like the subtraction (checked on
-// random values over the range of the exponents) and without unpacking the
-// parts first: 7 instructions a pair instead of 11.  (The constants are made
-// opaque: folded into the instruction as an inline literal they land in the
-// wrong half.)
+// random values over the range of the exponents; an infinite value makes both
+// remainders NaN) and without unpacking the parts first: 7 instructions a pair
+// instead of 11.  (The constants are made opaque: folded into the instruction as
+// an inline literal they land in the wrong half.)
 __device__ __forceinline__ void split2(float x0, float x1, b2& h, b2& m, b2& l) {
   unsigned c0 = 0x0000bf80u, c1 = 0xbf800000u;   // (-1, 0) and (0, -1)
   asm("" : "+s"(c0));
@@ -173,7 +175,7 @@ __device__ __forceinline__ b8 join(b4 x, b4 y) { return b8{x[0], x[1], x[2], x[3
 // s1 = 4e/(1+e)^2 (no cancellation for large |a|); below 0.7, where 1 - e
 // cancels, t = |a| + |a|^3 P(a^2) (as in tanh_value) and s1 = 1 - t^2.  Without
 // that branch a step is 4 to 10 % faster, but the error of one gradient against 64
-// bits is 1.3e-7 instead of 7e-8 (strips of 50) and, repeating at every step,
+// bits is 1.3e-7 instead of 7e-8 (8 strips of 50) and, repeating at every step,
 // it adds up: after 20 Adam steps of the 16-subdomain mix 1.57 against 0.89 times
 // the float32-MFMA step's (geometric means of 7 seeds).
 __device__ __forceinline__ void tanh_s1(float a, float& t, float& s1) {
@@ -432,7 +434,7 @@ constexpr int split_matrix_bytes(int wp) { return 6 * wp * wp; }
 // registers, one sum over the waves at the end of the layer) instead of a
 // share of the blocks over all 64 points: classes up to 48, where the blocks
 // take at most 36 registers.  No barriers between the streams, and each
-// fragment read from LDS serves a row or column of blocks.  (3 strips of 20:
+// fragment read from LDS serves a row or column of blocks.  (16 networks of 20:
 // 169 us a step with shared blocks, 159 with private ones.)
 constexpr bool private_dw(int wp) { return wp <= 48; }
 constexpr int stage_bytes(int wp) { return 2 * 3 * 2 * TP * (wp + 4); }
@@ -757,9 +759,12 @@ struct Tile {
   // [WP + 4] bf16, a row per point of one stream and the neurons along it, so that a lane writes its four
   // neurons of a block in 8 bytes; the operand fragments, which run along the
   // points, come out of the transposing LDS read (ds_read_b64_tr_b16).  LDS
-  // takes writes 16 lanes and 32 banks at a time: rows an odd multiple of 8
-  // bytes apart put the 16 points of a lane group on all 32 banks (6 cycles a
-  // wave and 8-byte write, measured; 16 with rows of WP neurons).
+  // takes 16 lanes and 32 banks at a time: rows an odd multiple of 8 bytes apart
+  // put the writes of the 16 points of a lane group on all 32 banks (6 cycles a
+  // wave and 8-byte write, measured; 16 with rows of WP neurons).  The reads, 4
+  // rows of 32 bytes at a time, still collide two ways (four at class 64): bank
+  // conflicts are a quarter of the LDS instructions' cycles on the 16-subdomain
+  // mix.
   static constexpr int ROW = 2 * (WP + 4);      // bytes
   static constexpr int PART = SROWS * ROW;      // bytes of one part of one operand
   __device__ __forceinline__ static void stage_put(char* base, int row, int g, const f4 (&X)[MB]) {
@@ -1101,7 +1106,7 @@ struct Tile {
     float* sSl = sRed + kWaves * kLossTerms;   // [kWaves] slope-gradient sums
     // the reverse pass follows the forward one here, and what it needs of the
     // last hidden layer is h^D, at hand, and a^D: of that layer, the value
-    // stream alone is stashed.  (Three space-time strips of 20 wide 147 -> 130
+    // stream alone is stashed.  (16 space-time boxes of 20 wide 147 -> 130
     // us a step, 50 wide 208 -> 203; a^D in registers as well spills and takes
     // that back.)
     constexpr bool HOLD = PHASE == PH_ALL && !GA;
@@ -2094,7 +2099,7 @@ struct Plain {
   // follows it as there).  Not inlined, and everything read again from the
   // kernel's arguments, for the registers of the path that matters: inlined a
   // step of 4 networks of 20 took 31.9 instead of 30.3 us, as a switch inside
-  // Tile 32.6 (and 3 strips of 50 wide 275 instead of 216); so it takes 30.8
+  // Tile 32.6 (and 8 strips of 50 wide 275 instead of 216); so it takes 30.8
   // (and the strips 212).
   __device__ __attribute__((noinline, cold)) static void item(const Args* args, int index, Lds* lds, int nb_at,
                                                               float* slot) {
@@ -2235,18 +2240,18 @@ __device__ __forceinline__ void dispatch(const KArgs& ka, const Item& it, const 
 // turn (per hidden layer, wave and tile of class 64: 582 MFMAs of 16.8 cycles
 // and 1960 vector instructions, a third of them splitting float32 into bf16
 // parts; two waves share a SIMD and overlap only in part), for narrow networks
-// the stash traffic (3 strips of 20 wide: about 4 of the 5 TB/s a copy
+// the stash traffic (16 boxes of 20 wide: about 4 of the 5 TB/s a copy
 // reaches) and latency, for a few tiles latency alone.  Train + reduce a step,
 // with float32 MFMAs and everything stashed twice -> now: 16-subdomain mix of
-// 143,157 points 719 -> 499 us, 9 subdomains of 60 wide 536 -> 364, 3 strips of
-// 20 184 -> 145, 4 of 24 38.6 -> 30.5.
+// 143,157 points 720 -> 495 us, 9 subdomains of 60 wide 535 -> 363, 16 boxes of
+// 20 184 -> 142, 4 of 20 38.5 -> 30.8.
 //
 // Persistent kernel: workgroup b starts with item b of the list (descending
 // cost), then workgroups pull items from a device counter until it is drained;
 // where every item has a workgroup the counter is not touched.  A first pull
 // cost a round trip to memory (the counter is shared by all L2 caches) with
-// nothing to hide it: 30.4 -> 29.2 us a step for 4 networks of 24 (one tile an
-// item), 143 -> 142 for 3 of 20, 457 -> 453 for the 16-subdomain mix.
+// nothing to hide it: 30.4 -> 29.2 us a step for 4 networks of 20 (one tile an
+// item), 143 -> 142 for 16 of 20, 457 -> 453 for the 16-subdomain mix.
 // Widths up to 80 fit two waves per SIMD (<= 256 registers); wider classes
 // run one wave per SIMD.
 template <int WPMAX>
@@ -2418,9 +2423,11 @@ __device__ __forceinline__ int find_net(const int64_t* net_poff, int n, int64_t 
 // time, then thread t takes entry t's four sums from LDS in order and updates
 // its parameter.  The order does not depend on timing.  Against a thread per
 // parameter that walks its rows one at a time, the offset of each found from
-// the parameter's, and the loss sums in block 0 (us): 3 space-time strips of 20
-// 17.4 -> 11.1, 9 subdomains of 60 20.2 -> 13.7, the 16-subdomain Poisson mix
-// 19.9 -> 17.1, 10 inverse subdomains 41 -> 28, 4 of 24 6.2 -> 6.0.
+// the parameter's, and the loss sums in block 0 (us): 16 space-time boxes of 20
+// 17.4 -> 10.6, 8 strips of 50 18.0 -> 13.5, 9 subdomains of 60 20.2 -> 12.7, the
+// 16-subdomain Poisson mix 20.5 -> 15.9, 10 adaptive pairs of 80 30 -> 22, 10
+// inverse pairs 28.7 -> 27.8 (99 with the autotuned plan, whose items are
+// shorter), 4 of 20 6.7 -> 5.8.
 constexpr int kRedRows = 8;
 
 __global__ __launch_bounds__(kRedParams) void k_reduce(RArgs ra) {
@@ -2563,14 +2570,14 @@ __global__ __launch_bounds__(256) void k_pack(const float* src, float* params, f
 // Each pair's outputs go to LDS and are summed in the order of the slots.
 // (One thread a point, with the activations in scratch memory, took 3.6 ms for
 // 40,401 points of 16 networks up to 80 wide and 11.1 ms for 10^6 points of 5 x
-// 60, the copies to the device included; now 0.10 and 1.24 ms, mostly copies.)
+// 60, the copies to the device included; now 0.10 and 1.20 ms, mostly copies.)
 constexpr int kEvalPts = 256;            // points per block at most
 
-// value of hidden layer k's activation; sin and cos as in training (sin_cos),
-// tanh from the library
-// tanh to about an ulp without a branch: 1 - 2 / (exp(2|y|) + 1), and below
-// 0.7, where that would cancel, y + y^3 P(y^2) with P fitted to
-// (tanh(y)/y - 1)/y^2 (relative error 1.5e-8; both together 1.4e-7 at most)
+// Activations of the evaluation: sin and cos as in training (sin_cos), tanh
+// without a branch: 1 - 2 / (exp(2|y|) + 1), and below 0.7, where that would
+// cancel, y + y^3 P(y^2) with P fitted to (tanh(y)/y - 1)/y^2 (tanh to 2.0e-8 in
+// exact arithmetic).  Largest relative error over every float from 2^-30 to
+// 30: 8.8e-8 below 0.7, 1.58e-7 above (tanh_s1: 8.8e-8 and 2.04e-7).
 __device__ __forceinline__ float tanh_value(float y) {
   const float a = fabsf(y), u = a * a;
   float p = -0.0051385928f;
@@ -2665,7 +2672,7 @@ __device__ __forceinline__ void eval_net(const float* K, const NetDesc& nd, int 
 // two waves per SIMD: 64 points of up to 80 neurons fit the registers, 32 of
 // the wider classes
 // (activations: the library's tanhf, a branch for each, took 43 us of kernel
-// for the 40,401 points and 446 for the 10^6; tanh_value 39 and 425)
+// for the 40,401 points and 446 for the 10^6; tanh_value 39 and 414)
 __global__ __launch_bounds__(NT, 2) void k_eval(const float* kparams, const NetDesc* nets, const int* sd_net, int n_sd,
                                                 int n, int pb, const float* xy, const int* owner, float* out,
                                                 int n_cols) {
