@@ -44,7 +44,8 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
 constexpr int TP = kTilePts;      // points per tile
-constexpr float kTinySeed = 0x1p-80f;   // items with nonzero output seeds below this run in float32 (Plain)
+constexpr float kTinySeed = 0x1p-80f;   // items with nonzero output seeds below this run in float32 (Plain); at this
+                                        // size the split loses nothing yet, at 2^-90 1e-9 of a gradient
 constexpr int NT = 64 * kWaves;   // threads per workgroup
 
 // One 16-byte-per-lane store into the activation stash, followed by wait
@@ -879,13 +880,19 @@ struct Tile {
     for (int c = 1; c < DO; ++c) f = f && finite4(u[c]);
     return f;
   }
-  __device__ __forceinline__ static bool tiny_seeds(const float (&ub)[DO][4]) {
+  // Seeds that are tiny because the loss or its derivatives are, not because
+  // the item's term has a small weight beside the subdomain's others (then its
+  // last bits do not matter, and the term may stand for one left out).
+  __device__ __forceinline__ static bool tiny_seeds(const Item& it, const NetDesc& nd, const float (&ub)[DO][4]) {
     float top = 0.f;
 #pragma unroll
     for (int c = 0; c < DO; ++c)
 #pragma unroll
       for (int s = 0; s < 4; ++s) top = fmaxf(top, fabsf(ub[c][s]));
-    return top > 0.f && top < kTinySeed;
+    const float wi = fmaxf(nd.loss_w[2], nd.loss_w[3]);
+    const float w = it.kind == KIND_RES ? nd.loss_w[1] : it.kind == KIND_IFACE ? wi : nd.loss_w[0];
+    const float most = fmaxf(fmaxf(nd.loss_w[0], nd.loss_w[1]), wi);
+    return top > 0.f && top < kTinySeed && top * (most / w) < kTinySeed;
   }
 
   // values this network contributes on an interface: u (DO) then the normal
@@ -1200,7 +1207,7 @@ struct Tile {
       // ---- loss terms and output seeds
       float ub[DO][4], loss[kLossTerms], kb[3];
       epilogue<MODE>(ka, it, nd, tp, valid, tgt, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss, kb);
-      if (!finite_streams(u) || !finite4(loss) || tiny_seeds(ub)) *sBad = 1;
+      if (!finite_streams(u) || !finite4(loss) || tiny_seeds(it, nd, ub)) *sBad = 1;
 #pragma unroll
       for (int t = 0; t < kLossTerms; ++t) {
         const float v = row_sum16(loss[t]);   // (the same in every lane group)

@@ -1191,3 +1191,17 @@ def test_autotune_does_not_take_a_plan_found_for_other_kernels(tmp_path):
     assert len(lines) == 2
     assert pb.autotune(iters=1, cache_path=cache) == choice and cache.read_text().splitlines() == lines
     pb.close()
+
+
+def test_a_term_of_tiny_weight_beside_others_keeps_its_bits():
+    """Interface terms weighted 2^-100 beside others of weight 1 have tiny seeds,
+    but not a tiny loss: their items run as with weight 1, with the same bits of
+    every loss term."""
+    terms = []
+    for w in (1.0, 2.0 ** -100):
+        prob = W.custom_box_problem("xpinn", "poisson2d", 2, 2, [[2] + [w_] * 3 + [1] for w_ in (20, 32, 60, 80)],
+                                    [150, 70, 64, 130], n_bnd_seg=9, n_iface=17, seed=3, loss_w=(1.0, 1.0, w, w))
+        pb, lt, g = run(prob, _params(prob, 5))
+        terms.append(lt[:, 1:])
+        pb.close()
+    assert np.array_equal(terms[0], terms[1])
