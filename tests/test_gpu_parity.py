@@ -1205,3 +1205,44 @@ def test_a_term_of_tiny_weight_beside_others_keeps_its_bits():
         terms.append(lt[:, 1:])
         pb.close()
     assert np.array_equal(terms[0], terms[1])
+
+
+@pytest.mark.parametrize("name,scale", [("c2_xpinn_poisson", 0.05), ("c5_xpinn_inverse_diffusion", 0.01),
+                                        ("c5_table4_adaptive", 0.05)])
+def test_float32_items_on_every_path(name, scale):
+    """An infinite weight sends items through the float32 run: the static-scratch
+    entry (fewer workgroups), side-by-side launches and one after the other, a
+    repeat and an Adam step leave the same bits, the per-subdomain path the same
+    finite entries; the loss is reported as not finite, and finite parameters
+    afterwards give the bits they gave before."""
+    prob = W.make_problem(name, seed=0, scale=scale)
+    params = _params(prob, 9)
+    bad = [p.copy() for p in params]
+    off, w = _hidden(prob.subdomains[0].widths, 2)
+    bad[0][off + w + 2] = np.inf
+    outs = []
+    for kw in (dict(concurrent=1), dict(concurrent=0), dict(fused=False)):
+        _say(f"{name}: {kw}")
+        pb = ddpinn.Problem(prob, **kw)
+        pb.set_params(params)
+        lt0, g0 = (x.clone() for x in pb.loss_and_grad())
+        pb.set_params(bad)
+        for entry in (pb.loss_and_grad, pb.loss_and_grad_static, pb.loss_and_grad):
+            lt, g = entry()
+            outs.append((kw, lt.cpu().numpy(), g.cpu().numpy()))
+        with pytest.raises(ddpinn.DDPError) as e:
+            pb.sync()
+        assert e.value.code == ddpinn.DDP_ENONFINITE
+        step = pb.step(1).cpu().numpy()
+        assert np.array_equal(step, outs[-1][1], equal_nan=True)
+        pb.set_params(params)
+        lt, g = pb.loss_and_grad()
+        assert torch.equal(lt, lt0) and torch.equal(g, g0)
+        pb.close()
+    _, lt0, g0 = outs[0]
+    assert np.isfinite(g0).any() and not np.isfinite(g0).all()
+    for kw, lt, g in outs:
+        if kw.get("fused", True):
+            assert np.array_equal(lt, lt0, equal_nan=True) and np.array_equal(g, g0, equal_nan=True)
+        else:
+            assert np.array_equal(np.isfinite(lt), np.isfinite(lt0)) and np.array_equal(np.isfinite(g), np.isfinite(g0))
