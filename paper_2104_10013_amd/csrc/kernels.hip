@@ -44,8 +44,9 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
 constexpr int TP = kTilePts;      // points per tile
-constexpr float kTinySeed = 0x1p-80f;   // items with nonzero output seeds below this run in float32 (Plain); at this
-                                        // size the split loses nothing yet, at 2^-90 1e-9 of a gradient
+// Items with nonzero output seeds below this run in float32 (Plain): the split
+// loses nothing yet there, and 1e-9 of a gradient at 2^-90.
+constexpr float kTinySeed = 0x1p-80f;
 constexpr int NT = 64 * kWaves;   // threads per workgroup
 
 // One 16-byte-per-lane store into the activation stash, followed by wait
@@ -880,19 +881,13 @@ struct Tile {
     for (int c = 1; c < DO; ++c) f = f && finite4(u[c]);
     return f;
   }
-  // Seeds that are tiny because the loss or its derivatives are, not because
-  // the item's term has a small weight beside the subdomain's others (then its
-  // last bits do not matter, and the term may stand for one left out).
-  __device__ __forceinline__ static bool tiny_seeds(const Item& it, const NetDesc& nd, const float (&ub)[DO][4]) {
+  __device__ __forceinline__ static bool tiny_seeds(const float (&ub)[DO][4]) {
     float top = 0.f;
 #pragma unroll
     for (int c = 0; c < DO; ++c)
 #pragma unroll
       for (int s = 0; s < 4; ++s) top = fmaxf(top, fabsf(ub[c][s]));
-    const float wi = fmaxf(nd.loss_w[2], nd.loss_w[3]);
-    const float w = it.kind == KIND_RES ? nd.loss_w[1] : it.kind == KIND_IFACE ? wi : nd.loss_w[0];
-    const float most = fmaxf(fmaxf(nd.loss_w[0], nd.loss_w[1]), wi);
-    return top > 0.f && top < kTinySeed && top * (most / w) < kTinySeed;
+    return top > 0.f && top < kTinySeed;
   }
 
   // values this network contributes on an interface: u (DO) then the normal
@@ -1207,7 +1202,7 @@ struct Tile {
       // ---- loss terms and output seeds
       float ub[DO][4], loss[kLossTerms], kb[3];
       epilogue<MODE>(ka, it, nd, tp, valid, tgt, sNb + tp * (PDE == PDE_INV ? 3 : DO + NEQ), sInv, u, ub, loss, kb);
-      if (!finite_streams(u) || !finite4(loss) || tiny_seeds(it, nd, ub)) *sBad = 1;
+      if (!finite_streams(u) || !finite4(loss) || tiny_seeds(ub)) *sBad = 1;
 #pragma unroll
       for (int t = 0; t < kLossTerms; ++t) {
         const float v = row_sum16(loss[t]);   // (the same in every lane group)
@@ -1696,6 +1691,16 @@ __device__ __forceinline__ bool nan_network(const KArgs& ka, const NetDesc& nd) 
   return nd.depth >= 2 && isnan((float)*reinterpret_cast<const __bf16*>(ka.kparams + nd.koff + L.k_w(2)));
 }
 
+// Whether the item's term has less than 2^-24 of the weight of another of its
+// subdomain: its seeds may be tiny for that alone, and the last bits of its
+// share are below those of the other's.  (A term weighted 1e-30 to leave it out
+// would otherwise have its items run again at every step.)
+__device__ __forceinline__ bool small_term(const Item& it, const NetDesc& nd) {
+  const float wi = fmaxf(nd.loss_w[2], nd.loss_w[3]);
+  const float w = it.kind == KIND_RES ? nd.loss_w[1] : it.kind == KIND_IFACE ? wi : nd.loss_w[0];
+  return w < 0x1p-24f * fmaxf(fmaxf(nd.loss_w[0], nd.loss_w[1]), wi);
+}
+
 // ---------------------------------------------------------------------------
 // The same item in float32 throughout, with sizes known at run time, for what
 // is no sum of three bf16 parts: infinities (a split one is infinity and NaN,
@@ -2102,6 +2107,26 @@ struct Plain {
     T::accum(R + L.g_slope() + k - 1, (v[0] + v[1]) + (v[2] + v[3]), first);
   }
 
+  // Whether the item's losses and first-layer gradients are finite: then it was
+  // sent here for its tiny seeds.
+  __device__ static bool finite_rows(const KArgs& ka, const Item& it, const NetDesc& nd, int* vote) {
+    const int tid = (int)threadIdx.x;
+    const bool pair = PDE == PDE_INV && nd.pair >= 0 && (it.kind == KIND_RES || it.kind == KIND_IFACE);
+    const float* R = ka.partial + it.prow;
+    float z = 0.f;
+    for (int t = tid; t < 4 * nd.wclass; t += NT) z = fmaf(T::device_load(R + t), 0.f, z);
+    if (pair)
+      for (int t = tid; t < 4 * ka.nets[nd.pair].wclass; t += NT) z = fmaf(T::device_load(R + nd.gsize + t), 0.f, z);
+    if (tid < kLossTerms) z = fmaf(T::device_load(ka.loss_part + (int64_t)it.lrow * kLossTerms + tid), 0.f, z);
+    if (tid == 0) *vote = 0;
+    __syncthreads();
+    if (!(z == 0.f)) *vote = 1;
+    __syncthreads();
+    const int v = __builtin_amdgcn_readfirstlane(*vote);
+    __syncthreads();
+    return v == 0;
+  }
+
   // dispatch of item idx (lds: the tile buffers; lds + nb_at: sNb and what
   // follows it as there).  Not inlined, and everything read again from the
   // kernel's arguments, for the registers of the path that matters: inlined a
@@ -2117,8 +2142,9 @@ struct Plain {
     const Item& it = ka.items[idx];
     const NetDesc& nd = ka.nets[it.q];
     if (nan_network(ka, nd)) return;
-    dma_landed();   // the rows are written again by other waves
+    dma_landed();   // the rows are read, and written again, by other waves
     __syncthreads();
+    if (small_term(it, nd) && finite_rows(ka, it, nd, reinterpret_cast<int*>(red))) return;
     float* sInv = sNb + 6 * TP;
     const IfaceDesc& ifd = ka.ifaces[it.kind == KIND_IFACE ? it.iface : 0];
     const NetDesc& nb = it.kind == KIND_IFACE ? ka.nets[it.side == 0 ? ifd.b_net : ifd.a_net] : nd;

@@ -1246,3 +1246,48 @@ def test_float32_items_on_every_path(name, scale):
             assert np.array_equal(lt, lt0, equal_nan=True) and np.array_equal(g, g0, equal_nan=True)
         else:
             assert np.array_equal(np.isfinite(lt), np.isfinite(lt0)) and np.array_equal(np.isfinite(g), np.isfinite(g0))
+
+
+def _boxes(pde, widths, acts, seed):
+    """A 4x2 or 2x1 box problem (the inverse problem: its cells) with the given
+    widths, three hidden layers, work items of several tiles with a ragged last
+    one, and interfaces between all of them."""
+    if pde == "inverse":
+        prob = W.c5_xpinn_inverse_diffusion(seed=3, scale=0.006)
+        rng = np.random.default_rng(seed)
+        for q, s in enumerate(prob.subdomains):
+            s.widths = [2] + [widths[q % len(widths)]] * 3 + [1]
+            s.aux_widths = [2] + [widths[(q + 3) % len(widths)]] * 2 + [1]
+            s.params = np.concatenate([W.glorot_params(rng, s.widths), W.glorot_params(rng, s.aux_widths)])
+    else:
+        out, coef = (3, (40.0,)) if pde == "ns2d_steady" else (1, (0.05,) if pde == "burgers1d" else ())
+        nx, ny = (4, 2) if len(widths) > 1 else (2, 1)
+        n = nx * ny
+        prob = W.custom_box_problem("cpinn" if seed % 2 else "xpinn", pde, nx, ny,
+                                    [[2] + [widths[q % len(widths)]] * 3 + [out] for q in range(n)],
+                                    [130 + 7 * q for q in range(n)], n_bnd_seg=9, n_iface=17, seed=seed, coef=coef)
+    return W.with_activations(prob, acts) if acts else prob
+
+
+@pytest.mark.parametrize("pde", ["poisson2d", "burgers1d", "ns2d_steady", "inverse"])
+@pytest.mark.parametrize("acts", [None, ("tanh", "sin", "tanh", "cos")])
+def test_every_kernel_and_class_against_oracle(pde, acts):
+    """Every train kernel with every width class it holds: one width at a time
+    (the kernel of that class), all widths at once (the groups up to 80 and up to
+    112), and the per-subdomain path (the widest kernel for all).  The compiler
+    holds values of the wide classes in accumulation registers or memory, and
+    has saved some under a partial mask of lanes, which gives errors of order
+    one: each kernel is checked by itself, at ten times the bar of the other
+    tests."""
+    for widths in [(w,) for w in (16, 32, 48, 64, 80, 96, 112)] + [(16, 112, 32, 96, 48, 80, 64, 20)]:
+        for seed in (1, 2):
+            prob = _boxes(pde, widths, acts, seed)
+            params = _params(prob, 13)
+            ref = oracle.loss_and_grad(prob, params)
+            for fused in (True, False) if len(widths) > 1 else (True,):
+                _say(f"{pde} {acts} widths {widths} seed {seed} fused {fused}")
+                pb, lt, g = run(prob, params, fused=fused, items_per_slot=1, chunk_points=4096)
+                compare(prob, params, lt, g, ref=ref, loss_rtol=1e-4, grad_rtol=1e-4)
+                pb.close()
+            if pde == "inverse":
+                break
